@@ -99,8 +99,9 @@ struct DevMem {
 // Device workspace of one batch of right-hand sides.
 struct Workspace {
     int prec = -1, NS = 0, B = 0;
+    int K = 0;            // residuals kept per right-hand side (iterations per block)
     bool check = false;   // laid out for the per-shift check (xs, rres, ysave)
-    DevMem r, tmp, p, ph, y, x0, tmp64, ap64, yacc, x0acc;
+    DevMem r, tmp, p, ph, y, x0, tmp64, ap64;
     DevMem xs, rres, ysave, sums, flags;   // per-shift check: x_i, residuals, saved y
     DevMem st_d;   // doubles of the MSState
     DevMem st_i;   // ints of the MSState
@@ -203,8 +204,9 @@ struct smpq_ctx {
     bool refining = false;          // inside a refinement solve, which has no check of its own
     double2 *cur_xs = nullptr;      // x_i accumulators of the solve in progress (check mode)
     bool trace = std::getenv("SMPQ_TRACE") != nullptr;   // one line per batch on stderr
-    // captured groups of kGroup CG iterations, one per accumulation variant; rebuilt when
-    // anything they capture (workspace, links, coefficients, solver settings) changes
+    // captured groups of kGroup CG iterations, one per position in the block and parity of the
+    // base direction's buffer; rebuilt when anything they capture (workspace, links,
+    // coefficients, solver settings) changes
     // [timed][variant]; the timed graphs carry event nodes around the stencil and update kernels
     hipGraphExec_t graphs[2][4] = {{nullptr, nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr, nullptr}};
     long long graph_gen[2][4] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
@@ -294,13 +296,21 @@ void spinor_from_device(const smpq_ctx *c, const std::vector<double> &stage, int
 
 
 // The CG body runs in groups of kGroup iterations; the host reads the number of active
-// right-hand sides after each group.  FP32 path: the first iterations build most of y and x0
-// (the residual falls by ~10^3 in the first 50 iterations at these condition numbers), so they
-// accumulate straight into FP64: y for the first kDirectY iterations, x0 until the first
-// reliable update.  Later contributions go to FP32 running sums, folded into FP64 at the end
-// of every group (y) and at every reliable update (x0).
+// right-hand sides after each group.  The shifted systems, y and x0 are updated once per block of K
+// iterations from the residuals kept since the last block, and always before a reliable update and
+// at the end, all sums into y and x0 in FP64.
 constexpr int kGroup = 10;
-constexpr int kDirectY = 30;   // a multiple of kGroup
+constexpr size_t kUnit = 16;   // bytes of a storage unit (double2 or float4)
+
+// Iterations per block, longest first.  K > 1 needs a second buffer for the base direction.  With
+// K = 20 the update moves, per site and iteration in FP32 with n active shifts, 134 + 9.6 n bytes
+// (K = 10: 173 + 19 n; K = 1, which takes the memory of a residual updated in place:
+// 864 + 192 n, as much as an update in every iteration).  A longer block buys little more and
+// holds K vectors per right-hand side.
+constexpr int kBlockIters[] = {20, 10, 5, 2, 1};
+// Sites x right-hand sides that keep the kernels busy: below this a batch is not made smaller for a
+// longer block.
+constexpr long long kFillSites = 4 << 20;
 
 // Internal precision codes follow smpq_precision: 0 FP64; 1 FP32 body; 2 / 3 FP32 body with
 // the shifted search directions stored in FP16 / BF16.  vec_prec is the precision of the
@@ -310,49 +320,54 @@ inline int vec_prec(int prec) { return prec == 0 ? 0 : 1; }
 inline int vec16_mode(int prec) { return prec == 4 ? 1 : prec == 5 ? 2 : 0; }
 inline int dir_store(int prec) { return prec == 2 ? kDirF16 : prec == 3 ? kDirBF16 : kDirF32; }
 
-size_t bytes_per_slot(const smpq_ctx *c, int prec, int NS) {
+// The 16-bit precisions round what they store after every iteration, so their block is one long.
+inline bool short_block(int prec) { return prec >= 2; }
+// entries of p per right-hand side: the shifts (only the base one with 16-bit directions) and, with
+// K > 1, the second buffer of the base direction
+inline int dir_entries(int prec, int NS, int K) { return (dir_store(prec) == kDirF32 ? NS : 1) + (K > 1 ? 1 : 0); }
+
+size_t bytes_per_slot(const smpq_ctx *c, int prec, int NS, int K) {
     const size_t v64 = 12 * 16 * c->vs, v32 = 6 * 16 * c->vs, v16 = v32 / 2;
     // per-shift check: x_i for every shift, the residual and the saved y (+ tmp64 and ap64 in FP64)
     const size_t check = c->shift_check ? (NS + 2) * v64 + (prec == 0 ? 2 * v64 : 0) : 0;
-    // r, tmp, the NS directions and y (+ in the FP32 path the running sums of y and x0, and the
-    // FP64 x0, tmp64 and ap64 of the reliable updates)
-    if (prec == 0) return (2 + NS) * v64 + v64 + check;
-    if (dir_store(prec) != kDirF32) return 5 * v32 + NS * v16 + 4 * v64 + check;
-    return (4 + NS) * v32 + 4 * v64 + check;
+    // K residuals, tmp, the directions and y (+ in the FP32 path the FP64 x0, tmp64 and ap64 of the
+    // reliable updates)
+    const size_t nt = K + 1 + dir_entries(prec, NS, K);
+    if (prec == 0) return (nt + 1) * v64 + check;
+    return nt * v32 + (dir_store(prec) != kDirF32 ? NS * v16 : 0) + 4 * v64 + check;
+}
+
+void release_vectors(Workspace &w) {
+    w.r.release(); w.tmp.release(); w.p.release(); w.ph.release(); w.y.release();
+    w.x0.release(); w.tmp64.release(); w.ap64.release();
+    w.xs.release(); w.rres.release(); w.ysave.release();
 }
 
 // Device workspace for at least B right-hand sides of the given precision and shift count.
 // Everything, including the per-RHS CG state, is sized and laid out for the capacity w.B, the
 // slot range every launch covers; a new layout invalidates the captured graphs.
-void ensure_workspace(smpq_ctx *c, int prec, int NS, int B) {
+void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     Workspace &w = c->ws;
     const Geom g = c->geom();
     const size_t v64 = 12 * 16 * c->vs, v32 = 6 * 16 * c->vs;
     const size_t vt = prec == 0 ? v64 : v32;
-    if (w.prec == prec && w.NS == NS && w.B >= B && w.check == c->shift_check && w.S.rr) return;
+    if (w.prec == prec && w.NS == NS && w.K == K && w.B >= B && w.check == c->shift_check && w.S.rr) return;
     c->gen++;
-    w.r.release(); w.tmp.release(); w.p.release(); w.ph.release(); w.y.release();
-    w.x0.release(); w.tmp64.release(); w.ap64.release(); w.yacc.release(); w.x0acc.release();
-    w.xs.release(); w.rres.release(); w.ysave.release();
+    release_vectors(w);
     w.prec = prec;
     w.NS = NS;
     w.B = B;
+    w.K = K;
     w.check = c->shift_check;
-    w.r.ensure(vt * B);
+    w.r.ensure(vt * B * K);
     w.tmp.ensure(vt * B);
-    if (dir_store(prec) != kDirF32) {
-        w.p.ensure(vt * B);              // base directions
-        w.ph.ensure(v32 / 2 * B * NS);   // shifted directions, 16 bits
-    } else {
-        w.p.ensure(vt * B * NS);
-    }
+    w.p.ensure(vt * B * dir_entries(prec, NS, K));
+    if (dir_store(prec) != kDirF32) w.ph.ensure(v32 / 2 * B * NS);   // shifted directions, 16 bits
     w.y.ensure(v64 * B);
     if (prec >= 1) {
         w.x0.ensure(v64 * B);
         w.tmp64.ensure(v64 * B);
         w.ap64.ensure(v64 * B);
-        w.yacc.ensure(v32 * B);
-        w.x0acc.ensure(v32 * B);
     }
     if (w.check) {
         w.xs.ensure(v64 * B * NS);
@@ -364,9 +379,10 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B) {
         w.flags.ensure(sizeof(int) * B);
     }
     const size_t pstride = partial_stride(g);
-    w.st_d.ensure(sizeof(double) * ((size_t)B * (5 + 3 * NS + 4 * NS + 3 * NS)));
-    w.st_i.ensure(sizeof(int) * ((size_t)B * (2 * NS + 4 + 2 * NS) + 16));
-    w.st_l.ensure(sizeof(long long) * (size_t)B * 4);
+    const size_t BN = (size_t)B * NS, BKN = BN * K;
+    w.st_d.ensure(sizeof(double) * ((size_t)B * 6 + 6 * BN + 4 * BKN));
+    w.st_i.ensure(sizeof(int) * ((size_t)B * 8 + 2 * BN + 16));
+    w.st_l.ensure(sizeof(long long) * (size_t)B * 5);
     w.partial.ensure(sizeof(double) * (size_t)B * pstride);
     w.list.ensure(sizeof(int) * B);
     w.count.ensure(sizeof(int) * 4);
@@ -375,50 +391,55 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B) {
     w.batch_classes.ensure(sizeof(int) * (B / 12 + 1));
     MSState &S = w.S;
     double *d = w.st_d.as<double>();
-    S.rr = d; d += B;
-    S.bnorm = d; d += B;
-    S.alpha = d; d += B;
-    S.alpha_prev = d; d += B;
-    S.beta_prev = d; d += B;
-    S.zeta = d; d += (size_t)B * NS;
-    S.zeta_prev = d; d += (size_t)B * NS;
-    S.zeta_new = d; d += (size_t)B * NS;
-    S.upd_cy = d; d += (size_t)B * NS;
-    S.upd_zeta = d; d += (size_t)B * NS;
-    S.upd_beta = d; d += (size_t)B * NS;
-    S.upd_ax = d; d += (size_t)B * NS;
-    S.sh_scale = d; d += (size_t)B * NS;
-    S.upd_sold = d; d += (size_t)B * NS;
-    S.upd_snew = d; d += (size_t)B * NS;
+    auto dbl = [&d](size_t n) { double *q = d; d += n; return q; };
+    S.rr = dbl(B);
+    S.bnorm = dbl(B);
+    S.alpha = dbl(B);
+    S.alpha_prev = dbl(B);
+    S.beta = dbl(B);
+    S.beta_prev = dbl(B);
+    S.zeta = dbl(BN);
+    S.zeta_prev = dbl(BN);
+    S.zeta_new = dbl(BN);
+    S.sh_scale = dbl(BN);
+    S.s_sold = dbl(BN);
+    S.s_snew = dbl(BN);
+    S.h_cy = dbl(BKN);
+    S.h_a = dbl(BKN);
+    S.h_b = dbl(BKN);
+    S.h_z = dbl(BKN);
     S.dir_norm = 1.0 / std::sqrt(24.0 * (double)c->V);
     int *ip = w.st_i.as<int>();
-    S.sh_active = ip; ip += (size_t)B * NS;
-    S.sh_iters = ip; ip += (size_t)B * NS;
-    S.done = ip; ip += B;
-    S.iters = ip; ip += B;
-    S.status = ip; ip += B;
-    S.upd_n = ip; ip += B;
-    S.upd_idx = ip; ip += (size_t)B * NS;
-    S.upd_pupd = ip; ip += (size_t)B * NS;
+    auto intg = [&ip](size_t n) { int *q = ip; ip += n; return q; };
+    S.sh_active = intg(BN);
+    S.sh_iters = intg(BN);
+    S.done = intg(B);
+    S.iters = intg(B);
+    S.status = intg(B);
+    S.blk_n = intg(B);
+    S.fl_m = intg(B);
+    S.fl_act = reinterpret_cast<unsigned *>(intg(B));
+    S.fl_rd = reinterpret_cast<unsigned *>(intg(B));
+    S.fl_wr = reinterpret_cast<unsigned *>(intg(B));
     long long *lp = w.st_l.as<long long>();
     S.cnt_entries = lp; lp += B;
-    S.cnt_pupd = lp; lp += B;
     S.cnt_active = lp; lp += B;
-    S.cnt_base_pupd = lp; lp += B;
+    S.cnt_fl = lp; lp += B;
+    S.cnt_fl_r = lp; lp += B;
+    S.cnt_fl_p = lp; lp += B;
     S.partial = w.partial.as<double>();
     S.pstride = pstride;
     S.list = w.list.as<int>();
     S.count = w.count.as<int>();
     S.NS = NS;
     S.B = B;
+    S.K = K;
 }
 
 // Free the right-hand-side vectors of the workspace (the next ensure_workspace lays it out again).
 void release_workspace(smpq_ctx *c) {
     Workspace &w = c->ws;
-    w.r.release(); w.tmp.release(); w.p.release(); w.ph.release(); w.y.release();
-    w.x0.release(); w.tmp64.release(); w.ap64.release(); w.yacc.release(); w.x0acc.release();
-    w.xs.release(); w.rres.release(); w.ysave.release();
+    release_vectors(w);
     w.prec = -1;
     w.B = 0;
     w.S.rr = nullptr;
@@ -428,28 +449,60 @@ void release_workspace(smpq_ctx *c) {
 size_t workspace_bytes(const smpq_ctx *c) {
     const Workspace &w = c->ws;
     return (size_t)w.r.bytes + w.tmp.bytes + w.p.bytes + w.ph.bytes + w.y.bytes + w.x0.bytes + w.tmp64.bytes +
-           w.ap64.bytes + w.yacc.bytes + w.x0acc.bytes + w.xs.bytes + w.rres.bytes + w.ysave.bytes;
+           w.ap64.bytes + w.xs.bytes + w.rres.bytes + w.ysave.bytes;
 }
 
-int choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool multiple_of_12) {
+// Right-hand sides per batch and residuals kept for each.
+struct BatchPlan {
+    int B, K;
+};
+
+BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool multiple_of_12) {
     size_t freeb = 0, totalb = 0;
     HIPCHK(hipMemGetInfo(&freeb, &totalb));
-    // memory already held by a workspace of the same shape is reusable
-    size_t held = 0;
-    if (c->ws.prec == prec && c->ws.NS == NS) held = bytes_per_slot(c, prec, NS) * c->ws.B;
-    else held = workspace_bytes(c);
+    // the memory that the workspace holds is reusable
+    const size_t held = workspace_bytes(c);
     const size_t limit = c->run_limit > 0 ? c->run_limit : c->mem_limit;
     const double budget = limit > 0 ? (double)limit : 0.80 * (double)(freeb + held);
-    long long B = (long long)(budget / (double)bytes_per_slot(c, prec, NS));
-    if (c->max_rhs > 0) B = std::min<long long>(B, c->max_rhs);
-    B = std::min<long long>(B, total_slots);
     const int q = multiple_of_12 ? 12 : 1;
-    B = (B / q) * q;
+    auto most = [&](int K) {
+        long long B = (long long)(budget / (double)bytes_per_slot(c, prec, NS, K));
+        if (c->max_rhs > 0) B = std::min<long long>(B, c->max_rhs);
+        return std::min<long long>(B, total_slots) / q * q;
+    };
+    // the longest block that leaves a batch of every source, or one that fills the device
+    const long long fill = std::min<long long>(most(1), (kFillSites / c->V + q) / q * q);
+    int K = 1;
+    if (!short_block(prec))
+        for (int k : kBlockIters)
+            if (most(k) >= std::max<long long>(fill, q)) {
+                K = k;
+                break;
+            }
+    const long long B = most(K);
     if (B < q) throw Fail{SMPQ_ENOMEM, "not enough device memory for one batch of right-hand sides"};
     // spread the right-hand sides evenly over the batches this limit implies
     const long long nb = (total_slots + B - 1) / B;
     const long long even = ((total_slots + nb - 1) / nb + q - 1) / q * q;
-    return (int)std::min(B, even);
+    return BatchPlan{(int)std::min(B, even), K};
+}
+
+// A workspace for at least B right-hand sides whatever the context's memory limit: the one at hand,
+// or a new one with the longest block that fits the free memory.
+void ensure_workspace_for(smpq_ctx *c, int prec, int NS, int B) {
+    const Workspace &w = c->ws;
+    if (w.prec == prec && w.NS == NS && w.B >= B) return ensure_workspace(c, prec, NS, w.B, w.K);
+    size_t freeb = 0, totalb = 0;
+    HIPCHK(hipMemGetInfo(&freeb, &totalb));
+    const double budget = 0.80 * (double)(freeb + workspace_bytes(c));
+    int K = 1;
+    if (!short_block(prec))
+        for (int k : kBlockIters)
+            if ((double)B * (double)bytes_per_slot(c, prec, NS, k) <= budget) {
+                K = k;
+                break;
+            }
+    ensure_workspace(c, prec, NS, B, K);
 }
 
 void require_gauge_zolo(smpq_ctx *c) {
@@ -480,84 +533,110 @@ void use_coef(smpq_ctx *c, bool inverse) {
 }
 
 struct BatchResult {
-    long long iters_sum = 0, iters_max = 0, n_reliable = 0, entries = 0, pupd = 0, active = 0;
+    long long iters_sum = 0, iters_max = 0, n_reliable = 0, entries = 0, active = 0;
     double max_true_resid = 0.0;
 };
 
-// One CG iteration for every active slot of the batch (capacity-sized launches; inactive
-// slots exit at once).  y64 / x64 select FP64 or FP32-running-sum accumulation (FP32 path).
-// The first stencil, tmp = D_W p, also sums <p, (H^2 + s0) p> = |tmp|^2 + s0 |p|^2, so alpha is
-// known before the second, which updates r -= alpha (D_W^dag tmp + s0 p) in place with the
-// partials of |r|^2 (the product itself is never stored).  With timers, events bracket the two
-// stencil launches and the update launch.
-void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, bool y64, bool x64, GroupTimers *tm,
-                       bool captured) {
+// Where the running batch stands: iterations of the current block, and which buffer holds the base
+// direction (0: entry 0 of the slot's directions, 1: the entry after the shifts).
+struct BlockPos {
+    int n = 0, par = 0;
+    void advance(int iters, int K) {
+        if (K > 1) par ^= (n + iters) / K & 1;
+        n = (n + iters) % K;
+    }
+};
+
+// Strides and offsets (units) of the residual ring and the base direction.
+struct SolveLayout {
+    size_t rs, rst, pst;
+    int alt;   // entry of the second base direction (0: none, the base is updated in place)
+    SolveLayout(const smpq_ctx *c, int prec, const MSState &S)
+        : rs((vec_prec(prec) == 0 ? 12 : 6) * c->vs),
+          rst(rs * S.K),
+          pst(rs * dir_entries(prec, S.NS, S.K)),
+          alt(S.K > 1 ? dir_entries(prec, S.NS, 1) : 0) {}
+    size_t base(int par) const { return par ? (size_t)alt * rs : 0; }
+    // ring position of the residual that iteration n of a block reads (it writes position n)
+    static int ring_in(int n, int K) { return n == 0 ? K - 1 : n - 1; }
+};
+
+// The end of a block: y, x0 and the directions of every slot with iterations in it.
+void enqueue_block_update(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos) {
+    Workspace &w = c->ws;
+    const Geom g = c->geom();
+    const SolveLayout L(c, prec, S);
+    const int vp = vec_prec(prec), dir = dir_store(prec);
+    launch_block_end(S, S.K == 1, dir, c->stream);
+    launch_block_update(vp, g, S, w.r.p, w.p.p, L.pst, pos.par ? L.alt : 0, w.y.as<double2>(),
+                        prec >= 1 ? w.x0.as<double2>() : nullptr, dir, w.ph.p, c->cur_xs, c->stream);
+    pos.advance(S.K - pos.n, S.K);
+}
+
+// One CG iteration for every active slot of the batch (capacity-sized launches; inactive slots
+// exit at once).  The first stencil, tmp = D_W p, also sums <p, (H^2 + s0) p> = |tmp|^2 + s0 |p|^2,
+// so alpha is known before the second, which writes r - alpha (D_W^dag tmp + s0 p) to the next ring
+// position with the partials of |r|^2 (the product itself is never stored).  The first
+// iteration of a block leaves the base direction it started from in place for the block update.
+// With timers, events bracket the two stencil launches and the updates.
+void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, GroupTimers *tm, bool captured) {
     Workspace &w = c->ws;
     const Geom g = c->geom();
     hipStream_t s = c->stream;
-    const int NS = S.NS, B = S.B;
-    const int vp = vec_prec(prec), dir = dir_store(prec);
-    const size_t rs = (vp == 0 ? 12 : 6) * c->vs;
-    // the base direction: one of NS per slot, or (16-bit shifted directions) the only one
-    const size_t pst = dir == kDirF32 ? NS * rs : rs, pofs = dir == kDirF32 ? S.i0 * rs : 0;
+    const int B = S.B;
+    const int vp = vec_prec(prec);
+    const SolveLayout L(c, prec, S);
+    const size_t rs = L.rs;
     const void *U = vp == 0 ? c->U64.p : c->U32.p;
+    // the current base direction: the block's first iteration finds it where the last block left it
+    const size_t pofs = pos.n == 0 || !L.alt ? L.base(pos.par) : L.base(pos.par ^ 1);
+    const size_t r_in = rs * SolveLayout::ring_in(pos.n, S.K), r_out = rs * pos.n;
+    char *rp = w.r.as<char>(), *pp = w.p.as<char>();
     // partials per slot of the first (D_W p) and the second (D_W^dag) stencil
     const int np_ds = dslash_partials(vp, g, false), np_dag = dslash_partials(vp, g, true);
-    const bool mixed = prec >= 1;
     const Slots act{S.list, S.count, 0};
     const double s0 = c->coef->s0;
     if (tm) tm->dslash.record(s, captured);
-    launch_dslash(vp, false, 3, U, w.p.p, pst, pofs, w.tmp.p, rs, nullptr, 0, 0, g, c->kappa, s0, act, B, S.partial, s);
+    launch_dslash(vp, false, 3, U, w.p.p, L.pst, pofs, w.tmp.p, rs, nullptr, 0, 0, g, c->kappa, s0, act, B, S.partial,
+                  s, nullptr, nullptr, 0, S.done);
     if (tm) tm->dslash.record(s, captured);
     const int m16 = vec16_mode(prec);
     if (m16) launch_round16(g, S, w.tmp.p, rs, 0, m16, s);   // D_W p as 16-bit storage would hold it
     launch_scalars_alpha(S, np_ds, s);
     if (tm) tm->dslash.record(s, captured);
-    launch_dslash(vp, true, 2, U, w.tmp.p, rs, 0, w.r.p, rs, w.p.p, pst, pofs, g, c->kappa, s0, act, B, S.partial, s,
-                  S.alpha, S.status);
+    launch_dslash(vp, true, 2, U, w.tmp.p, rs, 0, rp + r_out * kUnit, L.rst, w.p.p, L.pst, pofs, g, c->kappa, s0, act,
+                  B, S.partial, s, S.alpha, S.status, (ptrdiff_t)r_in - (ptrdiff_t)r_out, S.done);
     if (tm) tm->dslash.record(s, captured);
-    launch_scalars_beta(S, np_dag, s);
+    launch_scalars_beta(vp, S, np_dag, s);
     if (tm) tm->update.record(s, captured);
-    launch_shift_update(vp, g, S, w.r.p, w.p.p, y64 ? w.y.p : w.yacc.p, y64,
-                        mixed ? (x64 ? w.x0.p : w.x0acc.p) : nullptr, x64, dir, w.ph.p, c->cur_xs, s);
+    if (L.alt)
+        launch_base_direction(vp, g, S, rp + r_out * kUnit, L.rst, pp + pofs * kUnit,
+                              pp + L.base(pos.par ^ 1) * kUnit, L.pst, s);
+    if (pos.n == S.K - 1)
+        enqueue_block_update(c, prec, S, pos);
+    else
+        pos.advance(1, S.K);
     if (tm) tm->update.record(s, captured);
-    if (m16) launch_round16(g, S, w.p.p, pst, pofs, m16, s);   // the new base direction
-    launch_compact(S, s);
+    if (m16) launch_round16(g, S, w.p.p, L.pst, L.base(pos.par), m16, s);   // the new base direction
 }
 
-// One group of kGroup iterations starting at iteration it0, plus the fold of the FP32 running
-// sum of y at its end when the group used it.
-void enqueue_group(smpq_ctx *c, int prec, const MSState &S, int it0, GroupTimers *tm, bool captured) {
-    const bool mixed = prec >= 1;
-    const bool y64 = !mixed || it0 < kDirectY;
-    const bool x64 = mixed && (c->reliable == 0 || it0 < c->reliable);
-    for (int gi = 0; gi < kGroup; ++gi) enqueue_iteration(c, prec, S, y64, x64, tm, captured);
-    if (mixed && !y64)
-        launch_fold(c->geom(), Slots{S.list, S.count, 0}, S.B, c->ws.y.as<double2>(), c->ws.yacc.p, nullptr, nullptr,
-                    c->stream);
+// One group of kGroup iterations from the given position, then the list of the slots still iterating.
+void enqueue_group(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, GroupTimers *tm, bool captured) {
+    for (int gi = 0; gi < kGroup; ++gi) enqueue_iteration(c, prec, S, pos, tm, captured);
+    launch_compact(S, c->stream);
 }
 
-// Graph variant of a group (0: FP64 path; 1-3: FP32 path with FP64 y and x0 / FP32 y and FP64 x0
-// / FP32 y and x0); -1 when the group is launched eagerly.
-int group_variant(const smpq_ctx *c, int prec, int it0) {
-    if (prec == 0) return 0;
-    if (c->reliable % kGroup != 0) return -1;   // x0 accumulation would switch inside a group
-    const bool y64 = it0 < kDirectY;
-    const bool x64 = c->reliable == 0 || it0 < c->reliable;
-    return y64 ? (x64 ? 1 : -1) : (x64 ? 2 : 3);
-}
-
-// Launch one group, as a captured graph where possible.  Returns the timers to read after
-// the stream has synchronised (null when not timing).
-GroupTimers *launch_group(smpq_ctx *c, int prec, const MSState &S, int it0) {
+// Launch one group, as a captured graph where possible, and advance pos.  Returns the timers to
+// read after the stream has synchronised (null when not timing).
+GroupTimers *launch_group(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos) {
     const bool timed = c->timing;
-    const int v = (!c->use_graphs || (timed && !c->graph_timing_ok)) ? -1 : group_variant(c, prec, it0);
-    if (v < 0) {
+    if (!c->use_graphs || (timed && !c->graph_timing_ok)) {
         GroupTimers *tm = timed ? &c->eager_timers : nullptr;
         if (tm) tm->dslash.used = tm->update.used = 0;
-        enqueue_group(c, prec, S, it0, tm, false);
+        enqueue_group(c, prec, S, pos, tm, false);
         return tm;
     }
+    const int v = (pos.n ? 2 : 0) + pos.par;   // a group starts a block or is the second half of one
     if (c->graph_coef != c->coef) {   // the graphs hold the coefficients of the other set
         c->gen++;
         c->graph_coef = c->coef;
@@ -569,16 +648,17 @@ GroupTimers *launch_group(smpq_ctx *c, int prec, const MSState &S, int it0) {
         c->graphs[t][v] = nullptr;
         if (tm) tm->dslash.used = tm->update.used = 0;
         hipGraph_t graph = nullptr;
+        BlockPos after = pos;
         HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         try {
-            enqueue_group(c, prec, S, it0, tm, true);
+            enqueue_group(c, prec, S, after, tm, true);
         } catch (const Fail &) {
             (void)hipStreamEndCapture(c->stream, &graph);
             if (graph) (void)hipGraphDestroy(graph);
             (void)hipGetLastError();
             if (!timed) throw;
             c->graph_timing_ok = false;   // no event nodes in graphs: time eagerly from now on
-            return launch_group(c, prec, S, it0);
+            return launch_group(c, prec, S, pos);
         }
         HIPCHK(hipStreamEndCapture(c->stream, &graph));
         const hipError_t e = hipGraphInstantiateWithFlags(&c->graphs[t][v], graph, 0);
@@ -587,6 +667,7 @@ GroupTimers *launch_group(smpq_ctx *c, int prec, const MSState &S, int it0) {
         c->graph_gen[t][v] = c->gen;
     }
     HIPCHK(hipGraphLaunch(c->graphs[t][v], c->stream));
+    pos.advance(kGroup, S.K);
     return tm;
 }
 
@@ -614,6 +695,9 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     const int np_unit = unit_parts(vp, g);
     const Slots act{S.list, S.count, 0};
     const bool mixed = prec >= 1;
+    const SolveLayout L(c, prec, S);
+    // the residual a block starts from is at the ring's last position
+    char *r0 = w.r.as<char>() + L.rs * (S.K - 1) * kUnit;
 
     const bool check = c->shift_check && !c->refining;
     if (check && !w.check) throw Fail{SMPQ_ESTATE, "workspace laid out without the per-shift check"};
@@ -622,30 +706,29 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     if (check) HIPCHK(hipMemsetAsync(w.xs.p, 0, (size_t)nslots * NS * rs64 * sizeof(double2), s));
     // the graphs capture this pointer: a change of check mode or refinement bumps c->gen
     c->cur_xs = check ? w.xs.as<double2>() : nullptr;
-    launch_cg_init(vp, g, src, nslots, NS, c->coef->c0, w.r.p, w.p.p, w.y.as<double2>(), mixed ? w.yacc.p : nullptr,
-                   mixed ? w.x0.as<double2>() : nullptr, mixed ? w.x0acc.p : nullptr, S.partial, dir, s);
+    launch_cg_init(vp, g, src, nslots, NS, c->coef->c0, r0, L.rst, w.p.p, L.pst, w.y.as<double2>(),
+                   mixed ? w.x0.as<double2>() : nullptr, S.partial, dir, s);
     launch_scalars_init(S, np_unit, nslots, s);
-    if (dir != kDirF32) launch_dir16_init(g, S, nslots, w.r.p, dir, w.ph.p, s);
+    if (dir != kDirF32) launch_dir16_init(g, S, nslots, r0, L.rst, dir, w.ph.p, s);
     launch_compact(S, s);
     if (vec16_mode(prec))   // the first base direction, b, with the scale |b|
-        launch_round16(g, S, w.p.p, dir == kDirF32 ? NS * rs64 / 2 : rs64 / 2, 0, vec16_mode(prec), s);
+        launch_round16(g, S, w.p.p, L.pst, 0, vec16_mode(prec), s);
     HIPCHK(hipGetLastError());
 
     BatchResult res;
     int iter = 0;
+    BlockPos pos;
     for (;;) {
-        GroupTimers *tm = launch_group(c, prec, S, iter);
+        GroupTimers *tm = launch_group(c, prec, S, pos);
         iter += kGroup;
         if (mixed && c->reliable > 0 && iter % c->reliable == 0) {
-            // residual replacement: fold the running base solution, r = b - (H^2 + s0) x0 in FP64
-            // the running sum of y was folded at the end of the group (or is still zero before
-            // the first FP32-summed group), so only x0's is folded here
-            launch_fold(g, act, S.B, nullptr, nullptr, w.x0.as<double2>(), w.x0acc.p, s);
+            // residual replacement: x0 up to date, r = b - (H^2 + s0) x0 in FP64
+            if (pos.n > 0) enqueue_block_update(c, prec, S, pos);
             launch_dslash(0, false, 0, c->U64.p, w.x0.p, rs64, 0, w.tmp64.p, rs64, nullptr, 0, 0, g,
                           c->kappa, 0.0, act, S.B, nullptr, s);
             launch_dslash(0, true, 1, c->U64.p, w.tmp64.p, rs64, 0, w.ap64.p, rs64, w.x0.p, rs64, 0, g,
                           c->kappa, s0, act, S.B, S.partial, s);
-            launch_reliable(vp, g, S, src, w.ap64.as<double2>(), w.r.p, s);
+            launch_reliable(vp, g, S, src, w.ap64.as<double2>(), r0, L.rst, s);
             launch_scalars_rr(S, np_unit, s);
             res.n_reliable++;
         }
@@ -657,9 +740,7 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
             st->update_ms += tm->update.sum();
         }
         if (*c->h_count == 0) {
-            if (mixed)   // the slots finished at different iterations: fold every one of them
-                launch_fold(g, Slots{nullptr, nullptr, nslots}, nslots, w.y.as<double2>(), w.yacc.p,
-                            w.x0.as<double2>(), w.x0acc.p, s);
+            if (pos.n > 0) enqueue_block_update(c, prec, S, pos);
             break;
         }
         if (iter >= c->max_iter)
@@ -667,7 +748,7 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     }
     if (mixed) {
         // FP64 true residual ||b - (H^2 + s0) x0|| / ||b|| of the base system of every slot,
-        // x0 being FP64 after the final fold
+        // x0 being complete after the last block update
         std::vector<int> all(nslots);
         for (int k = 0; k < nslots; ++k) all[k] = k;
         *c->h_count = nslots;
@@ -677,7 +758,7 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
                       S.B, nullptr, s);
         launch_dslash(0, true, 1, c->U64.p, w.tmp64.p, rs64, 0, w.ap64.p, rs64, w.x0.p, rs64, 0, g, c->kappa, s0,
                       act, S.B, S.partial, s);
-        launch_reliable(vp, g, S, src, w.ap64.as<double2>(), w.r.p, s);
+        launch_reliable(vp, g, S, src, w.ap64.as<double2>(), r0, L.rst, s);
         launch_scalars_rr(S, np_unit, s);
         HIPCHK(hipGetLastError());
         std::vector<double> rr(nslots), bn(nslots);
@@ -689,29 +770,28 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     }
     c->cur_xs = nullptr;
     std::vector<int> status(nslots), iters(nslots);
-    std::vector<long long> ent(nslots), pup(nslots), actv(nslots), bpup(nslots);
+    std::vector<long long> ent(nslots), actv(nslots), fl(nslots), flr(nslots), flp(nslots);
     HIPCHK(hipMemcpy(status.data(), S.status, sizeof(int) * nslots, hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(iters.data(), S.iters, sizeof(int) * nslots, hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(ent.data(), S.cnt_entries, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(pup.data(), S.cnt_pupd, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
     HIPCHK(hipMemcpy(actv.data(), S.cnt_active, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(bpup.data(), S.cnt_base_pupd, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
-    long long base_pupd = 0;
+    HIPCHK(hipMemcpy(fl.data(), S.cnt_fl, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpy(flr.data(), S.cnt_fl_r, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpy(flp.data(), S.cnt_fl_p, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
+    long long blocks = 0, ring_reads = 0, dir_moves = 0;
     for (int k = 0; k < nslots; ++k) {
         if (status[k] != kStatusOK) throw Fail{SMPQ_ENUMERIC, "CG breakdown: <p, A p> <= 0 or not finite"};
         res.iters_sum += iters[k];
         res.iters_max = std::max<long long>(res.iters_max, iters[k]);
         res.entries += ent[k];
-        res.pupd += pup[k];
         res.active += actv[k];
-        base_pupd += bpup[k];
+        blocks += fl[k];
+        ring_reads += flr[k];
+        dir_moves += flp[k];
     }
     if (st) {
         const double s_t = prec == 0 ? 16.0 : 8.0;           // bytes per complex spinor entry
         const double link_site = prec == 0 ? 576.0 : 192.0;   // link bytes per site (FP32: two rows)
-        // bytes per complex entry of a listed direction: the base direction (one entry per
-        // slot-iteration) is stored like r, 16-bit shifted directions take 4
-        const double s_dir = dir == kDirF32 ? s_t : 4.0;
         const double V = c->V;
         // algorithmic bytes: each stencil reads the links once and each input spinor once; the
         // first writes tmp, the second reads p for the "+ s0 p" term and reads and writes r.
@@ -720,26 +800,14 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
         const double launched = (double)res.iters_max;
         st->dslash_bytes += launched * 2.0 * link_site * V + (double)res.active * V * 12.0 * s_t * 6.0;
         st->dslash_launches += 2LL * res.iters_max;
-        // update kernel: r read, the running sum read+write and, in the FP32 path, the running
-        // base solution read+write (both in the iteration precision), every listed p_i read,
-        // every updated p_i written.
-        // All slots of a batch start together, so slot k ran iterations 0 .. iters[k]-1: the
-        // first min(iters, kDirectY) of them summed y in FP64, the first min(iters, reliable)
-        // summed x0 in FP64 (FP32 path).
-        double acc_bytes = 0.0;
-        for (int k = 0; k < nslots; ++k) {
-            const double n = iters[k];
-            if (prec == 0) {
-                acc_bytes += n * 2.0 * 192.0;
-            } else {
-                const double ny = std::min<double>(n, kDirectY);
-                const double nx = c->reliable > 0 ? std::min<double>(n, c->reliable) : n;
-                acc_bytes += ny * 2.0 * 192.0 + (n - ny) * 2.0 * 96.0 + nx * 2.0 * 192.0 + (n - nx) * 2.0 * 96.0;
-            }
-        }
-        const double dir_units = (double)(res.active + base_pupd) * s_t +
-                                 (double)(res.entries - res.active + res.pupd - base_pupd) * s_dir;
-        st->update_bytes += V * ((double)res.active * 12.0 * s_t + acc_bytes + 12.0 * dir_units);
+        // updates: the base direction (r and p read, p written) in every iteration, and per block
+        // its residuals read, the listed directions read and written (16-bit ones 4 bytes per
+        // complex entry) and y and x0 read and written in FP64; with K = 1 the block update
+        // writes the base direction and there is no other.
+        const double s_dir = dir == kDirF32 ? s_t : 4.0;
+        const double base_moves = S.K > 1 ? 3.0 * (double)res.active : 0.0;
+        st->update_bytes += V * 12.0 * (s_t * (base_moves + (double)ring_reads) + s_dir * (double)dir_moves +
+                                        (double)blocks * 2.0 * 16.0 * (mixed ? 2.0 : 1.0));
         st->update_launches += res.iters_max;
         st->n_reliable_updates += res.n_reliable;
         st->max_true_resid = std::max(st->max_true_resid, res.max_true_resid);
@@ -1022,7 +1090,7 @@ void deflate(smpq_ctx *c, int k, int steps, double *theta_out, double *tmax_out,
     c->tol = 1e-14;
     c->shift_check = false;   // the inner solves are single-shift FP64 solves to 1e-14
     use_coef(c, true);
-    ensure_workspace(c, 0, 1, c->ws.prec == 0 && c->ws.NS == 1 ? c->ws.B : 1);
+    ensure_workspace_for(c, 0, 1, 1);
     auto inverse = [&](const double2 *q, double2 *o) {
         Source src{nullptr, nullptr, nullptr, q};
         run_batch(c, 0, 1, src, nullptr);
@@ -1126,8 +1194,9 @@ void qx_classes(smpq_ctx *c, const std::vector<int> &classes, bool point, smpq_s
     const int NS = c->coef->n;
     const int total = (int)classes.size() * 12;
     if (total == 0) return;
-    const int B = choose_batch(c, prec, NS, total, true);
-    ensure_workspace(c, prec, NS, B);
+    const BatchPlan plan = choose_batch(c, prec, NS, total, true);
+    const int B = plan.B;
+    ensure_workspace(c, prec, NS, B, plan.K);
     Workspace &w = c->ws;
     const int *colour = point ? c->d_pcolour.as<int>() : c->d_colour.as<int>();
     const int *cptr = point ? c->d_pptr.as<int>() : c->d_cptr.as<int>();
@@ -1789,8 +1858,9 @@ smpq_status smpq_apply_dov(smpq_ctx *c, const double *in, double *out, int n) {
         bin.ensure(v64 * n);
         bout.ensure(v64 * n);
         HIPCHK(hipMemcpyAsync(bin.p, stage.data(), v64 * n, hipMemcpyHostToDevice, c->stream));
-        const int B = choose_batch(c, prec, NS, n, false);
-        ensure_workspace(c, prec, NS, B);
+        const BatchPlan plan = choose_batch(c, prec, NS, n, false);
+        const int B = plan.B;
+        ensure_workspace(c, prec, NS, B, plan.K);
         for (int k0 = 0; k0 < n; k0 += B) {
             const int nb = std::min(B, n - k0);
             const double2 *bptr = bin.as<double2>() + (size_t)k0 * 12 * c->vs;
@@ -1911,7 +1981,7 @@ smpq_status smpq_compute_qx_multi(smpq_ctx *const *ctxs, int n_ctx, const int32_
         }
     std::vector<std::vector<int>> cls(n_ctx);
     std::vector<double> work(n_ctx, 0.0);
-    std::vector<int> planned(n_ctx, 0);
+    std::vector<BatchPlan> planned(n_ctx, BatchPlan{0, 1});
     auto give_up = [&](int k, smpq_status s) {
         for (int j = 0; j < n_ctx; ++j) ctxs[j]->run_limit = 0;
         if (failed) *failed = k;
@@ -1953,18 +2023,20 @@ smpq_status smpq_compute_qx_multi(smpq_ctx *const *ctxs, int n_ctx, const int32_
             if (ctxs[k]->mem_limit > 0) fixed += ctxs[k]->mem_limit;
         }
         double pool = std::max(0.0, 0.80 * (double)(freeb + held) - (double)fixed);
-        // every context first gets one batch of 12 right-hand sides; the rest goes out in
-        // proportion to the work, never beyond what a context can use (all its sources at
-        // once), with what a capped context leaves handed on to the others
+        // every context first gets one batch of 12 right-hand sides (with the shortest block); the
+        // rest goes out in proportion to the work, never beyond what a context can use (all its
+        // sources at once with the longest block), with what a capped context leaves handed on to
+        // the others
         std::vector<double> share(n_ctx, 0.0), cap(n_ctx, 0.0), slotb(n_ctx, 0.0);
         std::vector<char> open(n_ctx, 0);
         for (int k = 0; k < n_ctx; ++k) {
             smpq_ctx *c = ctxs[k];
             if (c->mem_limit > 0 || cls[k].empty()) continue;
-            const double slot = (double)bytes_per_slot(c, (int)c->prec, c->zolo.n);
-            slotb[k] = slot;
-            share[k] = 12.0 * slot;
-            cap[k] = 12.0 * (double)cls[k].size() * slot;
+            const int prec = (int)c->prec;
+            slotb[k] = (double)bytes_per_slot(c, prec, c->zolo.n, 1);
+            share[k] = 12.0 * slotb[k];
+            cap[k] = 12.0 * (double)cls[k].size() *
+                     (double)bytes_per_slot(c, prec, c->zolo.n, short_block(prec) ? 1 : kBlockIters[0]);
             pool -= share[k];
             open[k] = 1;
         }
@@ -1999,16 +2071,17 @@ smpq_status smpq_compute_qx_multi(smpq_ctx *const *ctxs, int n_ctx, const int32_
                 const int prec = (int)c->prec;
                 if (cls[k].empty()) return;
                 planned[k] = choose_batch(c, prec, c->zolo.n, (int)cls[k].size() * 12, true);
-                if (c->ws.prec != prec || c->ws.NS != c->zolo.n || c->ws.B != planned[k]) release_workspace(c);
+                if (c->ws.prec != prec || c->ws.NS != c->zolo.n || c->ws.B != planned[k].B || c->ws.K != planned[k].K)
+                    release_workspace(c);
             });
             if (s != SMPQ_OK) return give_up(k, s);
         }
         for (int k = 0; k < n_ctx; ++k) {
             smpq_ctx *c = ctxs[k];
             const smpq_status s = guarded(c, [&] {
-                if (planned[k] > 0) ensure_workspace(c, (int)c->prec, c->zolo.n, planned[k]);
-                if (planned[k] > 0 && c->defl_k > 0)
-                    c->defl_coef.ensure(sizeof(double2) * (size_t)planned[k] * c->defl_k);
+                if (planned[k].B > 0) ensure_workspace(c, (int)c->prec, c->zolo.n, planned[k].B, planned[k].K);
+                if (planned[k].B > 0 && c->defl_k > 0)
+                    c->defl_coef.ensure(sizeof(double2) * (size_t)planned[k].B * c->defl_k);
             });
             if (s != SMPQ_OK) return give_up(k, s);
         }
@@ -2067,7 +2140,7 @@ smpq_status smpq_dov_locality(smpq_ctx *c, int64_t site, double *mean_abs, smpq_
         const int prec = (int)c->prec;
         use_coef(c, false);
         ensure_point_device(c);
-        ensure_workspace(c, prec, c->zolo.n, std::max(12, c->ws.prec == prec && c->ws.NS == c->zolo.n ? c->ws.B : 12));
+        ensure_workspace_for(c, prec, c->zolo.n, 12);
         Workspace &w = c->ws;
         std::vector<int> sc(12, (int)site), sp(12);
         for (int j = 0; j < 12; ++j) sp[j] = j;
@@ -2123,8 +2196,8 @@ smpq_status smpq_prepare(smpq_ctx *c) {
         require_gauge_zolo(c);
         if (!c->have_scheme) throw Fail{SMPQ_ESTATE, "no scheme set"};
         const int prec = (int)c->prec;
-        const int B = choose_batch(c, prec, c->zolo.n, 12 * c->n_classes, true);
-        ensure_workspace(c, prec, c->zolo.n, B);
+        const BatchPlan plan = choose_batch(c, prec, c->zolo.n, 12 * c->n_classes, true);
+        ensure_workspace(c, prec, c->zolo.n, plan.B, plan.K);
         ensure_scheme_device(c);
     });
 }
@@ -2241,7 +2314,7 @@ smpq_status smpq_autotune(smpq_ctx *c, int n_rhs, smpq_tuning *chosen) {
         if (n_rhs == 0) {   // the batch a whole q(x) map of the current scheme would use
             if (c->n_classes == 0) throw Fail{SMPQ_ESTATE, "n_rhs = 0 needs a probing scheme"};
             if (!c->have_zolo) throw Fail{SMPQ_ESTATE, "n_rhs = 0 needs the Zolotarev coefficients"};
-            n_rhs = choose_batch(c, (int)c->prec, c->zolo.n, 12 * c->n_classes, true);
+            n_rhs = choose_batch(c, (int)c->prec, c->zolo.n, 12 * c->n_classes, true).B;
         }
         double by;
         struct Cand {

@@ -43,22 +43,36 @@ struct Slots {
     int n;
 };
 
-// Per-batch multi-shift CG state (all device pointers; one entry per slot or slot*NS).
+// Per-batch multi-shift CG state (all device pointers; one entry per slot, slot*NS + shift, or
+// (slot*K + j)*NS + shift for iteration j of a block).
+//
+// The shifted systems are updated once per block of up to K iterations: the residuals r_1 .. r_m of
+// the block's m iterations stay in a ring of K vectors per right-hand side, with the coefficients
+// of every shift, and the block update runs the recurrences y += c_i a p_i, p_i = z r + b p_i of
+// all its iterations in registers.  The arithmetic is that of an update in every iteration, so
+// results do not depend on K.
 struct MSState {
-    int B, NS, i0;
+    int B, NS, i0, K;
     double tol;
-    double *rr, *bnorm, *alpha, *alpha_prev, *beta_prev;
+    double *rr, *bnorm, *alpha, *alpha_prev, *beta, *beta_prev;
     double *zeta, *zeta_prev, *zeta_new;
     int *sh_active, *sh_iters;
     int *done, *iters, *status;
-    int *upd_n, *upd_idx, *upd_pupd;
-    double *upd_cy, *upd_zeta, *upd_beta;
-    double *upd_ax;      // alpha^i of each update-list entry (0 for a converged base entry)
-    // 16-bit shifted directions: p_i is stored as p_i / sh_scale[slot NS + i]; per update-list
-    // entry the scale that decodes the stored direction and the reciprocal of the new one
-    double *sh_scale, *upd_sold, *upd_snew;
+    // the current block: iterations done and their coefficients, [slot][K][NS]: c_i a, a, and z and b
+    // in the iteration precision
+    int *blk_n;
+    double *h_cy, *h_a;
+    void *h_z, *h_b;
+    // the block update: number of residuals, masks of the shifts active at the block's start (or to
+    // be written) and of those to write
+    int *fl_m;
+    unsigned *fl_act, *fl_rd, *fl_wr;
+    // 16-bit shifted directions: p_i is stored as p_i / sh_scale[slot NS + i]; the scale that
+    // decodes the stored direction and the reciprocal of the one the block update stores with
+    double *sh_scale, *s_sold, *s_snew;
     double dir_norm;     // 1 / sqrt(24 V): a direction of norm n has entries of size ~ n dir_norm
-    long long *cnt_entries, *cnt_pupd, *cnt_active, *cnt_base_pupd;
+    long long *cnt_entries, *cnt_active;               // listed shifts, iterations
+    long long *cnt_fl, *cnt_fl_r, *cnt_fl_p;           // block updates, residuals and directions they moved
     const double *c, *delta;
     double *partial;     // per-block partial sums, slot stride pstride
     size_t pstride;
@@ -83,15 +97,17 @@ enum { kStatusOK = 0, kStatusBreakdown = 1 };
 //   epi 0: out = d
 //   epi 1: out = d + sigma * aux, partial[slot][block] = Re <aux, out>
 //   epi 3: out = d, partial = |d|^2 + sigma |in|^2   (= <in, (H^2 + sigma) in> when dag = 0)
-//   epi 2: out holds r; r -= alpha[slot] (d + sigma * aux) unless status[slot] is not OK;
-//          partial = |r|^2 (the product d + sigma aux is not stored)
+//   epi 2: out = r - alpha[slot] (d + sigma * aux), r read at out + r_ofs units (out = r when
+//          status[slot] is not OK); partial = |out|^2 (the product d + sigma aux is not stored)
+// done (nullable): slots whose flag is set are skipped.
 // prec: 0 = FP64, 1 = FP32 (FP32: epi 0 both ways, epi 3 with dag = 0, epi 1 and 2 with
 // dag = 1).  The kernel variant comes from g's tuning fields; epilogues 1-3 write
 // dslash_partials(prec, g) partials per slot.
 void launch_dslash(int prec, bool dag, int epi, const void *U, const void *in, size_t in_stride,
                    size_t in_extra, void *out, size_t out_stride, const void *aux, size_t aux_stride,
                    size_t aux_extra, const Geom &g, double kappa, double sigma, Slots sl, int max_slots,
-                   double *partial, hipStream_t st, const double *alpha = nullptr, const int *status = nullptr);
+                   double *partial, hipStream_t st, const double *alpha = nullptr, const int *status = nullptr,
+                   ptrdiff_t r_ofs = 0, const int *done = nullptr);
 __host__ __device__ int site_blocks(const Geom &g);   // blocks of 256 sites
 int dslash_partials(int prec, const Geom &g, bool dag);   // partials per slot of the stencil epilogue
 bool plane_tileable(const Geom &g);
@@ -104,30 +120,33 @@ size_t partial_stride(const Geom &g);           // slot stride of the partial bu
 
 // Storage of the shifted search directions p_i (i != base) in the FP32 path: FP32, or FP16 /
 // BF16 scaled by a per-direction FP64 factor (the base direction, which the stencil reads,
-// stays FP32).  With 16-bit storage, p holds only the base direction of each slot (slot
-// stride one vector) and ph the NS directions in 16 bits (the base entry unused).
+// stays FP32).  With 16-bit storage, p holds only the base direction of each slot and ph the NS
+// directions in 16 bits (the base entry unused).
 enum { kDirF32 = 0, kDirF16 = 1, kDirBF16 = 2 };
 
-// r = p_i = b, y = c0 b; FP32 path: yacc = 0, x0 = 0, x0acc = 0 (pass null otherwise).  With
-// 16-bit directions only r and the base direction are written; launch_dir16_init writes the
-// others after launch_scalars_init has set their scales from |b|.
-void launch_cg_init(int prec, const Geom &g, const Source &src, int nslots, int NS, double c0, void *r,
-                    void *p, double2 *y, void *yacc, double2 *x0, void *x0acc, double *partial, int dir,
-                    hipStream_t st);
-void launch_dir16_init(const Geom &g, const MSState &s, int nslots, const void *r, int dir, void *ph, hipStream_t st);
+// r = p_i = b, y = c0 b; FP32 path: x0 = 0 (null otherwise).  r and p have slot strides rst and
+// pst (units).  With 16-bit directions only r and the base direction are written;
+// launch_dir16_init writes the others after launch_scalars_init has set their scales from |b|.
+void launch_cg_init(int prec, const Geom &g, const Source &src, int nslots, int NS, double c0, void *r, size_t rst,
+                    void *p, size_t pst, double2 *y, double2 *x0, double *partial, int dir, hipStream_t st);
+void launch_dir16_init(const Geom &g, const MSState &s, int nslots, const void *r, size_t rst, int dir, void *ph,
+                       hipStream_t st);
 void launch_scalars_init(const MSState &s, int npart, int nslots, hipStream_t st);
 void launch_scalars_alpha(const MSState &s, int npart, hipStream_t st);
-void launch_scalars_beta(const MSState &s, int npart, hipStream_t st);
-// Shift update.  yt receives sum_i c_i alpha^i p_i: the FP64 y when y64, else a running sum in
-// the storage precision of p.  xt (FP32 path only, else null) receives alpha p_base: the FP64
-// x0 when x64, else a running sum.  The FP64 path always uses y64 (and no xt).  xs (null, or
-// FP64 vectors [slot][NS][12][vs], FP32 directions only) receives every shift's own solution,
-// x_i += alpha^i p_i, for the per-shift true-residual check.
-void launch_shift_update(int prec, const Geom &g, const MSState &s, const void *r, void *p, void *yt, bool y64,
-                         void *xt, bool x64, int dir, void *ph, double2 *xs, hipStream_t st);
-// FP32 path: y += yacc, yacc = 0 (and x0 += x0acc, x0acc = 0 when x0acc is not null)
-void launch_fold(const Geom &g, Slots sl, int max_slots, double2 *y, void *yacc, double2 *x0, void *x0acc,
-                 hipStream_t st);
+void launch_scalars_beta(int prec, const MSState &s, int npart, hipStream_t st);
+// p_out = r + beta p_in of the base system, slots of the list that are not done; r at
+// slot * rst, p_in and p_out at slot * pst units.
+void launch_base_direction(int prec, const Geom &g, const MSState &s, const void *r, size_t rst, const void *p_in,
+                           void *p_out, size_t pst, hipStream_t st);
+// Ends the block: what the block update has to do, blk_n = 0, and the new scales of 16-bit
+// directions.  base_inline: the block update writes the base direction too.
+void launch_block_end(const MSState &s, bool base_inline, int dir, hipStream_t st);
+// The block update: y, x0 (null in the FP64 path) and every direction that is still needed,
+// from the ring (slot stride K vectors) and the directions at the block's start (the base one at
+// entry base_sel of the slot's directions; slot stride pst units).  xs (null, or FP64 vectors
+// [slot][NS][12][vs]) receives every shift's own solution.
+void launch_block_update(int prec, const Geom &g, const MSState &s, const void *ring, void *p, size_t pst,
+                         int base_sel, double2 *y, double2 *x0, int dir, void *ph, double2 *xs, hipStream_t st);
 void launch_compact(const MSState &s, hipStream_t st);
 // Evaluated precision: FP32 vectors of the listed slots (v + slot * slot_stride + extra, in
 // float4 units) rounded in place to FP16 (mode 1, scaled by sqrt(|r|^2 / (24 V)) of the slot)
@@ -135,7 +154,7 @@ void launch_compact(const MSState &s, hipStream_t st);
 void launch_round16(const Geom &g, const MSState &s, void *v, size_t slot_stride, size_t extra, int mode,
                     hipStream_t st);
 void launch_reliable(int prec, const Geom &g, const MSState &s, const Source &src, const double2 *ap64,
-                     void *r, hipStream_t st);
+                     void *r, size_t rst, hipStream_t st);
 void launch_scalars_rr(const MSState &s, int npart, hipStream_t st);
 
 // Per-shift check (FP64 vectors, slot stride 12 vs, the first nslots slots):

@@ -10,10 +10,10 @@
 //                  H^2 + sigma (Eq. 4).
 //  k_cg_init ...   multi-shift CG for (D_W^dag D_W + q_i) x_i = b (Eqs. 6-8): the stencil
 //                  epilogues sum <p, A p> = |D_W p|^2 + s0 |p|^2 in the first stencil and
-//                  update the residual in place in the second; fused update of every active
-//                  shift's search direction plus the
-//                  running rational sum y = c_0 b + sum_i c_i x_i, scalar recurrences on the
-//                  device (one wave per right-hand side), FP64 residual replacement.
+//                  update the residual in the second; scalar recurrences on the device (one wave
+//                  per right-hand side); every K iterations one update of all active shifts'
+//                  directions and of y = c_0 b + sum_i c_i x_i from the residuals kept since the
+//                  last one; FP64 residual replacement.
 //  k_contract      q(x) += 1/2 [gamma5 D_ov phi](x, alpha, a) on the probed sites (Eq. 16), or
 //                  the probing estimate of tr D_W^-1 (x, x) from the unshifted solve.
 //  k_multi_dot ... low-mode deflation: many dot products and linear combinations at once
@@ -236,7 +236,7 @@ __device__ __forceinline__ void unit_store_stream(float4 *p, size_t vs, int k, i
 //   EPI 0  out = d
 //   EPI 1  out = d + sigma aux;                         returns Re <aux, out>(s)
 //   EPI 3  out = d;                                     returns |d|^2 + sigma |self|^2
-//   EPI 2  a = d + sigma aux, not stored; out, which holds the residual r, becomes r - alpha a;
+//   EPI 2  a = d + sigma aux, not stored; out = r - alpha a with the residual r at out + r_ofs;
 //          returns |r - alpha a|^2 (a slot whose status is not OK keeps r: alpha is taken as 0)
 // In a CG iteration on H^2 + sigma (D_W^dag D_W + sigma) the first stencil D_W p with EPI 3
 // yields <p, (H^2 + sigma) p> = |D_W p|^2 + sigma |p|^2, so alpha is known before the second
@@ -246,11 +246,11 @@ template <class T, int EPI>
 __device__ __forceinline__ double stencil_epilogue(cpx<T> d[12], const cpx<T> self[12],
                                                    const typename Store<T>::vec *aux,
                                                    typename Store<T>::vec *out, size_t vs, int s, T sigma,
-                                                   T alpha, bool ok) {
+                                                   T alpha, bool ok, ptrdiff_t r_ofs) {
     constexpr int UN = Store<T>::units, CU = 12 / UN;   // units per spinor, complexes per unit
     double acc = 0.0;
     if constexpr (EPI == 2) {
-        if (!ok) alpha = T(0);   // a broken-down slot keeps its residual (written back unchanged)
+        if (!ok) alpha = T(0);   // a broken-down slot keeps its residual
     }
 #pragma unroll
     for (int k = 0; k < UN; ++k) {
@@ -267,7 +267,7 @@ __device__ __forceinline__ double stencil_epilogue(cpx<T> d[12], const cpx<T> se
         }
         if constexpr (EPI == 2) {
             cpx<T> r[CU];
-            unit_load_stream(out, vs, k, s, r);
+            unit_load_stream(out + r_ofs, vs, k, s, r);
 #pragma unroll
             for (int j = 0; j < CU; ++j) {
                 r[j] = r[j] - alpha * dk[j];
@@ -330,7 +330,8 @@ __global__ __launch_bounds__(kBlock) void k_dslash(const typename Store<T>::link
                                                    size_t aux_stride, size_t aux_extra, Geom g, T kappa, T sigma,
                                                    Slots sl, int lgR, int nsb, double *__restrict__ partial,
                                                    size_t pstride, const double *__restrict__ alpha,
-                                                   const int *__restrict__ status) {
+                                                   const int *__restrict__ status, ptrdiff_t r_ofs,
+                                                   const int *__restrict__ done) {
     const int R = 1 << lgR;
     const int L = xcd_swizzle(blockIdx.x, gridDim.x);
     const int sb = L % nsb, rg = L / nsb;
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(kBlock) void k_dslash(const typename Store<T>::link
     const int k = rg * R + rl;
     const int slot = k < cnt ? slot_of(sl, k) : 0;
     double dot = 0.0;
-    if (k < cnt && s < g.V) {
+    if (k < cnt && s < g.V && !(done && done[slot])) {
         const auto *src = in + slot * in_stride + in_extra;
         cpx<T> acc[12];
         hop_site<T, DAG ? -1 : 1>(U, g, src, s, acc);
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(kBlock) void k_dslash(const typename Store<T>::link
         for (int c = 0; c < 12; ++c) v[c] = self[c] - kappa * acc[c];
         dot = stencil_epilogue<T, EPI>(v, self, aux + slot * aux_stride + aux_extra, out + slot * out_stride, g.vs, s,
                                        sigma, EPI == 2 ? (T)alpha[slot] : T(0),
-                                       EPI == 2 ? status[slot] == kStatusOK : true);
+                                       EPI == 2 ? status[slot] == kStatusOK : true, r_ofs);
     }
     if constexpr (EPI != 0) {
         // lanes with equal (lane mod R) hold the same right-hand side
@@ -383,7 +384,8 @@ __global__ __launch_bounds__(kBlock) void k_dslash_f32(const float4 *__restrict_
                                                        size_t aux_stride, size_t aux_extra, Geom g, float kappa,
                                                        float sigma, Slots sl, int nsb, double *__restrict__ partial,
                                                        size_t pstride, const double *__restrict__ alpha,
-                                                       const int *__restrict__ status) {
+                                                       const int *__restrict__ status, ptrdiff_t r_ofs,
+    const int *__restrict__ done) {
     constexpr int SF = DAG ? -1 : 1;
     const int L = xcd_swizzle(blockIdx.x, gridDim.x);
     const int sb = L % nsb, rg = L / nsb;
@@ -411,8 +413,8 @@ __global__ __launch_bounds__(kBlock) void k_dslash_f32(const float4 *__restrict_
     for (int r = 0; r < NR; ++r) {
         const int k = k0 + r;
         if (k >= cnt) break;  // uniform over the block
-        if (!site_ok) continue;
         const int slot = slot_of(sl, k);
+        if (!site_ok || (done && done[slot])) continue;
         const float4 *src = in + slot * in_stride + in_extra;
         cpx<float> acc[12], u[9], p[12], h[6], w[6];
 #pragma unroll
@@ -439,7 +441,7 @@ __global__ __launch_bounds__(kBlock) void k_dslash_f32(const float4 *__restrict_
         for (int c = 0; c < 12; ++c) v[c] = p[c] - kappa * acc[c];
         dot[r] = stencil_epilogue<float, EPI>(v, p, aux + slot * aux_stride + aux_extra, out + slot * out_stride, g.vs,
                                               sv, sigma, EPI == 2 ? (float)alpha[slot] : 0.f,
-                                              EPI == 2 ? status[slot] == kStatusOK : true);
+                                              EPI == 2 ? status[slot] == kStatusOK : true, r_ofs);
     }
     if constexpr (EPI != 0) {
         __shared__ double lds[NR][kBlock / 64];
@@ -472,7 +474,8 @@ __global__ __launch_bounds__(kBlock) void k_dslash_f32_tile(const float4 *__rest
                                                             size_t aux_extra, Geom g, float kappa, float sigma,
                                                             Slots sl, int nsb, double *__restrict__ partial,
                                                             size_t pstride, const double *__restrict__ alpha,
-                                                            const int *__restrict__ status) {
+                                                            const int *__restrict__ status, ptrdiff_t r_ofs,
+    const int *__restrict__ done) {
     constexpr int SF = DAG ? -1 : 1;
     constexpr int kTileSites = kBlock + 2 * 64;
     __shared__ float4 tile[6][kTileSites];
@@ -514,6 +517,7 @@ __global__ __launch_bounds__(kBlock) void k_dslash_f32_tile(const float4 *__rest
         const int k = k0 + r;
         if (k >= cnt) break;  // uniform over the block
         const int slot = slot_of(sl, k);
+        if (done && done[slot]) continue;  // uniform over the block
         const float4 *src = in + slot * in_stride + in_extra;
         __syncthreads();  // the previous right-hand side is done with the tile
 #pragma unroll
@@ -567,7 +571,7 @@ __global__ __launch_bounds__(kBlock) void k_dslash_f32_tile(const float4 *__rest
         for (int c = 0; c < 12; ++c) v[c] = p[c] - kappa * acc[c];
         dot[r] = stencil_epilogue<float, EPI>(v, p, aux + slot * aux_stride + aux_extra, out + slot * out_stride, g.vs,
                                               s, sigma, EPI == 2 ? (float)alpha[slot] : 0.f,
-                                              EPI == 2 ? status[slot] == kStatusOK : true);
+                                              EPI == 2 ? status[slot] == kStatusOK : true, r_ofs);
     }
     if constexpr (EPI != 0) {
         __shared__ double lds[NR][kBlock / 64];
@@ -595,7 +599,8 @@ __device__ __forceinline__ void dslash_f32_plane_body(const float4 *__restrict__
                                                              size_t aux_extra, Geom g, float kappa, float sigma,
                                                              Slots sl, int nsb, double *__restrict__ partial,
                                                              size_t pstride, const double *__restrict__ alpha,
-                                                             const int *__restrict__ status) {
+                                                             const int *__restrict__ status, ptrdiff_t r_ofs,
+    const int *__restrict__ done) {
     constexpr int SF = DAG ? -1 : 1;
     __shared__ float4 tile[6][kBlock];
     // XYL: the plane's x and y links in LDS (the backward ones are the neighbours' forward
@@ -631,6 +636,7 @@ __device__ __forceinline__ void dslash_f32_plane_body(const float4 *__restrict__
         const int k = k0 + r;
         if (k >= cnt) break;  // uniform over the block
         const int slot = slot_of(sl, k);
+        if (done && done[slot]) continue;  // uniform over the block
         const float4 *src = in + slot * in_stride + in_extra;
         __syncthreads();  // the previous right-hand side is done with the tile
 #pragma unroll
@@ -683,7 +689,7 @@ __device__ __forceinline__ void dslash_f32_plane_body(const float4 *__restrict__
         for (int c = 0; c < 12; ++c) v[c] = p[c] - kappa * acc[c];
         double d = stencil_epilogue<float, EPI>(v, p, aux + slot * aux_stride + aux_extra, out + slot * out_stride,
                                                 g.vs, s, sigma, EPI == 2 ? (float)alpha[slot] : 0.f,
-                                                EPI == 2 ? status[slot] == kStatusOK : true);
+                                                EPI == 2 ? status[slot] == kStatusOK : true, r_ofs);
         if constexpr (EPI != 0) {
             d = wave_sum(d);
             if (lane == 0) ldsdot[r][wv] = d;
@@ -709,9 +715,10 @@ __global__ __launch_bounds__(kBlock) void k_dslash_f32_plane(const float4 *__res
                                                              size_t aux_extra, Geom g, float kappa, float sigma,
                                                              Slots sl, int nsb, double *__restrict__ partial,
                                                              size_t pstride, const double *__restrict__ alpha,
-                                                             const int *__restrict__ status) {
+                                                             const int *__restrict__ status, ptrdiff_t r_ofs,
+    const int *__restrict__ done) {
     dslash_f32_plane_body<NR, DAG, EPI, false>(U, in, in_stride, in_extra, out, out_stride, aux, aux_stride, aux_extra,
-                                               g, kappa, sigma, sl, nsb, partial, pstride, alpha, status);
+                                               g, kappa, sigma, sl, nsb, partial, pstride, alpha, status, r_ofs, done);
 }
 
 // The same with the x and y links in LDS, at 3 waves per SIMD.
@@ -720,9 +727,10 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
     const float4 *__restrict__ U, const float4 *__restrict__ in, size_t in_stride, size_t in_extra,
     float4 *__restrict__ out, size_t out_stride, const float4 *__restrict__ aux, size_t aux_stride, size_t aux_extra,
     Geom g, float kappa, float sigma, Slots sl, int nsb, double *__restrict__ partial, size_t pstride,
-    const double *__restrict__ alpha, const int *__restrict__ status) {
+    const double *__restrict__ alpha, const int *__restrict__ status, ptrdiff_t r_ofs,
+    const int *__restrict__ done) {
     dslash_f32_plane_body<NR, DAG, EPI, true>(U, in, in_stride, in_extra, out, out_stride, aux, aux_stride, aux_extra,
-                                              g, kappa, sigma, sl, nsb, partial, pstride, alpha, status);
+                                              g, kappa, sigma, sl, nsb, partial, pstride, alpha, status, r_ofs, done);
 }
 
 // Stencil on xy-tiles with the links read for every right-hand side (FP64 kind 1, FP32 kind 4):
@@ -788,7 +796,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TileWave
                                                            size_t aux_stride, size_t aux_extra, Geom g, T kappa,
                                                            T sigma, Slots sl, int nsb, double *__restrict__ partial,
                                                            size_t pstride, const double *__restrict__ alpha,
-                                                           const int *__restrict__ status) {
+                                                           const int *__restrict__ status, ptrdiff_t r_ofs,
+    const int *__restrict__ done) {
     using vec = typename Store<T>::vec;
     using link = typename Store<T>::link;
     constexpr int SF = DAG ? -1 : 1;
@@ -834,6 +843,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TileWave
         const int k = k0 + r;
         if (k >= cnt) break;  // uniform over the block
         const int slot = slot_of(sl, k);
+        if (done && done[slot]) continue;  // uniform over the block
         const vec *src = in + slot * in_stride + in_extra;
         // the links are re-read for every right-hand side: an empty asm makes the base pointer
         // opaque in each iteration, so that the compiler does not hoist all eight links out of
@@ -882,7 +892,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(TileWave
         for (int c = 0; c < 12; ++c) v[c] = p[c] - kappa * acc[c];
         double d = stencil_epilogue<T, EPI>(v, p, aux + slot * aux_stride + aux_extra, out + slot * out_stride, g.vs, s,
                                             sigma, EPI == 2 ? (T)alpha[slot] : T(0),
-                                            EPI == 2 ? status[slot] == kStatusOK : true);
+                                            EPI == 2 ? status[slot] == kStatusOK : true, r_ofs);
         if constexpr (EPI != 0) {
             d = wave_sum(d);
             if (lane == 0) ldsdot[r][wv] = d;
@@ -957,7 +967,7 @@ template <class T, int NR, bool DAG, int EPI>
 static void launch_tile_rl(const void *U, const void *in, size_t in_stride, size_t in_extra, void *out,
                            size_t out_stride, const void *aux, size_t aux_stride, size_t aux_extra, const Geom &g,
                            double kappa, double sigma, Slots sl, int max_slots, double *partial, const double *alpha,
-                           const int *status, hipStream_t st) {
+                           const int *status, ptrdiff_t r_ofs, const int *done, hipStream_t st) {
     using vec = typename Store<T>::vec;
     using link = typename Store<T>::link;
     const int nsb = tile_blocks(g);
@@ -969,21 +979,21 @@ static void launch_tile_rl(const void *U, const void *in, size_t in_stride, size
     hipLaunchKernelGGL((k_dslash_tile_rl<T, NR, DAG, EPI>), dim3(nsb * ngr), dim3(g.nx * g.tile_y), lds, st,
                        (const link *)U, (const vec *)in, in_stride, in_extra, (vec *)out, out_stride, (const vec *)aux,
                        aux_stride, aux_extra, g, (T)kappa, (T)sigma, sl, nsb, partial, partial_stride(g), alpha,
-                       status);
+                       status, r_ofs, done);
 }
 
 template <class T, bool DAG, int EPI>
 static void launch_dslash_t(const void *U, const void *in, size_t in_stride, size_t in_extra, void *out,
                             size_t out_stride, const void *aux, size_t aux_stride, size_t aux_extra, const Geom &g,
                             double kappa, double sigma, Slots sl, int max_slots, double *partial, const double *alpha,
-                            const int *status, hipStream_t st) {
+                            const int *status, ptrdiff_t r_ofs, const int *done, hipStream_t st) {
     using vec = typename Store<T>::vec;
     using link = typename Store<T>::link;
     if constexpr (std::is_same<T, double>::value) {
         if (g.f64_kind == 1) {
 #define SMPQ_F64T(NR)                                                                                             \
     launch_tile_rl<double, NR, DAG, EPI>(U, in, in_stride, in_extra, out, out_stride, aux, aux_stride, aux_extra, g, \
-                                         kappa, sigma, sl, max_slots, partial, alpha, status, st)
+                                         kappa, sigma, sl, max_slots, partial, alpha, status, r_ofs, done, st)
             if (g.f64_nr == 1) SMPQ_F64T(1);
             else if (g.f64_nr == 2) SMPQ_F64T(2);
             else if (g.f64_nr == 8) SMPQ_F64T(8);
@@ -998,50 +1008,51 @@ static void launch_dslash_t(const void *U, const void *in, size_t in_stride, siz
     const int ngr = (max_slots + R - 1) / R;
     hipLaunchKernelGGL((k_dslash<T, DAG, EPI>), dim3(nsb * ngr), dim3(kBlock), 0, st, (const link *)U,
                        (const vec *)in, in_stride, in_extra, (vec *)out, out_stride, (const vec *)aux, aux_stride,
-                       aux_extra, g, (T)kappa, (T)sigma, sl, lgR, nsb, partial, partial_stride(g), alpha, status);
+                       aux_extra, g, (T)kappa, (T)sigma, sl, lgR, nsb, partial, partial_stride(g), alpha, status, r_ofs, done);
 }
 
 template <int NR, bool DAG, int EPI, int KIND>
 static void launch_f32(const void *U, const void *in, size_t in_stride, size_t in_extra, void *out, size_t out_stride,
                        const void *aux, size_t aux_stride, size_t aux_extra, const Geom &g, double kappa, double sigma,
                        Slots sl, int max_slots, double *partial, const double *alpha, const int *status,
-                       hipStream_t st) {
+                       ptrdiff_t r_ofs, const int *done, hipStream_t st) {
     const int nsb = KIND == 2 ? tile_blocks(g) : site_blocks(g);
     const int ngr = (max_slots + NR - 1) / NR;
     if constexpr (KIND == 2)
         hipLaunchKernelGGL((k_dslash_f32_tile<NR, DAG, EPI>), dim3(nsb * ngr), dim3(g.nx * g.tile_y), 0, st,
                            (const float4 *)U, (const float4 *)in, in_stride, in_extra, (float4 *)out, out_stride,
                            (const float4 *)aux, aux_stride, aux_extra, g, (float)kappa, (float)sigma, sl, nsb, partial,
-                           partial_stride(g), alpha, status);
+                           partial_stride(g), alpha, status, r_ofs, done);
     else if constexpr (KIND == 3)
         hipLaunchKernelGGL((k_dslash_f32_plane_xyl<NR, DAG, EPI>), dim3(nsb * ngr), dim3(kBlock), 0, st,
                            (const float4 *)U, (const float4 *)in, in_stride, in_extra, (float4 *)out, out_stride,
                            (const float4 *)aux, aux_stride, aux_extra, g, (float)kappa, (float)sigma, sl, nsb, partial,
-                           partial_stride(g), alpha, status);
+                           partial_stride(g), alpha, status, r_ofs, done);
     else if constexpr (KIND == 1)
         hipLaunchKernelGGL((k_dslash_f32_plane<NR, DAG, EPI>), dim3(nsb * ngr), dim3(kBlock), 0, st,
                            (const float4 *)U, (const float4 *)in, in_stride, in_extra, (float4 *)out, out_stride,
                            (const float4 *)aux, aux_stride, aux_extra, g, (float)kappa, (float)sigma, sl, nsb, partial,
-                           partial_stride(g), alpha, status);
+                           partial_stride(g), alpha, status, r_ofs, done);
     else
         hipLaunchKernelGGL((k_dslash_f32<NR, DAG, EPI>), dim3(nsb * ngr), dim3(kBlock), 0, st, (const float4 *)U,
                            (const float4 *)in, in_stride, in_extra, (float4 *)out, out_stride, (const float4 *)aux,
                            aux_stride, aux_extra, g, (float)kappa, (float)sigma, sl, nsb, partial, partial_stride(g),
-                           alpha, status);
+                           alpha, status, r_ofs, done);
 }
 
 template <bool DAG, int EPI>
 static void launch_f32_tuned(const void *U, const void *in, size_t in_stride, size_t in_extra, void *out,
                              size_t out_stride, const void *aux, size_t aux_stride, size_t aux_extra, const Geom &g,
                              double kappa, double sigma, Slots sl, int max_slots, double *partial,
-                             const double *alpha, const int *status, hipStream_t st) {
+                             const double *alpha, const int *status, ptrdiff_t r_ofs, const int *done,
+                             hipStream_t st) {
 #define SMPQ_F32(NR, PL)                                                                                       \
     launch_f32<NR, DAG, EPI, PL>(U, in, in_stride, in_extra, out, out_stride, aux, aux_stride, aux_extra, g, kappa, \
-                                 sigma, sl, max_slots, partial, alpha, status, st)
+                                 sigma, sl, max_slots, partial, alpha, status, r_ofs, done, st)
     if (g.f32_kind == 4) {
 #define SMPQ_F32RL(NR)                                                                                            \
     launch_tile_rl<float, NR, DAG, EPI>(U, in, in_stride, in_extra, out, out_stride, aux, aux_stride, aux_extra, g, \
-                                        kappa, sigma, sl, max_slots, partial, alpha, status, st)
+                                        kappa, sigma, sl, max_slots, partial, alpha, status, r_ofs, done, st)
         if (g.f32_nr == 1) SMPQ_F32RL(1);
         else if (g.f32_nr == 2) SMPQ_F32RL(2);
         else if (g.f32_nr == 8) SMPQ_F32RL(8);
@@ -1070,9 +1081,10 @@ static void launch_f32_tuned(const void *U, const void *in, size_t in_stride, si
 void launch_dslash(int prec, bool dag, int epi, const void *U, const void *in, size_t in_stride, size_t in_extra,
                    void *out, size_t out_stride, const void *aux, size_t aux_stride, size_t aux_extra, const Geom &g,
                    double kappa, double sigma, Slots sl, int max_slots, double *partial, hipStream_t st,
-                   const double *alpha, const int *status) {
+                   const double *alpha, const int *status, ptrdiff_t r_ofs, const int *done) {
     using Fn = void (*)(const void *, const void *, size_t, size_t, void *, size_t, const void *, size_t, size_t,
-                        const Geom &, double, double, Slots, int, double *, const double *, const int *, hipStream_t);
+                        const Geom &, double, double, Slots, int, double *, const double *, const int *, ptrdiff_t,
+                        const int *, hipStream_t);
     if (!valid_tuning(prec, g)) throw std::invalid_argument("stencil variant does not fit this lattice");
     if (epi < 0 || epi > 3) throw std::invalid_argument("unknown stencil epilogue");
     if (epi == 2 && (!alpha || !status)) throw std::invalid_argument("the residual epilogue needs alpha and status");
@@ -1088,7 +1100,7 @@ void launch_dslash(int prec, bool dag, int epi, const void *U, const void *in, s
     const Fn f = table[prec == 0 ? 0 : 1][dag ? 1 : 0][epi];
     if (!f) throw std::invalid_argument("stencil epilogue not built for this precision and direction");
     f(U, in, in_stride, in_extra, out, out_stride, aux, aux_stride, aux_extra, for_direction(g, prec, dag), kappa,
-      sigma, sl, max_slots, partial, alpha, status, st);
+      sigma, sl, max_slots, partial, alpha, status, r_ofs, done, st);
 }
 
 // ------------------------------------------------------------------ element-wise kernels
@@ -1228,14 +1240,13 @@ __device__ __forceinline__ cpx<double> source_entry(const Source &src, int slot,
 
 int unit_parts(int prec, const Geom &g) { return (prec == 0 ? 12 : 6) * site_blocks(g); }
 
-// r = b, p_i = b for every shift, y = c0 b (FP64), running accumulators yacc = x0acc = 0 in the
-// iteration precision (FP32 path only; the FP64 path accumulates into y directly and has no x0);
-// partial = |b|^2 per block.
+// r = b, p_i = b for every shift, y = c0 b (FP64), x0 = 0 (FP32 path only; the FP64 path has no
+// x0); partial = |b|^2 per block.
 template <class T, int D>
 __global__ __launch_bounds__(kBlock) void k_cg_init(Geom g, Source src, int NS, double c0,
-                                                    typename Store<T>::vec *r, typename Store<T>::vec *p, double2 *y,
-                                                    typename Store<T>::vec *yacc, double2 *x0,
-                                                    typename Store<T>::vec *x0acc, double *partial, size_t pstride) {
+                                                    typename Store<T>::vec *r, size_t rst,
+                                                    typename Store<T>::vec *p, size_t pst, double2 *y, double2 *x0,
+                                                    double *partial, size_t pstride) {
     constexpr int C = Unit<T>::C;
     const int slot = blockIdx.y;
     const int nsb = site_blocks(g);
@@ -1244,52 +1255,49 @@ __global__ __launch_bounds__(kBlock) void k_cg_init(Geom g, Source src, int NS, 
     const size_t rs = Store<T>::units * g.vs;
     double nrm = 0.0;
     if (s < g.V) {
-        cpx<T> bt[C], z[C];
+        cpx<T> bt[C];
         double2 *ys = y + (size_t)slot * 12 * g.vs;
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             const int c = u * C + i;
             const cpx<double> b = source_entry(src, slot, c, s, g.vs);
             bt[i] = {(T)b.re, (T)b.im};
-            z[i] = {T(0), T(0)};
             nrm += (double)bt[i].re * bt[i].re + (double)bt[i].im * bt[i].im;
             st64(ys, g.vs, c, s, c0 * b);
             if (x0) st64(x0 + (size_t)slot * 12 * g.vs, g.vs, c, s, {0.0, 0.0});
         }
-        Unit<T>::store(r + slot * rs, g.vs, u, s, bt);
+        Unit<T>::store(r + slot * rst, g.vs, u, s, bt);
         if constexpr (D == kDirF32) {
-            for (int i = 0; i < NS; ++i) Unit<T>::store(p + ((size_t)slot * NS + i) * rs, g.vs, u, s, bt);
+            for (int i = 0; i < NS; ++i) Unit<T>::store(p + slot * pst + i * rs, g.vs, u, s, bt);
         } else {
             // the base direction; the 16-bit ones follow from r once |b| is known (k_dir16_init)
-            Unit<T>::store(p + slot * rs, g.vs, u, s, bt);
+            Unit<T>::store(p + slot * pst, g.vs, u, s, bt);
         }
-        if (yacc) Unit<T>::store(yacc + slot * rs, g.vs, u, s, z);
-        if (x0acc) Unit<T>::store(x0acc + slot * rs, g.vs, u, s, z);
     }
     block_partial(nrm, partial, (size_t)slot * pstride + blockIdx.x);
 }
 
-void launch_cg_init(int prec, const Geom &g, const Source &src, int nslots, int NS, double c0, void *r, void *p,
-                    double2 *y, void *yacc, double2 *x0, void *x0acc, double *partial, int dir, hipStream_t st) {
+void launch_cg_init(int prec, const Geom &g, const Source &src, int nslots, int NS, double c0, void *r, size_t rst,
+                    void *p, size_t pst, double2 *y, double2 *x0, double *partial, int dir, hipStream_t st) {
     dim3 grid(unit_parts(prec, g), nslots);
     if (prec == 0) {
         if (dir != kDirF32) throw std::invalid_argument("16-bit directions need the FP32 path");
-        hipLaunchKernelGGL((k_cg_init<double, kDirF32>), grid, dim3(kBlock), 0, st, g, src, NS, c0, (double2 *)r,
-                           (double2 *)p, y, (double2 *)yacc, x0, (double2 *)x0acc, partial, partial_stride(g));
+        hipLaunchKernelGGL((k_cg_init<double, kDirF32>), grid, dim3(kBlock), 0, st, g, src, NS, c0, (double2 *)r, rst,
+                           (double2 *)p, pst, y, x0, partial, partial_stride(g));
         return;
     }
     if (dir == kDirF32)
-        hipLaunchKernelGGL((k_cg_init<float, kDirF32>), grid, dim3(kBlock), 0, st, g, src, NS, c0, (float4 *)r,
-                           (float4 *)p, y, (float4 *)yacc, x0, (float4 *)x0acc, partial, partial_stride(g));
+        hipLaunchKernelGGL((k_cg_init<float, kDirF32>), grid, dim3(kBlock), 0, st, g, src, NS, c0, (float4 *)r, rst,
+                           (float4 *)p, pst, y, x0, partial, partial_stride(g));
     else   // only the base direction's layout depends on the 16-bit format
-        hipLaunchKernelGGL((k_cg_init<float, kDirF16>), grid, dim3(kBlock), 0, st, g, src, NS, c0, (float4 *)r,
-                           (float4 *)p, y, (float4 *)yacc, x0, (float4 *)x0acc, partial, partial_stride(g));
+        hipLaunchKernelGGL((k_cg_init<float, kDirF16>), grid, dim3(kBlock), 0, st, g, src, NS, c0, (float4 *)r, rst,
+                           (float4 *)p, pst, y, x0, partial, partial_stride(g));
 }
 
 // 16-bit directions: p_i = b = r for every shift but the base, stored with the scale that
 // k_scalars_init set from |b| (so that the entries of any source are near 1).
 template <int D>
-__global__ __launch_bounds__(kBlock) void k_dir16_init(Geom g, MSState S, const float4 *r, void *ph) {
+__global__ __launch_bounds__(kBlock) void k_dir16_init(Geom g, MSState S, const float4 *r, size_t rst, void *ph) {
     const int slot = blockIdx.y;
     const int nsb = site_blocks(g);
     const int u = blockIdx.x / nsb;
@@ -1297,35 +1305,31 @@ __global__ __launch_bounds__(kBlock) void k_dir16_init(Geom g, MSState S, const 
     if (s >= g.V) return;
     const size_t rs = Store<float>::units * g.vs;
     cpx<float> v[2];
-    Unit<float>::load(r + slot * rs, g.vs, u, s, v);
+    Unit<float>::load(r + slot * rst, g.vs, u, s, v);
     for (int i = 0; i < S.NS; ++i)
         if (i != S.i0)
             store_dir16<D>(static_cast<typename Dir16<D>::v *>(ph) + ((size_t)slot * S.NS + i) * rs, g.vs, u, s,
                            (float)(1.0 / S.sh_scale[slot * S.NS + i]), v);
 }
 
-void launch_dir16_init(const Geom &g, const MSState &s, int nslots, const void *r, int dir, void *ph, hipStream_t st) {
+void launch_dir16_init(const Geom &g, const MSState &s, int nslots, const void *r, size_t rst, int dir, void *ph,
+                       hipStream_t st) {
     dim3 grid(unit_parts(1, g), nslots);
     if (dir == kDirF16)
-        hipLaunchKernelGGL(k_dir16_init<kDirF16>, grid, dim3(kBlock), 0, st, g, s, (const float4 *)r, ph);
+        hipLaunchKernelGGL(k_dir16_init<kDirF16>, grid, dim3(kBlock), 0, st, g, s, (const float4 *)r, rst, ph);
     else if (dir == kDirBF16)
-        hipLaunchKernelGGL(k_dir16_init<kDirBF16>, grid, dim3(kBlock), 0, st, g, s, (const float4 *)r, ph);
+        hipLaunchKernelGGL(k_dir16_init<kDirBF16>, grid, dim3(kBlock), 0, st, g, s, (const float4 *)r, rst, ph);
     else
         throw std::invalid_argument("launch_dir16_init: not a 16-bit format");
 }
 
 // ------------------------------------------------------------------ CG scalars (one wave per slot)
-// Slots >= nslots are not part of this batch and start finished.
+// Lane i holds shift i (NS <= 32).  Slots >= nslots are not part of this batch and start finished.
 __global__ void k_scalars_init(MSState S, int npart, int nslots) {
     const int slot = blockIdx.x;
     const double rr = slot < nslots ? wave_sum_partials(S.partial + (size_t)slot * S.pstride, npart) : 0.0;
-    if (threadIdx.x != 0) return;
-    S.rr[slot] = rr;
-    S.bnorm[slot] = sqrt(rr);
-    S.alpha_prev[slot] = 1.0;
-    S.beta_prev[slot] = 0.0;
-    S.alpha[slot] = 0.0;
-    for (int i = 0; i < S.NS; ++i) {
+    const int i = threadIdx.x;
+    if (i < S.NS) {
         const int k = slot * S.NS + i;
         S.zeta[k] = 1.0;
         S.zeta_prev[k] = 1.0;
@@ -1334,14 +1338,24 @@ __global__ void k_scalars_init(MSState S, int npart, int nslots) {
         S.sh_iters[k] = 0;
         S.sh_scale[k] = rr > 0.0 ? sqrt(rr) * S.dir_norm : 1.0;
     }
+    if (i != 0) return;
+    S.rr[slot] = rr;
+    S.bnorm[slot] = sqrt(rr);
+    S.alpha_prev[slot] = 1.0;
+    S.beta_prev[slot] = 0.0;
+    S.alpha[slot] = 0.0;
+    S.beta[slot] = 0.0;
     S.done[slot] = !(rr > 0.0);
     S.iters[slot] = 0;
     S.status[slot] = kStatusOK;
-    S.upd_n[slot] = 0;
+    S.blk_n[slot] = 0;
+    S.fl_m[slot] = 0;
+    S.fl_act[slot] = rr > 0.0 ? (unsigned)((1ull << S.NS) - 1) : 0u;
     S.cnt_entries[slot] = 0;
-    S.cnt_pupd[slot] = 0;
     S.cnt_active[slot] = 0;
-    S.cnt_base_pupd[slot] = 0;
+    S.cnt_fl[slot] = 0;
+    S.cnt_fl_r[slot] = 0;
+    S.cnt_fl_p[slot] = 0;
 }
 
 void launch_scalars_init(const MSState &s, int npart, int nslots, hipStream_t st) {
@@ -1352,293 +1366,333 @@ void launch_scalars_init(const MSState &s, int npart, int nslots, hipStream_t st
 __global__ void k_scalars_alpha(MSState S, int npart) {
     if ((int)blockIdx.x >= *S.count) return;
     const int slot = S.list[blockIdx.x];
+    if (S.done[slot]) return;
     const double pap = wave_sum_partials(S.partial + (size_t)slot * S.pstride, npart);
-    if (threadIdx.x != 0) return;
+    const int i = threadIdx.x;
     if (!(pap > 0.0) || !isfinite(pap)) {
-        S.status[slot] = kStatusBreakdown;
-        S.alpha[slot] = 0.0;
+        if (i == 0) {
+            S.status[slot] = kStatusBreakdown;
+            S.alpha[slot] = 0.0;
+        }
         return;
     }
     const double a = S.rr[slot] / pap;
+    if (i == 0) S.alpha[slot] = a;
+    if (i >= S.NS) return;
+    const int k = slot * S.NS + i;
+    if (!S.sh_active[k]) return;
     const double ap = S.alpha_prev[slot], bp = S.beta_prev[slot];
-    S.alpha[slot] = a;
-    for (int i = 0; i < S.NS; ++i) {
-        const int k = slot * S.NS + i;
-        if (!S.sh_active[k]) continue;
-        const double z = S.zeta[k], zp = S.zeta_prev[k];
-        S.zeta_new[k] = z * zp * ap / (a * bp * (zp - z) + zp * ap * (1.0 + S.delta[i] * a));
-    }
+    const double z = S.zeta[k], zp = S.zeta_prev[k];
+    S.zeta_new[k] = z * zp * ap / (a * bp * (zp - z) + zp * ap * (1.0 + S.delta[i] * a));
 }
 
 void launch_scalars_alpha(const MSState &s, int npart, hipStream_t st) {
     hipLaunchKernelGGL(k_scalars_alpha, dim3(s.B), dim3(64), 0, st, s, npart);
 }
 
-// beta_k = |r_{k+1}|^2/|r_k|^2; per active shift: alpha^i, beta^i, convergence
-// (zeta^i_{k+1} |r_{k+1}| <= tol |b|); build this iteration's update list.  The base
-// shift's direction keeps being updated while any shift of the slot is active.
+// beta_k = |r_{k+1}|^2/|r_k|^2; per active shift the block's coefficients a = alpha^i, b = beta^i,
+// z = zeta^i and convergence (zeta^i_{k+1} |r_{k+1}| <= tol |b|).  The base shift's direction
+// keeps being updated while any shift of the slot is active (a = 0 once it has converged).
+template <class T>
 __global__ void k_scalars_beta(MSState S, int npart) {
     if ((int)blockIdx.x >= *S.count) return;
     const int slot = S.list[blockIdx.x];
+    if (S.done[slot]) return;
     const double rrn = wave_sum_partials(S.partial + (size_t)slot * S.pstride, npart);
-    if (threadIdx.x != 0) return;
+    const int i = threadIdx.x;
     if (S.status[slot] != kStatusOK) {
-        S.done[slot] = 1;
-        S.upd_n[slot] = 0;
+        if (i == 0) S.done[slot] = 1;
         return;
     }
     const double a = S.alpha[slot];
     const double b = rrn / S.rr[slot];
-    const double rn = sqrt(rrn);
-    const double lim = S.tol * S.bnorm[slot];
-    const int it = S.iters[slot];
-    int n = 0, still = 0, npupd = 0;
-    for (int i = 0; i < S.NS; ++i) {
+    const int it = S.iters[slot], j = S.blk_n[slot];
+    const bool act = i < S.NS && S.sh_active[slot * S.NS + i];
+    bool conv = false;
+    if (i < S.NS) {
         const int k = slot * S.NS + i;
-        const int u = slot * S.NS + n;
-        if (S.sh_active[k]) {
+        double ha = 0.0, hb = i == S.i0 ? b : 0.0, hz = i == S.i0 ? 1.0 : 0.0;
+        if (act) {
             const double z = S.zeta[k], zn = S.zeta_new[k];
             const double ratio = zn / z;
-            const bool conv = zn * rn <= lim;
-            S.upd_idx[u] = i;
-            S.upd_cy[u] = S.c[i] * a * ratio;
-            S.upd_ax[u] = a * ratio;
-            S.upd_zeta[u] = zn;
-            S.upd_beta[u] = b * ratio * ratio;
-            S.upd_pupd[u] = (!conv || i == S.i0) ? 1 : 0;
-            ++n;
+            conv = zn * sqrt(rrn) <= S.tol * S.bnorm[slot];
+            ha = a * ratio;
+            hb = b * ratio * ratio;
+            hz = zn;
             if (conv) {
                 S.sh_active[k] = 0;
                 S.sh_iters[k] = it + 1;
-            } else {
-                ++still;
             }
             S.zeta_prev[k] = z;
             S.zeta[k] = zn;
-        } else if (i == S.i0) {
-            S.upd_idx[u] = i;
-            S.upd_cy[u] = 0.0;
-            S.upd_ax[u] = 0.0;
-            S.upd_zeta[u] = 1.0;
-            S.upd_beta[u] = b;
-            S.upd_pupd[u] = 1;
-            ++n;
         }
+        const size_t h = ((size_t)slot * S.K + j) * S.NS + i;
+        S.h_a[h] = ha;
+        S.h_cy[h] = S.c[i] * ha;
+        static_cast<T *>(S.h_b)[h] = (T)hb;
+        static_cast<T *>(S.h_z)[h] = (T)hz;
     }
-    if (still == 0) {  // slot finished: no direction needs updating any more
-        for (int e = 0; e < n; ++e) S.upd_pupd[slot * S.NS + e] = 0;
-        S.done[slot] = 1;
-    }
-    // 16-bit directions: the stored p_i is decoded with its current scale and the new one is
-    // stored divided by zeta^i_{k+1} |r_{k+1}| dir_norm, which keeps its entries near 1
-    for (int e = 0; e < n; ++e) {
-        const int u = slot * S.NS + e;
-        const int k = slot * S.NS + S.upd_idx[u];
-        S.upd_sold[u] = S.sh_scale[k];
-        if (S.upd_pupd[u]) {
-            double sc = S.upd_zeta[u] * rn * S.dir_norm;
-            if (!(sc > 0.0) || !isfinite(sc)) sc = S.sh_scale[k];
-            S.sh_scale[k] = sc;
-            S.upd_snew[u] = 1.0 / sc;
-            npupd++;
-            if (S.upd_idx[u] == S.i0) S.cnt_base_pupd[slot] += 1;
-        } else {
-            S.upd_snew[u] = 1.0;
-        }
-    }
-    S.upd_n[slot] = n;
-    S.cnt_entries[slot] += n;
-    S.cnt_pupd[slot] += npupd;
+    const unsigned long long listed = __ballot(act || i == S.i0), still = __ballot(act && !conv);
+    if (i != 0) return;
+    if (still == 0) S.done[slot] = 1;   // slot finished: no direction needs updating any more
+    S.cnt_entries[slot] += __popcll(listed);
     S.cnt_active[slot] += 1;
     S.alpha_prev[slot] = a;
     S.beta_prev[slot] = b;
+    S.beta[slot] = b;
     S.rr[slot] = rrn;
     S.iters[slot] = it + 1;
+    S.blk_n[slot] = j + 1;
 }
 
-void launch_scalars_beta(const MSState &s, int npart, hipStream_t st) {
-    hipLaunchKernelGGL(k_scalars_beta, dim3(s.B), dim3(64), 0, st, s, npart);
+void launch_scalars_beta(int prec, const MSState &s, int npart, hipStream_t st) {
+    if (prec == 0)
+        hipLaunchKernelGGL(k_scalars_beta<double>, dim3(s.B), dim3(64), 0, st, s, npart);
+    else
+        hipLaunchKernelGGL(k_scalars_beta<float>, dim3(s.B), dim3(64), 0, st, s, npart);
 }
 
-// For every entry of the slot's update list: y += c_i alpha^i p_i (old p_i), then
-// p_i = zeta^i r + beta^i p_i; x0 += alpha p_base where an x0 target is given (FP32 path).
-// The sums go either straight into the FP64 vectors (Y64 / X64) or into running sums in the
-// storage precision of p, which k_fold adds to FP64 every few iterations.  The FP64 path
-// always accumulates into y directly.  D: storage of the shifted directions (kDirF32: all NS
-// directions in p; 16-bit: the base in p, slot stride one vector, the others scaled in ph).
-// XS: also x_i += alpha^i p_i in FP64 for every listed shift (xs [slot][NS][12][vs]).
-template <class T, bool Y64, bool X64, int D, bool XS>
-__global__ __launch_bounds__(kBlock) void k_shift_update(Geom g, MSState S, const typename Store<T>::vec *r,
-                                                         typename Store<T>::vec *p, void *yt, void *xt, void *ph,
-                                                         double2 *xs) {
-    using vec = typename Store<T>::vec;
+// ------------------------------------------------------------------ base direction
+// z r + b p, rounded as b p + (z r) with one fused step: the same in every kernel that advances a
+// direction.
+template <class T>
+__device__ __forceinline__ cpx<T> next_direction(T z, cpx<T> r, T b, cpx<T> p) {
+    return {fmadd(b, p.re, z * r.re), fmadd(b, p.im, z * r.im)};
+}
+
+// p_out = r + beta p_in: three streamed vectors, bound by HBM.
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_base_direction(Geom g, MSState S, const typename Store<T>::vec *r,
+                                                           size_t rst, const typename Store<T>::vec *p_in,
+                                                           typename Store<T>::vec *p_out, size_t pst) {
     constexpr int C = Unit<T>::C;
     if ((int)blockIdx.y >= *S.count) return;
     const int slot = S.list[blockIdx.y];
+    if (S.done[slot]) return;
     const int nsb = site_blocks(g);
     const int u = blockIdx.x / nsb;
     const int s = (blockIdx.x % nsb) * kBlock + threadIdx.x;
     if (s >= g.V) return;
-    const int n = S.upd_n[slot];
-    if (n == 0) return;
-    const size_t rs = Store<T>::units * g.vs, r64 = 12 * g.vs;
-    cpx<T> rv[C];
-    Unit<T>::load_stream(r + slot * rs, g.vs, u, s, rv);
-    cpx<double> y64[C], x64[C];
-    cpx<T> yl[C], xl[C];
-    if constexpr (Y64) {
+    const T b = (T)S.beta[slot];
+    cpx<T> rv[C], pv[C];
+    Unit<T>::load_stream(r + slot * rst, g.vs, u, s, rv);
+    Unit<T>::load_stream(p_in + slot * pst, g.vs, u, s, pv);
 #pragma unroll
-        for (int j = 0; j < C; ++j) y64[j] = ld64_stream((double2 *)yt + slot * r64, g.vs, u * C + j, s);
-    } else {
-        Unit<T>::load_stream((vec *)yt + slot * rs, g.vs, u, s, yl);
+    for (int j = 0; j < C; ++j) pv[j] = next_direction(T(1), rv[j], b, pv[j]);
+    Unit<T>::store_stream(p_out + slot * pst, g.vs, u, s, pv);
+}
+
+void launch_base_direction(int prec, const Geom &g, const MSState &s, const void *r, size_t rst, const void *p_in,
+                           void *p_out, size_t pst, hipStream_t st) {
+    dim3 grid(unit_parts(prec, g), s.B);
+    if (prec == 0)
+        hipLaunchKernelGGL(k_base_direction<double>, grid, dim3(kBlock), 0, st, g, s, (const double2 *)r, rst,
+                           (const double2 *)p_in, (double2 *)p_out, pst);
+    else
+        hipLaunchKernelGGL(k_base_direction<float>, grid, dim3(kBlock), 0, st, g, s, (const float4 *)r, rst,
+                           (const float4 *)p_in, (float4 *)p_out, pst);
+}
+
+// ------------------------------------------------------------------ block update of the shifts
+// One wave per slot, lane i = shift i.
+__global__ void k_block_end(MSState S, int base_inline, int dir) {
+    const int slot = blockIdx.x, i = threadIdx.x;
+    const int m = S.blk_n[slot];
+    const bool on = i < S.NS;
+    const int k = slot * S.NS + (on ? i : 0);
+    const bool active = on && S.sh_active[k];
+    const bool was = on && (S.fl_act[slot] >> i & 1);
+    const bool write = on && !S.done[slot] && (i == S.i0 ? base_inline != 0 : active);
+    const unsigned rd = (unsigned)__ballot(was || write), wr = (unsigned)__ballot(write),
+                   now = (unsigned)__ballot(active);
+    if (i == 0) S.fl_m[slot] = m;
+    if (m == 0) return;
+    if (on && dir != kDirF32) {
+        // 16-bit directions: the stored p_i is decoded with its current scale and the new one is
+        // stored divided by zeta^i |r| dir_norm, which keeps its entries near 1
+        S.s_sold[k] = S.sh_scale[k];
+        double sc = S.zeta[k] * sqrt(S.rr[slot]) * S.dir_norm;
+        if (!(sc > 0.0) || !isfinite(sc)) sc = S.sh_scale[k];
+        if (write) S.sh_scale[k] = sc;
+        S.s_snew[k] = 1.0 / sc;
     }
-    bool x_touched = false;
-#pragma unroll 1
-    for (int e = 0; e < n; ++e) {
-        const int k = slot * S.NS + e;
-        const int i = S.upd_idx[k];
-        const double cy = S.upd_cy[k];
-        const bool full = D == kDirF32 || i == S.i0;   // this direction is stored in T
-        vec *pp = D == kDirF32 ? p + ((size_t)slot * S.NS + i) * rs : p + slot * rs;
-        cpx<T> pv[C];
-        if constexpr (D == kDirF32) {
-            Unit<T>::load_stream(pp, g.vs, u, s, pv);
-        } else {
-            if (full) Unit<T>::load_stream(pp, g.vs, u, s, pv);
-            else load_dir16<D>(static_cast<typename Dir16<D>::v *>(ph) + ((size_t)slot * S.NS + i) * rs, g.vs, u, s,
-                               (float)S.upd_sold[k], pv);
-        }
-        if constexpr (XS) {
-            const double ax = S.upd_ax[k];
-            if (ax != 0.0) {
-                double2 *xp = xs + ((size_t)slot * S.NS + i) * r64;
+    if (i != 0) return;
+    S.blk_n[slot] = 0;
+    S.fl_rd[slot] = rd;
+    S.fl_wr[slot] = wr;
+    S.fl_act[slot] = now;
+    S.cnt_fl[slot] += 1;
+    S.cnt_fl_r[slot] += m;
+    S.cnt_fl_p[slot] += __popc(rd) + __popc(wr);
+}
+
+void launch_block_end(const MSState &s, bool base_inline, int dir, hipStream_t st) {
+    hipLaunchKernelGGL(k_block_end, dim3(s.B), dim3(64), 0, st, s, base_inline ? 1 : 0, dir);
+}
+
+// acc += w v in FP64
+template <class T>
+__device__ __forceinline__ void add_scaled(double w, cpx<T> v, cpx<double> &acc) {
+    acc.re = fmadd(w, (double)v.re, acc.re);
+    acc.im = fmadd(w, (double)v.im, acc.im);
+}
+
+// The iterations l = 0 .. m-1 of a block for every listed shift: y += c_i a p_i and, for the base
+// shift, x0 += a p_i (FP64 sums of products that are exact in FP64 for FP32 vectors), then
+// p_i = z r_l + b p_i.  CH directions are held in registers while the block's residuals stream
+// by, so that a direction is read and written once per block instead of once per iteration and
+// y and x0 are read and written once: per site and iteration, in FP32 with n listed shifts,
+// 96 (1 + 2 n / K) + 768 / K bytes against 96 (1 + 2 n) + 192 .. 768.  Bound by HBM (the FP64
+// sums, four instructions a direction and real, take half of that time).  Against an update in
+// every iteration: four 16^4 classes (r = 4) in FP64 559 -> 366 ms, a whole 8^4 map (r = 2) in mixed
+// precision 99.5 -> 61.0 ms, eight unshifted 16^4 classes 376 -> 291 ms.  More than CH shifts take
+// further passes over the residuals.
+template <class T, int CH, int D, bool XS>
+__global__ __launch_bounds__(kBlock) void k_block_update(
+    Geom g, int NS, int K, int i0, const int *__restrict__ fl_m, const unsigned *__restrict__ fl_rd,
+    const unsigned *__restrict__ fl_wr, const double *__restrict__ h_cy, const double *__restrict__ h_a,
+    const T *__restrict__ h_z, const T *__restrict__ h_b, const double *__restrict__ s_sold,
+    const double *__restrict__ s_snew, const typename Store<T>::vec *__restrict__ ring, typename Store<T>::vec *p,
+    size_t pst, int base_sel, double2 *y, double2 *x0, void *ph, double2 *xs) {
+    using vec = typename Store<T>::vec;
+    constexpr int C = Unit<T>::C;
+    const int slot = blockIdx.y;
+    const int m = fl_m[slot];
+    if (m == 0) return;
+    const int nsb = site_blocks(g);
+    const int u = blockIdx.x / nsb;
+    const int s = (blockIdx.x % nsb) * kBlock + threadIdx.x;
+    if (s >= g.V) return;
+    const unsigned rd = fl_rd[slot], wr = fl_wr[slot];
+    const size_t rs = Store<T>::units * g.vs, r64 = 12 * g.vs;
+    const vec *rp = ring + (size_t)slot * K * rs;
+    vec *pp = p + slot * pst;
+    const bool with_x = x0 && (rd >> i0 & 1);
+    cpx<double> ya[C], xa[C];
 #pragma unroll
-                for (int j = 0; j < C; ++j)
-                    st64_stream(xp, g.vs, u * C + j, s,
-                                ld64_stream(xp, g.vs, u * C + j, s) + ax * cpx<double>{(double)pv[j].re, (double)pv[j].im});
-            }
-        }
-        if (cy != 0.0) {
+    for (int c = 0; c < C; ++c) {
+        ya[c] = ld64_stream(y + slot * r64, g.vs, u * C + c, s);
+        xa[c] = {0.0, 0.0};
+        if (with_x) xa[c] = ld64_stream(x0 + slot * r64, g.vs, u * C + c, s);
+    }
+    for (int c0 = 0; c0 < NS; c0 += CH) {
+        constexpr unsigned kMask = CH >= 32 ? ~0u : (1u << CH) - 1;
+        const unsigned on = rd >> c0 & kMask;   // never a bit of a shift >= NS
+        if (on == 0) continue;
+        cpx<T> pv[CH][C];
+        cpx<double> xv[XS ? CH : 1][C];
 #pragma unroll
-            for (int j = 0; j < C; ++j) {
-                if constexpr (Y64) y64[j] = y64[j] + cy * cpx<double>{(double)pv[j].re, (double)pv[j].im};
-                else yl[j] = yl[j] + (T)cy * pv[j];
-            }
-            if (xt && i == S.i0) {
-                const double a = S.alpha[slot];
-                x_touched = true;
-                if constexpr (X64) {
+        for (int e = 0; e < CH; ++e) {
+            const int i = c0 + e;
 #pragma unroll
-                    for (int j = 0; j < C; ++j)
-                        x64[j] = ld64_stream((double2 *)xt + slot * r64, g.vs, u * C + j, s) +
-                                 a * cpx<double>{(double)pv[j].re, (double)pv[j].im};
-                } else {
-                    Unit<T>::load_stream((vec *)xt + slot * rs, g.vs, u, s, xl);
+            for (int c = 0; c < C; ++c) pv[e][c] = {T(0), T(0)};
+            if (on >> e & 1) {
+                if (D == kDirF32 || i == i0)
+                    Unit<T>::load_stream(pp + (i == i0 ? base_sel : i) * rs, g.vs, u, s, pv[e]);
+                else if constexpr (D != kDirF32)
+                    load_dir16<D>(static_cast<typename Dir16<D>::v *>(ph) + ((size_t)slot * NS + i) * rs, g.vs, u, s,
+                                  (float)s_sold[slot * NS + i], pv[e]);
+                if constexpr (XS) {
 #pragma unroll
-                    for (int j = 0; j < C; ++j) xl[j] = xl[j] + (T)a * pv[j];
+                    for (int c = 0; c < C; ++c)
+                        xv[e][c] = ld64_stream(xs + ((size_t)slot * NS + i) * r64, g.vs, u * C + c, s);
                 }
             }
         }
-        if (S.upd_pupd[k]) {
-            const T zn = (T)S.upd_zeta[k], bi = (T)S.upd_beta[k];
+        cpx<T> next[C];
+        Unit<T>::load_stream(rp, g.vs, u, s, next);
+#pragma unroll 1
+        for (int l = 0; l < m; ++l) {
+            cpx<T> rv[C];
 #pragma unroll
-            for (int j = 0; j < C; ++j) pv[j] = zn * rv[j] + bi * pv[j];
-            if constexpr (D == kDirF32) {
-                Unit<T>::store_stream(pp, g.vs, u, s, pv);
-            } else {
-                if (full) Unit<T>::store_stream(pp, g.vs, u, s, pv);
-                else store_dir16<D>(static_cast<typename Dir16<D>::v *>(ph) + ((size_t)slot * S.NS + i) * rs, g.vs,
-                                    u, s, (float)S.upd_snew[k], pv);
+            for (int c = 0; c < C; ++c) rv[c] = next[c];
+            if (l + 1 < m) Unit<T>::load_stream(rp + (l + 1) * rs, g.vs, u, s, next);
+            const size_t h = ((size_t)slot * K + l) * NS + c0;
+#pragma unroll
+            for (int e = 0; e < CH; ++e) {
+                if (on >> e & 1) {
+                    const double cy = h_cy[h + e];
+                    const T z = h_z[h + e], b = h_b[h + e];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        add_scaled(cy, pv[e][c], ya[c]);
+                        if constexpr (XS) add_scaled(h_a[h + e], pv[e][c], xv[e][c]);
+                    }
+                    if (with_x && c0 + e == i0) {
+                        const double a = h_a[h + e];
+#pragma unroll
+                        for (int c = 0; c < C; ++c) add_scaled(a, pv[e][c], xa[c]);
+                    }
+#pragma unroll
+                    for (int c = 0; c < C; ++c) pv[e][c] = next_direction(z, rv[c], b, pv[e][c]);
+                }
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < CH; ++e) {
+            const int i = c0 + e;
+            if (on >> e & 1) {
+                if (wr >> i & 1) {
+                    if (D == kDirF32 || i == i0)
+                        Unit<T>::store_stream(pp + (i == i0 ? base_sel : i) * rs, g.vs, u, s, pv[e]);
+                    else if constexpr (D != kDirF32)
+                        store_dir16<D>(static_cast<typename Dir16<D>::v *>(ph) + ((size_t)slot * NS + i) * rs, g.vs, u,
+                                       s, (float)s_snew[slot * NS + i], pv[e]);
+                }
+                if constexpr (XS) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c)
+                        st64_stream(xs + ((size_t)slot * NS + i) * r64, g.vs, u * C + c, s, xv[e][c]);
+                }
             }
         }
     }
-    if constexpr (Y64) {
 #pragma unroll
-        for (int j = 0; j < C; ++j) st64_stream((double2 *)yt + slot * r64, g.vs, u * C + j, s, y64[j]);
-    } else {
-        Unit<T>::store_stream((vec *)yt + slot * rs, g.vs, u, s, yl);
-    }
-    if (x_touched) {
-        if constexpr (X64) {
-#pragma unroll
-            for (int j = 0; j < C; ++j) st64_stream((double2 *)xt + slot * r64, g.vs, u * C + j, s, x64[j]);
-        } else {
-            Unit<T>::store_stream((vec *)xt + slot * rs, g.vs, u, s, xl);
-        }
+    for (int c = 0; c < C; ++c) {
+        st64_stream(y + slot * r64, g.vs, u * C + c, s, ya[c]);
+        if (with_x) st64_stream(x0 + slot * r64, g.vs, u * C + c, s, xa[c]);
     }
 }
 
-void launch_shift_update(int prec, const Geom &g, const MSState &s, const void *r, void *p, void *yt, bool y64,
-                         void *xt, bool x64, int dir, void *ph, double2 *xs, hipStream_t st) {
-    dim3 grid(unit_parts(prec, g), s.B);
+template <class T, int CH, int D, bool XS>
+static void launch_block_update_t(const Geom &g, const MSState &s, const void *ring, void *p, size_t pst, int base_sel,
+                                  double2 *y, double2 *x0, void *ph, double2 *xs, hipStream_t st) {
+    using vec = typename Store<T>::vec;
+    dim3 grid(unit_parts(std::is_same<T, double>::value ? 0 : 1, g), s.B);
+    hipLaunchKernelGGL((k_block_update<T, CH, D, XS>), grid, dim3(kBlock), 0, st, g, s.NS, s.K, s.i0, s.fl_m, s.fl_rd,
+                       s.fl_wr, s.h_cy, s.h_a, (const T *)s.h_z, (const T *)s.h_b, s.s_sold, s.s_snew, (const vec *)ring, (vec *)p, pst, base_sel, y, x0, ph, xs);
+}
+
+// Directions per pass: all of them where they are one (the trace of D_W^-1, refinement and inner
+// solves) or up to 14 (the usual order of the sign function), else 8; the same with the per-shift
+// check, so that it does not change the order of the sums.
+template <class T, int D, bool XS>
+static void launch_block_update_d(const Geom &g, const MSState &s, const void *ring, void *p, size_t pst, int base_sel,
+                                  double2 *y, double2 *x0, void *ph, double2 *xs, hipStream_t st) {
+    if (s.NS == 1)
+        launch_block_update_t<T, 1, D, XS>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else if (s.NS > 8 && s.NS <= 14)
+        launch_block_update_t<T, 14, D, XS>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else
+        launch_block_update_t<T, 8, D, XS>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+}
+
+void launch_block_update(int prec, const Geom &g, const MSState &s, const void *ring, void *p, size_t pst,
+                         int base_sel, double2 *y, double2 *x0, int dir, void *ph, double2 *xs, hipStream_t st) {
     if (xs && dir != kDirF32) throw std::invalid_argument("the per-shift check needs FP32 or FP64 directions");
-    if (prec == 0) {
-        if (dir != kDirF32) throw std::invalid_argument("16-bit directions need the FP32 path");
-        if (xs)
-            hipLaunchKernelGGL((k_shift_update<double, true, true, kDirF32, true>), grid, dim3(kBlock), 0, st, g, s,
-                               (const double2 *)r, (double2 *)p, yt, xt, ph, xs);
-        else
-            hipLaunchKernelGGL((k_shift_update<double, true, true, kDirF32, false>), grid, dim3(kBlock), 0, st, g, s,
-                               (const double2 *)r, (double2 *)p, yt, xt, ph, xs);
-        return;
-    }
-#define SMPQ_SU(Y, X, D, XS)                                                                                      \
-    hipLaunchKernelGGL((k_shift_update<float, Y, X, D, XS>), grid, dim3(kBlock), 0, st, g, s, (const float4 *)r,   \
-                       (float4 *)p, yt, xt, ph, xs)
-#define SMPQ_SU_D(D, XS)                         \
-    if (y64 && x64) SMPQ_SU(true, true, D, XS);  \
-    else if (y64) SMPQ_SU(true, false, D, XS);   \
-    else if (x64) SMPQ_SU(false, true, D, XS);   \
-    else SMPQ_SU(false, false, D, XS)
-    if (dir == kDirF16) {
-        SMPQ_SU_D(kDirF16, false);
-    } else if (dir == kDirBF16) {
-        SMPQ_SU_D(kDirBF16, false);
-    } else if (xs) {
-        SMPQ_SU_D(kDirF32, true);
-    } else {
-        SMPQ_SU_D(kDirF32, false);
-    }
-#undef SMPQ_SU_D
-#undef SMPQ_SU
-}
-
-// FP32 path: y += yacc, yacc = 0 when y is given, and x0 += x0acc, x0acc = 0 when x0acc is
-// given, for the listed slots, in FP64.
-__global__ __launch_bounds__(kBlock) void k_fold(Geom g, Slots sl, double2 *y, float4 *yacc, double2 *x0,
-                                                 float4 *x0acc) {
-    if ((int)blockIdx.y >= slot_count(sl)) return;
-    const int slot = slot_of(sl, blockIdx.y);
-    const int nsb = site_blocks(g);
-    const int u = blockIdx.x / nsb;
-    const int s = (blockIdx.x % nsb) * kBlock + threadIdx.x;
-    if (s >= g.V) return;
-    const size_t rs = 6 * g.vs, ys = 12 * g.vs;
-    const cpx<float> z[2] = {{0.f, 0.f}, {0.f, 0.f}};
-    cpx<float> a[2];
-    if (y) {
-        Unit<float>::load_stream(yacc + slot * rs, g.vs, u, s, a);
-        double2 *yp = y + slot * ys;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            st64_stream(yp, g.vs, 2 * u + j, s,
-                        ld64_stream(yp, g.vs, 2 * u + j, s) + cpx<double>{(double)a[j].re, (double)a[j].im});
-        Unit<float>::store_stream(yacc + slot * rs, g.vs, u, s, z);
-    }
-    if (x0acc) {
-        Unit<float>::load_stream(x0acc + slot * rs, g.vs, u, s, a);
-        double2 *xp = x0 + slot * ys;
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            st64_stream(xp, g.vs, 2 * u + j, s, ld64_stream(xp, g.vs, 2 * u + j, s) + cpx<double>{(double)a[j].re, (double)a[j].im});
-        Unit<float>::store_stream(x0acc + slot * rs, g.vs, u, s, z);
-    }
-}
-
-void launch_fold(const Geom &g, Slots sl, int max_slots, double2 *y, void *yacc, double2 *x0, void *x0acc,
-                 hipStream_t st) {
-    dim3 grid(unit_parts(1, g), max_slots);
-    hipLaunchKernelGGL(k_fold, grid, dim3(kBlock), 0, st, g, sl, y, (float4 *)yacc, x0, (float4 *)x0acc);
+    if (prec == 0 && dir != kDirF32) throw std::invalid_argument("16-bit directions need the FP32 path");
+    if (prec == 0 && xs)
+        launch_block_update_d<double, kDirF32, true>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else if (prec == 0)
+        launch_block_update_d<double, kDirF32, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else if (dir == kDirF16)
+        launch_block_update_d<float, kDirF16, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else if (dir == kDirBF16)
+        launch_block_update_d<float, kDirBF16, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else if (xs)
+        launch_block_update_d<float, kDirF32, true>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else
+        launch_block_update_d<float, kDirF32, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
 }
 
 // Evaluated precision: an FP32 vector of every listed slot rounded in place to what 16-bit
@@ -1670,29 +1724,49 @@ void launch_round16(const Geom &g, const MSState &s, void *v, size_t slot_stride
     hipLaunchKernelGGL(k_round16, grid, dim3(kBlock), 0, st, g, s, (float4 *)v, slot_stride, extra, mode);
 }
 
-// Ordered list of the slots still iterating.
-__global__ void k_compact(MSState S) {
-    if (threadIdx.x != 0) return;
+// Ordered list of the slots still iterating: one block, each thread counting a contiguous range
+// of slots (one thread walking all of them waits for a load per slot: 24 us for 192 slots).
+__global__ __launch_bounds__(kBlock) void k_compact(MSState S) {
+    __shared__ int wave_n[kBlock / 64];
+    const int per = (S.B + kBlock - 1) / kBlock;
+    const int beg = min(S.B, (int)threadIdx.x * per), end = min(S.B, beg + per);
     int n = 0;
-    for (int slot = 0; slot < S.B; ++slot)
-        if (!S.done[slot]) S.list[n++] = slot;
-    *S.count = n;
+    for (int slot = beg; slot < end; ++slot) n += !S.done[slot];
+    int before = n;   // inclusive prefix sum over the wave
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(before, off);
+        if (lane >= off) before += t;
+    }
+    if (lane == 63) wave_n[wv] = before;
+    __syncthreads();
+    int at = before - n, total = 0;
+#pragma unroll
+    for (int i = 0; i < kBlock / 64; ++i) {
+        if (i < wv) at += wave_n[i];
+        total += wave_n[i];
+    }
+    for (int slot = beg; slot < end; ++slot)
+        if (!S.done[slot]) S.list[at++] = slot;
+    if (threadIdx.x == 0) *S.count = total;
 }
 
-void launch_compact(const MSState &s, hipStream_t st) { hipLaunchKernelGGL(k_compact, dim3(1), dim3(64), 0, st, s); }
+void launch_compact(const MSState &s, hipStream_t st) {
+    hipLaunchKernelGGL(k_compact, dim3(1), dim3(kBlock), 0, st, s);
+}
 
 // Residual replacement: r = b - (H^2 + s) x0 evaluated in FP64 (ap64 holds (H^2 + s) x0),
 // stored in the iteration precision; partial |r|^2 of the stored values.
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_reliable(Geom g, MSState S, Source src, const double2 *ap64,
-                                                     typename Store<T>::vec *r) {
+                                                     typename Store<T>::vec *r, size_t rst) {
     constexpr int C = Unit<T>::C;
     if ((int)blockIdx.y >= *S.count) return;
     const int slot = S.list[blockIdx.y];
     const int nsb = site_blocks(g);
     const int u = blockIdx.x / nsb;
     const int s = (blockIdx.x % nsb) * kBlock + threadIdx.x;
-    const size_t rs = Store<T>::units * g.vs;
     double nrm = 0.0;
     if (s < g.V) {
         cpx<T> rv[C];
@@ -1703,18 +1777,18 @@ __global__ __launch_bounds__(kBlock) void k_reliable(Geom g, MSState S, Source s
             rv[i] = {(T)d.re, (T)d.im};
             nrm += (double)rv[i].re * rv[i].re + (double)rv[i].im * rv[i].im;
         }
-        Unit<T>::store(r + slot * rs, g.vs, u, s, rv);
+        Unit<T>::store(r + slot * rst, g.vs, u, s, rv);
     }
     block_partial(nrm, S.partial, (size_t)slot * S.pstride + blockIdx.x);
 }
 
 void launch_reliable(int prec, const Geom &g, const MSState &s, const Source &src, const double2 *ap64, void *r,
-                     hipStream_t st) {
+                     size_t rst, hipStream_t st) {
     dim3 grid(unit_parts(prec, g), s.B);
     if (prec == 0)
-        hipLaunchKernelGGL(k_reliable<double>, grid, dim3(kBlock), 0, st, g, s, src, ap64, (double2 *)r);
+        hipLaunchKernelGGL(k_reliable<double>, grid, dim3(kBlock), 0, st, g, s, src, ap64, (double2 *)r, rst);
     else
-        hipLaunchKernelGGL(k_reliable<float>, grid, dim3(kBlock), 0, st, g, s, src, ap64, (float4 *)r);
+        hipLaunchKernelGGL(k_reliable<float>, grid, dim3(kBlock), 0, st, g, s, src, ap64, (float4 *)r, rst);
 }
 
 __global__ void k_scalars_rr(MSState S, int npart) {
