@@ -401,20 +401,22 @@ smpq_status smpq_bench_copy(smpq_ctx *ctx, size_t bytes, int launches, double *m
  * smpq_bench_copy's library copy. */
 smpq_status smpq_bench_stream(smpq_ctx *ctx, size_t bytes, int launches, int nontemporal, double *ms_per_copy);
 
-/* Stencil variants.  f32_kind: 0 = one site per thread (f32_nr = 2, 4 or 8 right-hand sides
- * per thread, links held in registers across them); 1 = one 16x16 xy-plane per block staged
+/* Stencil variants.  f32_kind: 0 = any lattice (f32_nr = 2, 4 or 8 right-hand sides per block, two
+ * at a time, the links read for each two; several whole xy-planes or rows of one staged in LDS,
+ * one site per thread, no LDS where nx > 128); 1 = one 16x16 xy-plane per block staged
  * in LDS (nx*ny = 256; f32_nr = 4, 8 or 16); 2 = xy-tiles of ty rows plus one halo row on
  * each side staged in LDS, ty the largest divisor of ny with nx*ty <= 256 and a multiple of 64
  * (nx <= 64; f32_nr = 4, 8 or 16); 3 = kind 1 with the plane's x and y links in LDS instead
  * of registers, at 3 waves per SIMD; 4 = kind 2's tiles with the links read for every
- * right-hand side instead of held in registers (f32_nr = 1, 2, 4 or 8; 3-4 waves per SIMD), the
- * tile without halo rows when it is the whole plane.  plane_band (kinds 1-4; 1, 2 or 4, dividing nz): the
+ * right-hand side, or every two where there are more than one, instead of held in registers
+ * (f32_nr = 1, 2, 4 or 8; 3-4 waves per SIMD), the tile without halo rows when it is the whole plane.  plane_band (kinds 1-4; 1, 2 or 4, dividing nz): the
  * blocks take the (z, t) planes in bands of that many z with t running inside a band, so the
  * +-t neighbours of a plane were read shortly before (1 = z fastest).  FP64 stencil:
- * f64_kind 0 interleaves 2^f64_lgr = 1, 2 or 4 right-hand sides over the lanes of a block;
+ * f64_kind 0 is the FP32 kind 0 with 2^f64_lgr = 1, 2 or 4 right-hand sides per block in turn;
  * f64_kind 1 stages xy-tiles in LDS as FP32 kind 2 does (one halo row on each side unless the
  * tile is the whole plane), f64_nr = 1, 2, 4 or 8 right-hand sides per block, the links read as
- * their first two rows with the third rebuilt (where a tile fits; plane_band applies too).
+ * their first two rows with the third rebuilt (in full where a loaded link's third row differs from
+ * that by more than 1e-14; where a tile fits; plane_band applies too).
  * f32_interleave (FP32 kind 4) and f64_interleave (FP64 kind 1): 1, 2, 4, 8 or 16 blocks in a
  * row take successive groups of right-hand sides of the same tile before the blocks move on
  * to the next tile, so that the links a tile reads for each right-hand side come from L2;
@@ -438,10 +440,11 @@ typedef struct {
  * right-hand sides where they would take more than half of the free device memory).  n_rhs = 0 times the batch size that a whole q(x)
  * map of the current scheme, coefficients and precision would use (ESTATE without them):
  * the variants' order can change with the number of right-hand sides through L2 reuse.  The choice is kept by the context and written to
- * *chosen (may be NULL); on an error the previous choice is kept.  Without this call a
- * context uses kind 1 / 8 where the plane fits, else kind 2 / 8 where a tile fits, else kind
- * 0 / 4 (the same for D_W and D_W^dag), with plane_band 1, f64_kind 0, f64_lgr 1 and the
- * interleaves 1. */
+ * *chosen (may be NULL); on an error the previous choice is kept.  Without this call or
+ * smpq_set_tuning every launch takes a variant by the lattice and its number of right-hand sides
+ * (on 16 x 16 planes kind 1 / 8 for D_W and kind 4 / 2, interleave 2, for D_W^dag; kind 4 / 1 on
+ * other tiles and with few right-hand sides; else kind 0; FP64 kind 1 / 1, interleave 2, where a
+ * tile fits), and smpq_get_tuning reports those of a large batch. */
 smpq_status smpq_autotune(smpq_ctx *ctx, int n_rhs, smpq_tuning *chosen);
 
 /* Select the variants explicitly.  SMPQ_EINVAL (previous choice kept) if a variant is not

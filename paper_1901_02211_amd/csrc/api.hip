@@ -215,13 +215,15 @@ struct smpq_ctx {
     bool graph_timing_ok = true;
     long long gen = 0;
     int *h_count = nullptr;     // pinned
-    // stencil variant (see Geom); defaults: plane tile where the xy-plane has 256 sites
-    int f32_kind = 0, f32_nr = 4, f64_lgr = 1, band = 1, f64_kind = 0, f64_nr = 4, f32_il = 1, f64_il = 1;
-    int f32_dag_kind = 0, f32_dag_nr = 4, f32_dag_il = 1;   // the D_W^dag launches
+    // stencil variant (see Geom)
+    int f32_kind = 0, f32_nr = 2, f64_lgr = 0, band = 1, f64_kind = 0, f64_nr = 1, f32_il = 1, f64_il = 1;
+    int f32_dag_kind = 0, f32_dag_nr = 2, f32_dag_il = 1;   // the D_W^dag launches
+    bool adapt = true;       // no stencil variant chosen by smpq_autotune or smpq_set_tuning
+    bool f64_full = false;   // a loaded link's third row is further than rounding from the other two's product
     Geom geom() const {
         return Geom{dims[0], dims[1], dims[2], dims[3], V, vs, f32_kind, f32_nr, f64_lgr, band,
-                    tile_rows(dims[0], dims[1]), f64_kind, f64_nr, f32_il, f64_il, f32_dag_kind, f32_dag_nr,
-                    f32_dag_il};
+                    tile_rows(dims[0], dims[1]), f64_kind, f64_nr, f32_il, f64_il, adapt ? 1 : 0, f64_full ? 1 : 0, f32_dag_kind,
+                    f32_dag_nr, f32_dag_il};
     }
     smpq_tuning tuning() const {
         return smpq_tuning{f32_kind, f32_nr, f64_lgr, band, f64_kind, f64_nr, f32_il, f64_il,
@@ -264,6 +266,11 @@ smpq_status guarded(smpq_ctx *c, F &&f) {
         return SMPQ_EINVAL;
     }
 }
+
+// Links of a field computed in FP64 have a third row within a few 1e-15 of the conjugate cross
+// product of the first two, and the FP64 stencils rebuild it from them (384 instead of 576 bytes a
+// site); a field accepted with more than this (up to 1e-10) keeps its own third rows.
+constexpr double kRow3Tol = 1e-14;
 
 double now_s() {
     using namespace std::chrono;
@@ -1441,12 +1448,17 @@ smpq_status smpq_create(const int dims[4], int device, smpq_ctx **out) {
     c->V = (int)V;
     c->vs = (size_t)((V + 255) / 256) * 256;
     c->device = device;
-    if (dims[0] * dims[1] == 256) {
-        c->f32_kind = c->f32_dag_kind = 1;
-        c->f32_nr = c->f32_dag_nr = 8;
-    } else if (tile_rows(dims[0], dims[1]) > 0) {
-        c->f32_kind = c->f32_dag_kind = 2;
-        c->f32_nr = c->f32_dag_nr = 8;
+    // the variants of a large batch, which smpq_get_tuning reports until one is chosen
+    if (tile_rows(dims[0], dims[1]) > 0) {
+        const bool plane = dims[0] * dims[1] == 256;
+        c->f64_kind = 1;
+        c->f64_il = 2;
+        c->f32_kind = plane ? 1 : 4;
+        c->f32_nr = plane ? 8 : 1;
+        c->f32_il = plane ? 1 : 2;
+        c->f32_dag_kind = 4;
+        c->f32_dag_nr = plane ? 2 : 1;
+        c->f32_dag_il = 2;
     }
     if (device >= 0) {
         int n = 0;
@@ -1492,9 +1504,10 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
         if (n != (size_t)72 * c->V) throw Fail{SMPQ_EDIM, "gauge field must hold 72*V doubles"};
         for (size_t i = 0; i < n; ++i)
             if (!std::isfinite(U[i])) throw Fail{SMPQ_ENUMERIC, "non-finite gauge link entry"};
+        double row3 = 0.0;   // largest deviation of a third row from the one rebuilt from the first two
         for (size_t l = 0; l < (size_t)4 * c->V; ++l) {
             const double *u = U + 18 * l;
-            double err = 0.0;
+            double err2 = 0.0;   // largest |(U^dag U - 1)_ab|^2
             for (int a = 0; a < 3; ++a)
                 for (int b = 0; b < 3; ++b) {
                     double re = 0.0, im = 0.0;   // (U^dag U)_ab = sum_k conj(U_ka) U_kb
@@ -1504,7 +1517,8 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
                         re += ar * br + ai * bi;
                         im += ar * bi - ai * br;
                     }
-                    err = std::max(err, std::hypot(re - (a == b), im));
+                    re -= a == b;
+                    err2 = std::max(err2, re * re + im * im);
                 }
             // det by cofactor expansion along the first row
             auto C = [&](int r, int k) { return std::pair<double, double>(u[2 * (3 * r + k)], u[2 * (3 * r + k) + 1]); };
@@ -1522,7 +1536,12 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
             auto t1 = mul(C(0, 1), m1), t2 = mul(C(0, 2), m2);
             det.first += -t1.first + t2.first;
             det.second += -t1.second + t2.second;
-            if (err > 1e-10 || std::hypot(det.first - 1.0, det.second) > 1e-10)
+            // the third row against the conjugate cross product of the first two
+            for (int b = 0; b < 3; ++b) {
+                const auto x = sub(mul(C(0, (b + 1) % 3), C(1, (b + 2) % 3)), mul(C(0, (b + 2) % 3), C(1, (b + 1) % 3)));
+                row3 = std::max(row3, std::max(std::fabs(C(2, b).first - x.first), std::fabs(C(2, b).second + x.second)));
+            }
+            if (err2 > 1e-20 || std::hypot(det.first - 1.0, det.second) > 1e-10)
                 throw Fail{SMPQ_ENUMERIC, "gauge link is not in SU(3) (|U^dag U - 1| or |det U - 1| > 1e-10)"};
         }
         need_device(c);
@@ -1552,6 +1571,7 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
         for (size_t i = 0; i < n * sizeof(double); ++i) h = (h ^ bytes[i]) * 0x100000001b3ull;
         c->gauge_hash = h;
         c->have_gauge = true;
+        c->f64_full = row3 > kRow3Tol;
         drop_deflation(c);   // eigenvectors of the previous operator
         c->gen++;
     });
@@ -2289,10 +2309,13 @@ smpq_status smpq_set_tuning(smpq_ctx *c, const smpq_tuning *t) {
     return guarded(c, [&] {
         if (!t) throw Fail{SMPQ_EINVAL, "null tuning"};
         const smpq_tuning keep = c->tuning();
+        const bool keep_adapt = c->adapt;
         c->set_tuning(*t);
+        c->adapt = false;
         const Geom g = c->geom();
         if (!valid_tuning(0, g) || !valid_tuning(1, g)) {
             c->set_tuning(keep);
+            c->adapt = keep_adapt;
             throw Fail{SMPQ_EINVAL, "unsupported stencil variant for this lattice"};
         }
         c->gen++;
@@ -2331,6 +2354,8 @@ smpq_status smpq_autotune(smpq_ctx *c, int n_rhs, smpq_tuning *chosen) {
                         if (c->dims[2] % band == 0 && (il == 1 || nr * il <= 4)) cand.push_back({kind, nr, band, il});
         }
         const smpq_tuning keep = c->tuning();
+        const bool keep_adapt = c->adapt;
+        c->adapt = false;
         StencilBench tb;   // one set of timing buffers per precision for the whole sweep
         try {
             // FP32: the two stencils of an iteration (D_W p with its partials, D_W^dag with the
@@ -2412,6 +2437,7 @@ smpq_status smpq_autotune(smpq_ctx *c, int n_rhs, smpq_tuning *chosen) {
             c->f64_il = p64.il;
         } catch (...) {
             c->set_tuning(keep);
+            c->adapt = keep_adapt;
             throw;
         }
         c->gen++;   // captured graphs used the previous variants

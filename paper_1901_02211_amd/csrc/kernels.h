@@ -21,14 +21,16 @@ struct Geom {
     // thread, 1: 16x16 xy-plane per block in LDS, 2: xy-tile of tile_y rows with y-halos in
     // LDS), FP32 right-hand sides per thread, log2 of the right-hand sides interleaved over the
     // lanes of an FP64 block, and the z-band of the plane order of kinds 1 and 2;
-    // tile_y = tile_rows(nx, ny) (0 when no tile fits); FP64 kernel kind (0: right-hand sides
-    // interleaved over the lanes, 2^f64_lgr per block; 1: xy-tiles in LDS like the FP32 kind 2,
-    // f64_nr right-hand sides per block, links read per right-hand side); f32_il / f64_il: in
+    // tile_y = tile_rows(nx, ny) (0 when no tile fits); FP64 kernel kind (0: any lattice, 2^f64_lgr
+    // right-hand sides per block; 1: xy-tiles in LDS like the FP32 kind 2, f64_nr right-hand sides
+    // per block; the links are read per right-hand side); f32_il / f64_il: in
     // the tile kernels (FP32 kind 4, FP64 kind 1) consecutive blocks take that many groups of
     // right-hand sides of one tile before the next tile, so that the tile's links are still in L2
     int f32_kind, f32_nr, f64_lgr, band, tile_y;
     int f64_kind, f64_nr;
     int f32_il, f64_il;
+    int adapt;      // no variant chosen: each launch takes the one that suits its size
+    int f64_full;   // FP64 links: read all nine entries (else two rows, the third rebuilt)
     // the FP32 variant of the D_W^dag launches (f32_kind, f32_nr and f32_il above apply to D_W):
     // the two stencils of a CG iteration have different epilogues and favour different variants
     int f32_dag_kind, f32_dag_nr, f32_dag_il;

@@ -75,27 +75,38 @@ __host__ __device__ __forceinline__ void project(const cpx<T> p[12], cpx<T> h[6]
     }
 }
 
-// acc += (1 - S gamma_MU) spinor whose upper half is g (lower half = -S A^dag g).
-template <int MU, int S, class T>
+// acc += (1 - S gamma_MU) spinor whose upper half is g (lower half = -S A^dag g); FIRST: acc = it
+// (adding to zeros costs an instruction per real).
+template <int MU, int S, bool FIRST = false, class T>
 __host__ __device__ __forceinline__ void accumulate(cpx<T> acc[12], const cpx<T> g[6]) {
     constexpr T s = static_cast<T>(S);
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
         const cpx<T> g0 = g[a], g1 = g[3 + a];
-        acc[a] = acc[a] + g0;
-        acc[3 + a] = acc[3 + a] + g1;
+        cpx<T> l0, l1;                  // A^dag g
         if constexpr (MU == 0) {        // A^dag = i sigma_1: A^dag g = (i g1, i g0)
-            acc[6 + a] = acc[6 + a] - s * mul_i(g1);
-            acc[9 + a] = acc[9 + a] - s * mul_i(g0);
+            l0 = mul_i(g1);
+            l1 = mul_i(g0);
         } else if constexpr (MU == 1) { // A^dag = [[0,1],[-1,0]]: A^dag g = (g1, -g0)
-            acc[6 + a] = acc[6 + a] - s * g1;
-            acc[9 + a] = acc[9 + a] + s * g0;
+            l0 = g1;
+            l1 = T(-1) * g0;
         } else if constexpr (MU == 2) { // A^dag = diag(i, -i): A^dag g = (i g0, -i g1)
-            acc[6 + a] = acc[6 + a] - s * mul_i(g0);
-            acc[9 + a] = acc[9 + a] + s * mul_i(g1);
+            l0 = mul_i(g0);
+            l1 = T(-1) * mul_i(g1);
         } else {
-            acc[6 + a] = acc[6 + a] - s * g0;
-            acc[9 + a] = acc[9 + a] - s * g1;
+            l0 = g0;
+            l1 = g1;
+        }
+        if constexpr (FIRST) {
+            acc[a] = g0;
+            acc[3 + a] = g1;
+            acc[6 + a] = T(-1) * (s * l0);
+            acc[9 + a] = T(-1) * (s * l1);
+        } else {
+            acc[a] = acc[a] + g0;
+            acc[3 + a] = acc[3 + a] + g1;
+            acc[6 + a] = acc[6 + a] - s * l0;
+            acc[9 + a] = acc[9 + a] - s * l1;
         }
     }
 }
