@@ -106,7 +106,7 @@ struct Workspace {
     DevMem st_d;   // doubles of the MSState
     DevMem st_i;   // ints of the MSState
     DevMem st_l;   // long longs of the MSState
-    DevMem partial, list, count, slot_class, slot_comp, batch_classes, bexp;
+    DevMem partial, partial2, list, count, slot_class, slot_comp, batch_classes, bexp;
     MSState S{};
 };
 
@@ -306,7 +306,7 @@ void spinor_from_device(const smpq_ctx *c, const std::vector<double> &stage, int
 // right-hand sides after each group.  The shifted systems, y and x0 are updated once per block of K
 // iterations from the residuals kept since the last block, and always before a reliable update and
 // at the end, all sums into y and x0 in FP64.
-constexpr int kGroup = 10;
+constexpr int kGroup = 10;   // even: the buffers of |r|^2 alternate within a group
 constexpr size_t kUnit = 16;   // bytes of a storage unit (double2 or float4)
 
 // Iterations per block, longest first.  K > 1 needs a second buffer for the base direction.  With
@@ -387,10 +387,11 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     }
     const size_t pstride = partial_stride(g);
     const size_t BN = (size_t)B * NS, BKN = BN * K;
-    w.st_d.ensure(sizeof(double) * ((size_t)B * 6 + 6 * BN + 4 * BKN));
+    w.st_d.ensure(sizeof(double) * ((size_t)B * 7 + 5 * BN + 4 * BKN));
     w.st_i.ensure(sizeof(int) * ((size_t)B * 8 + 2 * BN + 16));
     w.st_l.ensure(sizeof(long long) * (size_t)B * 5);
     w.partial.ensure(sizeof(double) * (size_t)B * pstride);
+    w.partial2.ensure(sizeof(double) * (size_t)B * pstride);
     w.list.ensure(sizeof(int) * B);
     w.count.ensure(sizeof(int) * 4);
     w.slot_class.ensure(sizeof(int) * B);
@@ -400,6 +401,7 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     double *d = w.st_d.as<double>();
     auto dbl = [&d](size_t n) { double *q = d; d += n; return q; };
     S.rr = dbl(B);
+    S.rr1 = dbl(B);
     S.bnorm = dbl(B);
     S.alpha = dbl(B);
     S.alpha_prev = dbl(B);
@@ -407,7 +409,6 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     S.beta_prev = dbl(B);
     S.zeta = dbl(BN);
     S.zeta_prev = dbl(BN);
-    S.zeta_new = dbl(BN);
     S.sh_scale = dbl(BN);
     S.s_sold = dbl(BN);
     S.s_snew = dbl(BN);
@@ -435,6 +436,7 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     S.cnt_fl_r = lp; lp += B;
     S.cnt_fl_p = lp; lp += B;
     S.partial = w.partial.as<double>();
+    S.partial2 = w.partial2.as<double>();
     S.pstride = pstride;
     S.list = w.list.as<int>();
     S.count = w.count.as<int>();
@@ -586,7 +588,10 @@ void enqueue_block_update(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos
 // position with the partials of |r|^2 (the product itself is never stored).  The first
 // iteration of a block leaves the base direction it started from in place for the block update.
 // With timers, events bracket the two stencil launches and the updates.
-void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, GroupTimers *tm, bool captured) {
+// On small lattices the second stencil and the base direction compute the scalars from the partials
+// themselves (gi: the iteration's number in its group, whose parity names the buffer of |r|^2).
+void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, int gi, GroupTimers *tm,
+                       bool captured) {
     Workspace &w = c->ws;
     const Geom g = c->geom();
     hipStream_t s = c->stream;
@@ -601,24 +606,32 @@ void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, G
     char *rp = w.r.as<char>(), *pp = w.p.as<char>();
     // partials per slot of the first (D_W p) and the second (D_W^dag) stencil
     const int np_ds = dslash_partials(vp, g, false), np_dag = dslash_partials(vp, g, true);
+    const bool fused = L.alt && dslash_takes_partials(vp, g, true) && std::max(np_ds, np_dag) <= kFusedPartials;
+    double *rr_in = fused && gi % 2 ? S.rr1 : S.rr, *rr_out = fused && gi % 2 == 0 ? S.rr1 : S.rr;
     const Slots act{S.list, S.count, 0};
     const double s0 = c->coef->s0;
     if (tm) tm->dslash.record(s, captured);
     launch_dslash(vp, false, 3, U, w.p.p, L.pst, pofs, w.tmp.p, rs, nullptr, 0, 0, g, c->kappa, s0, act, B, S.partial,
-                  s, nullptr, nullptr, 0, S.done);
+                  s, ResidualStep{}, S.done);
     if (tm) tm->dslash.record(s, captured);
     const int m16 = vec16_mode(prec);
     if (m16) launch_round16(g, S, w.tmp.p, rs, 0, m16, s);   // D_W p as 16-bit storage would hold it
-    launch_scalars_alpha(S, np_ds, s);
+    if (!fused) launch_scalars_alpha(S, np_ds, s);
+    ResidualStep rstep{S.alpha, S.status, (ptrdiff_t)r_in - (ptrdiff_t)r_out};
+    if (fused) {
+        rstep.pap = S.partial;
+        rstep.rr = rr_in;
+        rstep.npart = np_ds;
+    }
     if (tm) tm->dslash.record(s, captured);
     launch_dslash(vp, true, 2, U, w.tmp.p, rs, 0, rp + r_out * kUnit, L.rst, w.p.p, L.pst, pofs, g, c->kappa, s0, act,
-                  B, S.partial, s, S.alpha, S.status, (ptrdiff_t)r_in - (ptrdiff_t)r_out, S.done);
+                  B, S.partial2, s, rstep, S.done);
     if (tm) tm->dslash.record(s, captured);
-    launch_scalars_beta(vp, S, np_dag, s);
+    if (!fused) launch_scalars_beta(vp, S, np_dag, s);
     if (tm) tm->update.record(s, captured);
     if (L.alt)
         launch_base_direction(vp, g, S, rp + r_out * kUnit, L.rst, pp + pofs * kUnit,
-                              pp + L.base(pos.par ^ 1) * kUnit, L.pst, s);
+                              pp + L.base(pos.par ^ 1) * kUnit, L.pst, fused ? np_ds : 0, np_dag, rr_in, rr_out, s);
     if (pos.n == S.K - 1)
         enqueue_block_update(c, prec, S, pos);
     else
@@ -629,7 +642,7 @@ void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, G
 
 // One group of kGroup iterations from the given position, then the list of the slots still iterating.
 void enqueue_group(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, GroupTimers *tm, bool captured) {
-    for (int gi = 0; gi < kGroup; ++gi) enqueue_iteration(c, prec, S, pos, tm, captured);
+    for (int gi = 0; gi < kGroup; ++gi) enqueue_iteration(c, prec, S, pos, gi, tm, captured);
     launch_compact(S, c->stream);
 }
 
@@ -1389,8 +1402,8 @@ double time_dslash(smpq_ctx *c, StencilBench &tb, int p, int n_rhs, int n_sets, 
                           tb.part.as<double>(), c->stream);
         if (mode != 2)
             launch_dslash(p, true, 2, tb.links[k].p, b, st, 0, tb.vecs[(size_t)k * nvec + 2].p, st, a, st, 0, g,
-                          c->kappa, 0.1, sl, n_rhs, tb.part.as<double>(), c->stream, tb.alpha.as<double>(),
-                          tb.status.as<int>());
+                          c->kappa, 0.1, sl, n_rhs, tb.part.as<double>(), c->stream,
+                          ResidualStep{tb.alpha.as<double>(), tb.status.as<int>()});
     };
     for (int i = 0; i < n_sets; ++i) one(i);   // warm-up
     hipEvent_t e0, e1;

@@ -56,8 +56,9 @@ struct Slots {
 struct MSState {
     int B, NS, i0, K;
     double tol;
-    double *rr, *bnorm, *alpha, *alpha_prev, *beta, *beta_prev;
-    double *zeta, *zeta_prev, *zeta_new;
+    double *rr, *rr1;    // |r|^2 (rr1: every other iteration where its readers and writer overlap)
+    double *bnorm, *alpha, *alpha_prev, *beta, *beta_prev;
+    double *zeta, *zeta_prev;
     int *sh_active, *sh_iters;
     int *done, *iters, *status;
     // the current block: iterations done and their coefficients, [slot][K][NS]: c_i a, a, and z and b
@@ -77,6 +78,7 @@ struct MSState {
     long long *cnt_fl, *cnt_fl_r, *cnt_fl_p;           // block updates, residuals and directions they moved
     const double *c, *delta;
     double *partial;     // per-block partial sums, slot stride pstride
+    double *partial2;    // the same of the second stencil of an iteration
     size_t pstride;
     int *list, *count;
 };
@@ -99,17 +101,26 @@ enum { kStatusOK = 0, kStatusBreakdown = 1 };
 //   epi 0: out = d
 //   epi 1: out = d + sigma * aux, partial[slot][block] = Re <aux, out>
 //   epi 3: out = d, partial = |d|^2 + sigma |in|^2   (= <in, (H^2 + sigma) in> when dag = 0)
-//   epi 2: out = r - alpha[slot] (d + sigma * aux), r read at out + r_ofs units (out = r when
+//   epi 2: out = r - alpha[slot] (d + sigma * aux), r read at out + rstep.r_ofs units (out = r when
 //          status[slot] is not OK); partial = |out|^2 (the product d + sigma aux is not stored)
 // done (nullable): slots whose flag is set are skipped.
 // prec: 0 = FP64, 1 = FP32 (FP32: epi 0 both ways, epi 3 with dag = 0, epi 1 and 2 with
 // dag = 1).  The kernel variant comes from g's tuning fields; epilogues 1-3 write
 // dslash_partials(prec, g) partials per slot.
+// Epilogue 2's step: alpha and status per slot, or (npart > 0, dslash_takes_partials) |r|^2 and the
+// npart partials of <p, A p> they follow from, slot stride partial_stride.
+struct ResidualStep {
+    const double *alpha = nullptr;
+    const int *status = nullptr;
+    ptrdiff_t r_ofs = 0;
+    const double *pap = nullptr, *rr = nullptr;
+    int npart = 0;
+};
 void launch_dslash(int prec, bool dag, int epi, const void *U, const void *in, size_t in_stride,
                    size_t in_extra, void *out, size_t out_stride, const void *aux, size_t aux_stride,
                    size_t aux_extra, const Geom &g, double kappa, double sigma, Slots sl, int max_slots,
-                   double *partial, hipStream_t st, const double *alpha = nullptr, const int *status = nullptr,
-                   ptrdiff_t r_ofs = 0, const int *done = nullptr);
+                   double *partial, hipStream_t st, const ResidualStep &rstep = {}, const int *done = nullptr);
+bool dslash_takes_partials(int prec, const Geom &g, bool dag);   // the variant can compute alpha itself
 __host__ __device__ int site_blocks(const Geom &g);   // blocks of 256 sites
 int dslash_partials(int prec, const Geom &g, bool dag);   // partials per slot of the stencil epilogue
 bool plane_tileable(const Geom &g);
@@ -137,9 +148,13 @@ void launch_scalars_init(const MSState &s, int npart, int nslots, hipStream_t st
 void launch_scalars_alpha(const MSState &s, int npart, hipStream_t st);
 void launch_scalars_beta(int prec, const MSState &s, int npart, hipStream_t st);
 // p_out = r + beta p_in of the base system, slots of the list that are not done; r at
-// slot * rst, p_in and p_out at slot * pst units.
+// slot * rst, p_in and p_out at slot * pst units.  np_pap > 0: instead of launch_scalars_alpha and
+// _beta, from the np_pap and np_rr partials of the two stencils, |r|^2 read from rr_in and
+// written to rr_out (another buffer); at most kFusedPartials of each.
+constexpr int kFusedPartials = 64;
 void launch_base_direction(int prec, const Geom &g, const MSState &s, const void *r, size_t rst, const void *p_in,
-                           void *p_out, size_t pst, hipStream_t st);
+                           void *p_out, size_t pst, int np_pap, int np_rr, const double *rr_in, double *rr_out,
+                           hipStream_t st);
 // Ends the block: what the block update has to do, blk_n = 0, and the new scales of 16-bit
 // directions.  base_inline: the block update writes the base direction too.
 void launch_block_end(const MSState &s, bool base_inline, int dir, hipStream_t st);
