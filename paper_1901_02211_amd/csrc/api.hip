@@ -196,6 +196,7 @@ struct smpq_ctx {
     DevMem d_pcolour, d_pptr;   // point scheme (identity) on demand
     Workspace ws;
     DevMem qx, qxi, lz;
+    DevMem io;   // spinors of the host-buffer calls, see IoBuffer
     bool timing = false;
     bool use_graphs = true;
     // per-shift FP64 true-residual check and mixed refinement (smpq_set_shift_check)
@@ -272,35 +273,56 @@ smpq_status guarded(smpq_ctx *c, F &&f) {
 // site); a field accepted with more than this (up to 1e-10) keeps its own third rows.
 constexpr double kRow3Tol = 1e-14;
 
+// Device memory of one host-buffer call: the context's, enlarged as needed, given back at the end
+// of the call unless it is small (an allocation of a few ten MB costs up to a millisecond).
+constexpr size_t kIoKept = size_t(128) << 20;
+struct IoBuffer {
+    smpq_ctx *c;
+    IoBuffer(smpq_ctx *ctx, size_t bytes) : c(ctx) { c->io.ensure(bytes); }
+    ~IoBuffer() {
+        if (c->io.bytes <= kIoKept) return;
+        (void)hipStreamSynchronize(c->stream);   // also after an error: launches may still use it
+        c->io.release();
+    }
+    template <class T>
+    T *as() const { return c->io.as<T>(); }
+};
+
 double now_s() {
     using namespace std::chrono;
     return duration<double>(steady_clock::now().time_since_epoch()).count();
 }
 
-// host spinor [rhs][site][spin][colour] complex128 <-> device [rhs][comp][site] double2
-void spinor_to_device(const smpq_ctx *c, const double *h, int n, std::vector<double> &stage) {
-    stage.assign((size_t)n * 24 * c->vs, 0.0);
-    for (int r = 0; r < n; ++r)
-        for (int s = 0; s < c->V; ++s)
-            for (int k = 0; k < 12; ++k) {
-                const double *src = h + ((size_t)r * c->V + s) * 24 + 2 * k;
-                double *dst = stage.data() + 2 * (((size_t)r * 12 + k) * c->vs + s);
-                dst[0] = src[0];
-                dst[1] = src[1];
-            }
+// host spinor [rhs][site][spin][colour] complex128 <-> device [rhs][comp][site] double2, n
+// right-hand sides: the host layout crosses as it is, in pieces through `stage`, and is converted on
+// the device (the host's loop over 24-double records took 20 of the 24 ms of a D_W on four 16^4
+// spinors).  The copy out returns when the host holds the data.
+constexpr size_t kStageBytes = size_t(64) << 20;   // of one piece, at least one right-hand side
+int stage_rhs(const smpq_ctx *c, int n) {
+    return (int)std::min<size_t>(n, std::max<size_t>(1, kStageBytes / ((size_t)c->V * 12 * sizeof(double2))));
+}
+size_t stage_bytes(const smpq_ctx *c, int n) { return (size_t)stage_rhs(c, n) * c->V * 12 * sizeof(double2); }
+
+void spinor_to_device(smpq_ctx *c, const double *h, int n, double2 *stage, double2 *dev) {
+    const int m = stage_rhs(c, n);
+    const size_t host_rhs = (size_t)24 * c->V, dev_rhs = 12 * c->vs;
+    for (int r = 0; r < n; r += m) {
+        const int k = std::min(m, n - r);
+        HIPCHK(hipMemcpyAsync(stage, h + r * host_rhs, k * host_rhs * sizeof(double), hipMemcpyHostToDevice, c->stream));
+        launch_layout(true, c->geom(), stage, dev + r * dev_rhs, k, c->stream);
+    }
 }
 
-void spinor_from_device(const smpq_ctx *c, const std::vector<double> &stage, int n, double *h) {
-    for (int r = 0; r < n; ++r)
-        for (int s = 0; s < c->V; ++s)
-            for (int k = 0; k < 12; ++k) {
-                const double *src = stage.data() + 2 * (((size_t)r * 12 + k) * c->vs + s);
-                double *dst = h + ((size_t)r * c->V + s) * 24 + 2 * k;
-                dst[0] = src[0];
-                dst[1] = src[1];
-            }
+void spinor_from_device(smpq_ctx *c, const double2 *dev, int n, double2 *stage, double *h) {
+    const int m = stage_rhs(c, n);
+    const size_t host_rhs = (size_t)24 * c->V, dev_rhs = 12 * c->vs;
+    for (int r = 0; r < n; r += m) {
+        const int k = std::min(m, n - r);
+        launch_layout(false, c->geom(), dev + r * dev_rhs, stage, k, c->stream);
+        HIPCHK(hipMemcpyAsync(h + r * host_rhs, stage, k * host_rhs * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    }
+    HIPCHK(hipStreamSynchronize(c->stream));
 }
-
 
 // The CG body runs in groups of kGroup iterations; the host reads the number of active
 // right-hand sides after each group.  The shifted systems, y and x0 are updated once per block of K
@@ -960,51 +982,42 @@ void ensure_point_device(smpq_ctx *c) {
     HIPCHK(hipMemcpy(c->d_pptr.p, id.data(), sizeof(int) * (c->V + 1), hipMemcpyHostToDevice));
 }
 
+// Extreme Ritz values of H^2 after `steps` steps.  alpha_j and beta_j stay on the device, summed by
+// the kernels that use them, and are read once at the end: waiting for two sums in every step
+// took 64 us a step on 8^3 x 16, the four kernels take a third of that.
 void lanczos(smpq_ctx *c, int steps, uint64_t seed, double *tmin, double *tmax) {
     const Geom g = c->geom();
     const size_t v64 = 12 * 16 * c->vs;
     c->lz.ensure(4 * v64);
     double2 *v = c->lz.as<double2>(), *vp = v + 12 * c->vs, *w = vp + 12 * c->vs, *t = w + 12 * c->vs;
-    const int np_ds = dslash_partials(0, g, true), np_unit = unit_parts(0, g);
-    DevMem part;
-    part.ensure(sizeof(double) * partial_stride(g));
-    std::vector<double> h((size_t)24 * c->V), stage;
-    for (size_t i = 0; i < h.size(); ++i) h[i] = 2.0 * splitmix64_uniform(seed, i) - 1.0;
-    double nrm = 0.0;
-    for (double x : h) nrm += x * x;
-    nrm = std::sqrt(nrm);
-    for (double &x : h) x /= nrm;
-    spinor_to_device(c, h.data(), 1, stage);
-    HIPCHK(hipMemsetAsync(c->lz.p, 0, 4 * v64, c->stream));
-    HIPCHK(hipMemcpyAsync(v, stage.data(), v64, hipMemcpyHostToDevice, c->stream));
-    std::vector<double> alpha, beta, hp(partial_stride(g));
+    const int np_ds = dslash_partials(0, g, true), np_w = site_blocks(g);
+    DevMem part, ab;
+    part.ensure(sizeof(double) * 2 * partial_stride(g));
+    ab.ensure(sizeof(double) * 2 * steps);
+    double *pd = part.as<double>(), *pw = pd + partial_stride(g);
+    double *da = ab.as<double>(), *db = da + steps;
+    launch_random_start(g, seed, w, pw, c->stream);
+    launch_lanczos_scale(g, v, w, pw, np_w, nullptr, c->stream);
     Slots one{nullptr, nullptr, 1};
-    double bprev = 0.0;
     for (int j = 0; j < steps; ++j) {
         launch_dslash(0, false, 0, c->U64.p, v, 0, 0, t, 0, nullptr, 0, 0, g, c->kappa, 0.0, one, 1, nullptr,
                       c->stream);
-        launch_dslash(0, true, 1, c->U64.p, t, 0, 0, w, 0, v, 0, 0, g, c->kappa, 0.0, one, 1, part.as<double>(),
-                      c->stream);
-        HIPCHK(hipMemcpyAsync(hp.data(), part.p, sizeof(double) * np_ds, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        double a = 0.0;
-        for (int i = 0; i < np_ds; ++i) a += hp[i];
-        alpha.push_back(a);
+        launch_dslash(0, true, 1, c->U64.p, t, 0, 0, w, 0, v, 0, 0, g, c->kappa, 0.0, one, 1, pd, c->stream);
+        launch_lanczos_step(g, w, v, j > 0 ? vp : nullptr, pd, np_ds, da + j, j > 0 ? db + j - 1 : nullptr, pw,
+                            c->stream);
         if (j == steps - 1) break;
-        launch_lanczos_update(g, w, v, vp, a, bprev, part.as<double>(), c->stream);
-        HIPCHK(hipMemcpyAsync(hp.data(), part.p, sizeof(double) * np_unit, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        double b2 = 0.0;
-        for (int i = 0; i < np_unit; ++i) b2 += hp[i];
-        const double b = std::sqrt(b2);
-        if (!(b > 0.0) || !std::isfinite(b)) break;
-        beta.push_back(b);
-        launch_scale(g, vp, w, 1.0 / b, c->stream);
+        launch_lanczos_scale(g, vp, w, pw, np_w, db + j, c->stream);
         std::swap(v, vp);
-        bprev = b;
     }
     HIPCHK(hipGetLastError());
-    beta.resize(alpha.size() - 1);
+    std::vector<double> alpha(steps), beta(steps);
+    HIPCHK(hipMemcpyAsync(alpha.data(), da, sizeof(double) * steps, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipMemcpyAsync(beta.data(), db, sizeof(double) * steps, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    int taken = 1;   // an invariant subspace ends the process: what follows is not used
+    while (taken < steps && beta[taken - 1] > 0.0 && std::isfinite(beta[taken - 1])) ++taken;
+    alpha.resize(taken);
+    beta.resize(taken - 1);
     tridiag_extremes(alpha, beta, tmin, tmax);
 }
 
@@ -1017,16 +1030,9 @@ void lanczos_full(smpq_ctx *c, int steps, uint64_t seed, double2 *Qp, DevMem &w,
     const Geom g = c->geom();
     const size_t vl = 12 * c->vs;
     hipStream_t s = c->stream;
-    std::vector<double> hv((size_t)24 * c->V), stage;
-    double nrm = 0.0;
-    for (size_t i = 0; i < hv.size(); ++i) {
-        hv[i] = 2.0 * splitmix64_uniform(seed, i) - 1.0;
-        nrm += hv[i] * hv[i];
-    }
-    for (double &x : hv) x /= std::sqrt(nrm);
-    spinor_to_device(c, hv.data(), 1, stage);
-    HIPCHK(hipMemcpyAsync(Qp, stage.data(), vl * sizeof(double2), hipMemcpyHostToDevice, s));
     double2 *wp = w.as<double2>();
+    launch_random_start(g, seed, wp, part.as<double>(), s);
+    launch_lanczos_scale(g, Qp, wp, part.as<double>(), site_blocks(g), nullptr, s);
     double2 hw[1];
     alpha.clear();
     beta.clear();
@@ -1771,28 +1777,26 @@ smpq_status smpq_apply_dw(smpq_ctx *c, const double *in, double *out, int n, int
         if (!c->have_gauge) throw Fail{SMPQ_ESTATE, "no gauge field loaded"};
         const Geom g = c->geom();
         const size_t v64 = 12 * 16 * c->vs, v32 = 6 * 16 * c->vs;
-        std::vector<double> stage;
-        spinor_to_device(c, in, n, stage);
-        DevMem a, b, a32, b32;
-        a.ensure(v64 * n);
-        b.ensure(v64 * n);
-        HIPCHK(hipMemcpyAsync(a.p, stage.data(), v64 * n, hipMemcpyHostToDevice, c->stream));
+        // in, out and the piece that crosses, in one allocation, kept for the next call where it is
+        // small
+        const size_t need = 2 * v64 * n + stage_bytes(c, n) + (prec == SMPQ_FP64 ? 0 : 2 * v32 * n);
+        IoBuffer io(c, need);
+        char *base = io.as<char>();
+        void *a = base, *b = base + v64 * n, *a32 = base + 2 * v64 * n, *b32 = base + 2 * v64 * n + v32 * n;
+        double2 *stage = reinterpret_cast<double2 *>(base + need - stage_bytes(c, n));
+        spinor_to_device(c, in, n, stage, static_cast<double2 *>(a));
         Slots sl{nullptr, nullptr, n};
         if (prec == SMPQ_FP64) {
-            launch_dslash(0, dagger != 0, 0, c->U64.p, a.p, 12 * c->vs, 0, b.p, 12 * c->vs, nullptr, 0, 0, g,
-                          c->kappa, 0.0, sl, n, nullptr, c->stream);
+            launch_dslash(0, dagger != 0, 0, c->U64.p, a, 12 * c->vs, 0, b, 12 * c->vs, nullptr, 0, 0, g, c->kappa, 0.0,
+                          sl, n, nullptr, c->stream);
         } else {
-            a32.ensure(v32 * n);
-            b32.ensure(v32 * n);
-            launch_convert(1, g, a.p, a32.p, n, c->stream);
-            launch_dslash(1, dagger != 0, 0, c->U32.p, a32.p, 6 * c->vs, 0, b32.p, 6 * c->vs, nullptr, 0, 0, g,
-                          c->kappa, 0.0, sl, n, nullptr, c->stream);
-            launch_convert(0, g, b32.p, b.p, n, c->stream);
+            launch_convert(1, g, a, a32, n, c->stream);
+            launch_dslash(1, dagger != 0, 0, c->U32.p, a32, 6 * c->vs, 0, b32, 6 * c->vs, nullptr, 0, 0, g, c->kappa,
+                          0.0, sl, n, nullptr, c->stream);
+            launch_convert(0, g, b32, b, n, c->stream);
         }
         HIPCHK(hipGetLastError());
-        HIPCHK(hipMemcpyAsync(stage.data(), b.p, v64 * n, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        spinor_from_device(c, stage, n, out);
+        spinor_from_device(c, static_cast<const double2 *>(b), n, stage, out);
     });
 }
 
@@ -1885,18 +1889,16 @@ smpq_status smpq_apply_dov(smpq_ctx *c, const double *in, double *out, int n) {
         const int NS = c->zolo.n;
         const Geom g = c->geom();
         const size_t v64 = 12 * 16 * c->vs;
-        std::vector<double> stage;
-        spinor_to_device(c, in, n, stage);
-        DevMem bin, bout, defl_part;
-        bin.ensure(v64 * n);
-        bout.ensure(v64 * n);
-        HIPCHK(hipMemcpyAsync(bin.p, stage.data(), v64 * n, hipMemcpyHostToDevice, c->stream));
+        DevMem defl_part;
+        IoBuffer io(c, 2 * v64 * n + stage_bytes(c, n));
+        double2 *bin = io.as<double2>(), *bout = bin + (size_t)n * 12 * c->vs, *stage = bout + (size_t)n * 12 * c->vs;
+        spinor_to_device(c, in, n, stage, bin);
         const BatchPlan plan = choose_batch(c, prec, NS, n, false);
         const int B = plan.B;
         ensure_workspace(c, prec, NS, B, plan.K);
         for (int k0 = 0; k0 < n; k0 += B) {
             const int nb = std::min(B, n - k0);
-            const double2 *bptr = bin.as<double2>() + (size_t)k0 * 12 * c->vs;
+            const double2 *bptr = bin + (size_t)k0 * 12 * c->vs;
             Source src{nullptr, nullptr, nullptr, bptr};
             const int dk = c->defl_k;
             if (dk > 0) {   // coefficients <u_i, b> of every right-hand side of the batch
@@ -1913,16 +1915,14 @@ smpq_status smpq_apply_dov(smpq_ctx *c, const double *in, double *out, int n) {
             // D_ov b = b + gamma5 eps b = b + D_W y   (eps b = gamma5 D_W y)
             Slots sl{nullptr, nullptr, nb};
             launch_dslash(0, false, 1, c->U64.p, c->ws.y.p, 12 * c->vs, 0,
-                          bout.as<double2>() + (size_t)k0 * 12 * c->vs, 12 * c->vs, bptr, 12 * c->vs, 0, g, c->kappa,
+                          bout + (size_t)k0 * 12 * c->vs, 12 * c->vs, bptr, 12 * c->vs, 0, g, c->kappa,
                           1.0, sl, nb, c->ws.partial.as<double>(), c->stream);
             if (dk > 0)
-                launch_add_defl(g, bout.as<double2>() + (size_t)k0 * 12 * c->vs, c->defl_w.as<double2>(), dk,
+                launch_add_defl(g, bout + (size_t)k0 * 12 * c->vs, c->defl_w.as<double2>(), dk,
                                 c->defl_coef.as<double2>(), nb, c->stream);
             HIPCHK(hipGetLastError());
         }
-        HIPCHK(hipMemcpyAsync(stage.data(), bout.p, v64 * n, hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        spinor_from_device(c, stage, n, out);
+        spinor_from_device(c, bout, n, stage, out);
     });
 }
 

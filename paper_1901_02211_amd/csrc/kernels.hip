@@ -573,7 +573,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 //   kTileNone   256 consecutive sites, all neighbours through the caches (kind 0, nx > 128)
 // A tile that is not whole planes has one halo row on each side.  Links: their first two rows (FP64
 // 96 bytes, FP32 48), the third rebuilt as conj(row0 x row1) (exact for SU(3) up to rounding); in
-// FP64 all nine entries (FULL) where a loaded link's third row is further than rounding from that.
+// FP64 all nine entries (FULL) outside the solver's iterations, and there where a loaded link's third
+// row is further than rounding from that.
 enum { kTileExact, kTileAny, kTileNone };
 
 // Rows ty of one plane and planes m of a kTileAny block (ty = ny where m > 1); ty = 0: kTileNone.
@@ -1020,13 +1021,21 @@ static void launch_rl(bool exact, const void *U, const void *in, size_t in_strid
     int ty, m;
     any_tile(g, ty, m);
     if constexpr (std::is_same<T, double>::value) {
-        if (exact && g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, true, false>);
-        else if (exact && nr == 1) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, true>);
-        else if (exact) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, false>);
-        else if (ty > 0 && g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, true, false>);
-        else if (ty > 0) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, false, false>);
-        else if (g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileNone, true, false>);
-        else go(launch_rl_t<double, 1, DAG, EPI, kTileNone, false, false>);
+        // D_W itself and H^2 + sigma (epilogues 0 and 1) keep the links as loaded: a rebuilt row costs
+        // a few 1e-16 of the result, which the solver's iterations (2 and 3) do not notice
+        if constexpr (EPI == 0 || EPI == 1) {
+            if (exact) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, true, false>);
+            else if (ty > 0) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, true, false>);
+            else go(launch_rl_t<double, 1, DAG, EPI, kTileNone, true, false>);
+        } else {
+            if (exact && g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, true, false>);
+            else if (exact && nr == 1) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, true>);
+            else if (exact) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, false>);
+            else if (ty > 0 && g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, true, false>);
+            else if (ty > 0) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, false, false>);
+            else if (g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileNone, true, false>);
+            else go(launch_rl_t<double, 1, DAG, EPI, kTileNone, false, false>);
+        }
     } else {
         if (exact && nr > 1) go(launch_rl_t<float, 2, DAG, EPI, kTileExact, false, false>);
         else if (exact) go(launch_rl_t<float, 1, DAG, EPI, kTileExact, false, true>);
@@ -1985,6 +1994,83 @@ void launch_lanczos_update(const Geom &g, double2 *w, const double2 *v, const do
                            double beta, double *partial, hipStream_t st) {
     hipLaunchKernelGGL(k_lanczos_update, dim3(unit_parts(0, g)), dim3(kBlock), 0, st, g, w, v, vprev, alpha, beta,
                        partial);
+}
+
+// Entry i (real and imaginary parts in order of site, spin, colour) of the start vector: 2 u - 1, u
+// the i-th SplitMix64 uniform of stream seed, as splitmix64_uniform gives it on the host.
+__device__ __forceinline__ double start_entry(uint64_t seed, uint64_t i) {
+    uint64_t z = seed + (i + 1) * 0x9e3779b97f4a7c15ull;
+    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
+    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
+    z ^= z >> 31;
+    return 2.0 * ((double)(z >> 11) * 0x1.0p-53) - 1.0;
+}
+
+// The Lanczos helpers below run one thread per site through its twelve components, so that a
+// vector's sum leaves site_blocks partials, few enough for every wave of the next kernel to add up.
+__global__ __launch_bounds__(kBlock) void k_random_start(Geom g, uint64_t seed, double2 *w, double *partial) {
+    const int s = blockIdx.x * kBlock + threadIdx.x;
+    double nrm = 0.0;
+    if (s < g.V) {
+        for (int c = 0; c < 12; ++c) {
+            const uint64_t i = 24 * (uint64_t)s + 2 * c;
+            const cpx<double> v = {start_entry(seed, i), start_entry(seed, i + 1)};
+            st64(w, g.vs, c, s, v);
+            nrm += v.re * v.re + v.im * v.im;
+        }
+    }
+    block_partial(nrm, partial, blockIdx.x);
+}
+
+void launch_random_start(const Geom &g, uint64_t seed, double2 *w, double *partial, hipStream_t st) {
+    hipLaunchKernelGGL(k_random_start, dim3(site_blocks(g)), dim3(kBlock), 0, st, g, seed, w, partial);
+}
+
+// alpha = <v, w> from the stencil's partials; w -= alpha v + beta vprev; partial |w|^2.
+__global__ __launch_bounds__(kBlock) void k_lanczos_step(Geom g, double2 *w, const double2 *v, const double2 *vprev,
+                                                         const double *dot_partials, int np, double *alpha_out,
+                                                         const double *beta_in, double *partial) {
+    const int s = blockIdx.x * kBlock + threadIdx.x;
+    const double a = wave_sum_partials(dot_partials, np);
+    const double b = vprev ? *beta_in : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha_out = a;
+    double nrm = 0.0;
+    if (s < g.V) {
+#pragma unroll
+        for (int c = 0; c < 12; ++c) {
+            cpx<double> t = ld64(w, g.vs, c, s);
+            const cpx<double> x = ld64(v, g.vs, c, s);
+            t = t - a * x;
+            if (vprev) t = t - b * ld64(vprev, g.vs, c, s);
+            st64(w, g.vs, c, s, t);
+            nrm += t.re * t.re + t.im * t.im;
+        }
+    }
+    block_partial(nrm, partial, blockIdx.x);
+}
+
+void launch_lanczos_step(const Geom &g, double2 *w, const double2 *v, const double2 *vprev, const double *dot_partials,
+                         int np, double *alpha_out, const double *beta_in, double *partial, hipStream_t st) {
+    hipLaunchKernelGGL(k_lanczos_step, dim3(site_blocks(g)), dim3(kBlock), 0, st, g, w, v, vprev, dot_partials, np,
+                       alpha_out, beta_in, partial);
+}
+
+// beta = |w| from its np partials; v = w / beta.
+__global__ __launch_bounds__(kBlock) void k_lanczos_scale(Geom g, double2 *v, const double2 *w,
+                                                          const double *partials, int np, double *beta_out) {
+    const int nsb = site_blocks(g);
+    const int c = blockIdx.x / nsb;
+    const int s = (blockIdx.x % nsb) * kBlock + threadIdx.x;
+    const double beta = sqrt(wave_sum_partials(partials, np));
+    if (beta_out && blockIdx.x == 0 && threadIdx.x == 0) *beta_out = beta;
+    if (s >= g.V) return;
+    const cpx<double> t = ld64(w, g.vs, c, s);
+    st64(v, g.vs, c, s, (1.0 / beta) * t);
+}
+
+void launch_lanczos_scale(const Geom &g, double2 *v, const double2 *w, const double *partials, int np, double *beta_out,
+                          hipStream_t st) {
+    hipLaunchKernelGGL(k_lanczos_scale, dim3(unit_parts(0, g)), dim3(kBlock), 0, st, g, v, w, partials, np, beta_out);
 }
 
 __global__ __launch_bounds__(kBlock) void k_scale(Geom g, double2 *dst, const double2 *src, double f) {
