@@ -601,7 +601,7 @@ void enqueue_block_update(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos
     launch_block_end(S, S.K == 1, dir, c->stream);
     launch_block_update(vp, g, S, w.r.p, w.p.p, L.pst, pos.par ? L.alt : 0, w.y.as<double2>(),
                         prec >= 1 ? w.x0.as<double2>() : nullptr, dir, w.ph.p, c->cur_xs, c->stream);
-    pos.advance(S.K - pos.n, S.K);
+    pos.advance(S.K - pos.n, S.K);   // to the start of the next block
 }
 
 // One CG iteration for every active slot of the batch (capacity-sized launches; inactive slots
@@ -663,7 +663,26 @@ void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, i
 }
 
 // One group of kGroup iterations from the given position, then the list of the slots still iterating.
+// On small lattices a launch takes all iterations up to the end of the group or the block (timed
+// groups keep the separate kernels, whose results are the same).
 void enqueue_group(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, GroupTimers *tm, bool captured) {
+    const int vp = vec_prec(prec);
+    const Geom g = c->geom();
+    const SolveLayout L(c, prec, S);
+    if (!tm && L.alt && small_lattice(vp, g)) {
+        char *pp = c->ws.p.as<char>();
+        for (int left = kGroup; left > 0;) {
+            const int n = std::min(left, S.K - pos.n);
+            launch_cg_small(vp, g, S, vp == 0 ? c->U64.p : c->U32.p, c->kappa, c->coef->s0,
+                            pp + L.base(pos.n == 0 ? pos.par : pos.par ^ 1) * kUnit, pp + L.base(pos.par ^ 1) * kUnit,
+                            L.pst, c->ws.r.p, pos.n, n, c->stream);
+            left -= n;
+            if (pos.n + n == S.K) enqueue_block_update(c, prec, S, pos);
+            else pos.advance(n, S.K);
+        }
+        launch_compact(S, c->stream);
+        return;
+    }
     for (int gi = 0; gi < kGroup; ++gi) enqueue_iteration(c, prec, S, pos, gi, tm, captured);
     launch_compact(S, c->stream);
 }

@@ -155,6 +155,14 @@ constexpr int kFusedPartials = 64;
 void launch_base_direction(int prec, const Geom &g, const MSState &s, const void *r, size_t rst, const void *p_in,
                            void *p_out, size_t pst, int np_pap, int np_rr, const double *rr_in, double *rr_out,
                            hipStream_t st);
+// Small lattices: up to `iters` iterations of the base system and the shifts' recurrences for every
+// listed slot in one launch (one workgroup per slot), from iteration n0 of the block: p_in and p_out
+// as the base direction's buffers, the residuals written to the ring.  Needs K > 1 and
+// n0 + iters <= K.
+constexpr int kSmallThreads = 512;
+bool small_lattice(int prec, const Geom &g);
+void launch_cg_small(int prec, const Geom &g, const MSState &s, const void *U, double kappa, double sigma,
+                     const void *p_in, void *p_out, size_t pst, void *ring, int n0, int iters, hipStream_t st);
 // Ends the block: what the block update has to do, blk_n = 0, and the new scales of 16-bit
 // directions.  base_inline: the block update writes the base direction too.
 void launch_block_end(const MSState &s, bool base_inline, int dir, hipStream_t st);

@@ -214,6 +214,36 @@ __device__ __forceinline__ int slot_count(const Slots &sl) { return sl.count ? *
 // yields <p, (H^2 + sigma) p> = |D_W p|^2 + sigma |p|^2, so alpha is known before the second
 // stencil, which with EPI 2 updates r directly and never writes (H^2 + sigma) p.  The vectors
 // are read and written one storage unit at a time, so that few extra registers are live.
+template <class T>
+__device__ __forceinline__ double norm2(cpx<T> v) {
+    return (double)v.re * (double)v.re + (double)v.im * (double)v.im;
+}
+// one entry's share of |d|^2 + sigma |e|^2
+template <class T>
+__device__ __forceinline__ double norm_term(cpx<T> d, cpx<T> e, T sigma) {
+    return (double)d.re * (double)d.re + (double)d.im * (double)d.im +
+           (double)sigma * ((double)e.re * (double)e.re + (double)e.im * (double)e.im);
+}
+// epilogues 3 and 2 on a spinor in registers (k_cg_small), the same sums in the same order
+template <class T>
+__device__ __forceinline__ double norm_step(const cpx<T> d[12], const cpx<T> self[12], T sigma) {
+    double acc = 0.0;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) acc += norm_term(d[c], self[c], sigma);
+    return acc;
+}
+template <class T>
+__device__ __forceinline__ double residual_step(cpx<T> d[12], const cpx<T> a[12], cpx<T> r[12], T sigma, T alpha) {
+    double acc = 0.0;
+#pragma unroll
+    for (int c = 0; c < 12; ++c) {
+        d[c] = d[c] + sigma * a[c];
+        r[c] = r[c] - alpha * d[c];
+        acc += norm2(r[c]);
+    }
+    return acc;
+}
+
 template <class T, int EPI>
 __device__ __forceinline__ double stencil_epilogue(cpx<T> d[12], const cpx<T> self[12],
                                                    const typename Store<T>::vec *aux,
@@ -243,7 +273,7 @@ __device__ __forceinline__ double stencil_epilogue(cpx<T> d[12], const cpx<T> se
 #pragma unroll
             for (int j = 0; j < CU; ++j) {
                 r[j] = r[j] - alpha * dk[j];
-                acc += (double)r[j].re * (double)r[j].re + (double)r[j].im * (double)r[j].im;
+                acc += norm2(r[j]);
             }
             unit_store_stream(out, vs, k, s, r);
         } else {
@@ -251,8 +281,7 @@ __device__ __forceinline__ double stencil_epilogue(cpx<T> d[12], const cpx<T> se
 #pragma unroll
                 for (int j = 0; j < CU; ++j) {
                     const cpx<T> e = self[k * CU + j];
-                    acc += (double)dk[j].re * (double)dk[j].re + (double)dk[j].im * (double)dk[j].im +
-                           (double)sigma * ((double)e.re * (double)e.re + (double)e.im * (double)e.im);
+                    acc += norm_term(dk[j], e, sigma);
                 }
             }
             unit_store_stream(out, vs, k, s, dk);
@@ -594,18 +623,22 @@ __host__ __device__ __forceinline__ void any_tile(const Geom &g, int &ty, int &m
     }
 }
 
-__device__ __forceinline__ void load_link64_rows(const double2 *U, int V, int mu, int s, cpx<double> u[9]) {
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-        const double2 t = unit_get(U + (size_t)(mu * 9 + k) * V, s);
-        u[k] = {t.x, t.y};
-    }
+// u's third row from its first two
+__device__ __forceinline__ void third_row(cpx<double> u[9]) {
     const cpx<double> r0 = cfma(u[1], u[5], -1.0 * cmul(u[2], u[4]));
     const cpx<double> r1 = cfma(u[2], u[3], -1.0 * cmul(u[0], u[5]));
     const cpx<double> r2 = cfma(u[0], u[4], -1.0 * cmul(u[1], u[3]));
     u[6] = {r0.re, -r0.im};
     u[7] = {r1.re, -r1.im};
     u[8] = {r2.re, -r2.im};
+}
+__device__ __forceinline__ void load_link64_rows(const double2 *U, int V, int mu, int s, cpx<double> u[9]) {
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+        const double2 t = unit_get(U + (size_t)(mu * 9 + k) * V, s);
+        u[k] = {t.x, t.y};
+    }
+    third_row(u);
 }
 template <bool FULL>
 __device__ __forceinline__ void load_link_rows(const double2 *U, int V, int mu, int s, cpx<double> u[9]) {
@@ -1380,54 +1413,96 @@ void launch_scalars_alpha(const MSState &s, int npart, hipStream_t st) {
     hipLaunchKernelGGL(k_scalars_alpha, dim3(s.B), dim3(64), 0, st, s, npart);
 }
 
-// One wave, lane i = shift i, after the residual update with step a: beta_k = |r_{k+1}|^2/|r_k|^2;
-// per active shift the new zeta, the block's coefficients alpha^i, beta^i and zeta^i, and
-// convergence (zeta^i_{k+1} |r_{k+1}| <= tol |b|).  The base shift's direction keeps being updated
-// while any shift of the slot is active (its alpha^i is 0 once it has converged).
+// The shifts' recurrences of one slot, one wave, lane i = shift i (NS <= 32): the state of a lane's
+// shift and of the slot, advanced after each residual update.
+struct ShiftLane {
+    double z, zp;                  // zeta^i and the one before
+    double alpha_prev, beta_prev;
+    double lim, delta, c;          // tol |b|, q_i - q_base, c_i
+    int act, it, j;                // shift active; iterations of the solve and of the block
+    long long entries, steps;      // listed shifts and iterations since load()
+
+    __device__ __forceinline__ void load(const MSState &S, int slot) {
+        const int i = threadIdx.x & 63, k = slot * S.NS + (i < S.NS ? i : 0);
+        z = S.zeta[k];
+        zp = S.zeta_prev[k];
+        act = i < S.NS && S.sh_active[k];
+        alpha_prev = S.alpha_prev[slot];
+        beta_prev = S.beta_prev[slot];
+        lim = S.tol * S.bnorm[slot];
+        delta = S.delta[i < S.NS ? i : 0];
+        c = S.c[i < S.NS ? i : 0];
+        it = S.iters[slot];
+        j = S.blk_n[slot];
+        entries = steps = 0;
+    }
+    // After the step a: beta_k = |r_{k+1}|^2/|r_k|^2; per active shift the new zeta, the block's
+    // coefficients alpha^i, beta^i and zeta^i, and convergence (zeta^i_{k+1} |r_{k+1}| <= tol |b|).
+    // The base shift's direction keeps being updated while any shift of the slot is active (its
+    // alpha^i is 0 once it has converged).  Returns whether one still is.
+    template <class T>
+    __device__ __forceinline__ bool advance(const MSState &S, int slot, double a, double rr, double rrn) {
+        const int i = threadIdx.x & 63;
+        const double b = rrn / rr;
+        bool conv = false;
+        const bool listed = act || i == S.i0;
+        if (i < S.NS) {
+            double ha = 0.0, hb = i == S.i0 ? b : 0.0, hz = i == S.i0 ? 1.0 : 0.0;
+            if (act) {
+                const double zn = z * zp * alpha_prev /
+                                  (a * beta_prev * (zp - z) + zp * alpha_prev * (1.0 + delta * a));
+                const double ratio = zn / z;
+                conv = zn * sqrt(rrn) <= lim;
+                ha = a * ratio;
+                hb = b * ratio * ratio;
+                hz = zn;
+                if (conv) S.sh_iters[slot * S.NS + i] = it + 1;
+                zp = z;
+                z = zn;
+            }
+            const size_t h = ((size_t)slot * S.K + j) * S.NS + i;
+            S.h_a[h] = ha;
+            S.h_cy[h] = c * ha;
+            static_cast<T *>(S.h_b)[h] = (T)hb;
+            static_cast<T *>(S.h_z)[h] = (T)hz;
+        }
+        entries += __popcll(__ballot(listed));
+        act = act && !conv;
+        alpha_prev = a;
+        beta_prev = b;
+        ++it;
+        ++j;
+        ++steps;
+        return __ballot(act) != 0;
+    }
+    __device__ __forceinline__ void store(const MSState &S, int slot, bool still, double rr, double *rr_out) const {
+        const int i = threadIdx.x & 63;
+        if (i < S.NS) {
+            const int k = slot * S.NS + i;
+            S.zeta[k] = z;
+            S.zeta_prev[k] = zp;
+            S.sh_active[k] = act;
+        }
+        if (i != 0) return;
+        if (!still) S.done[slot] = 1;   // slot finished: no direction needs updating any more
+        S.cnt_entries[slot] += entries;
+        S.cnt_active[slot] += steps;
+        S.alpha_prev[slot] = alpha_prev;
+        S.beta_prev[slot] = beta_prev;
+        S.beta[slot] = beta_prev;
+        rr_out[slot] = rr;
+        S.iters[slot] = it;
+        S.blk_n[slot] = j;
+    }
+};
+
 template <class T>
 __device__ __forceinline__ void advance_shifts(const MSState &S, int slot, double a, double rr, double rrn,
                                                double *rr_out) {
-    const int i = threadIdx.x & 63;
-    const double b = rrn / rr;
-    const double ap = S.alpha_prev[slot], bp = S.beta_prev[slot];
-    const int it = S.iters[slot], j = S.blk_n[slot];
-    const bool act = i < S.NS && S.sh_active[slot * S.NS + i];
-    bool conv = false;
-    if (i < S.NS) {
-        const int k = slot * S.NS + i;
-        double ha = 0.0, hb = i == S.i0 ? b : 0.0, hz = i == S.i0 ? 1.0 : 0.0;
-        if (act) {
-            const double z = S.zeta[k], zp = S.zeta_prev[k];
-            const double zn = z * zp * ap / (a * bp * (zp - z) + zp * ap * (1.0 + S.delta[i] * a));
-            const double ratio = zn / z;
-            conv = zn * sqrt(rrn) <= S.tol * S.bnorm[slot];
-            ha = a * ratio;
-            hb = b * ratio * ratio;
-            hz = zn;
-            if (conv) {
-                S.sh_active[k] = 0;
-                S.sh_iters[k] = it + 1;
-            }
-            S.zeta_prev[k] = z;
-            S.zeta[k] = zn;
-        }
-        const size_t h = ((size_t)slot * S.K + j) * S.NS + i;
-        S.h_a[h] = ha;
-        S.h_cy[h] = S.c[i] * ha;
-        static_cast<T *>(S.h_b)[h] = (T)hb;
-        static_cast<T *>(S.h_z)[h] = (T)hz;
-    }
-    const unsigned long long listed = __ballot(act || i == S.i0), still = __ballot(act && !conv);
-    if (i != 0) return;
-    if (still == 0) S.done[slot] = 1;   // slot finished: no direction needs updating any more
-    S.cnt_entries[slot] += __popcll(listed);
-    S.cnt_active[slot] += 1;
-    S.alpha_prev[slot] = a;
-    S.beta_prev[slot] = b;
-    S.beta[slot] = b;
-    rr_out[slot] = rrn;
-    S.iters[slot] = it + 1;
-    S.blk_n[slot] = j + 1;
+    ShiftLane lane;
+    lane.load(S, slot);
+    const bool still = lane.advance<T>(S, slot, a, rr, rrn);
+    lane.store(S, slot, still, rrn, rr_out);
 }
 
 template <class T>
@@ -1514,6 +1589,249 @@ void launch_base_direction(int prec, const Geom &g, const MSState &s, const void
     else
         hipLaunchKernelGGL(k_base_direction<float>, grid, dim3(kBlock), 0, st, g, s, (const float4 *)r, rst,
                            (const float4 *)p_in, (float4 *)p_out, pst, np_pap, np_rr, rr_in, rr_out);
+}
+
+// ------------------------------------------------------------------ small lattices
+// Iterations of a solve with one workgroup per right-hand side: on a lattice of at most
+// kSmallThreads sites the whole of one vector fits a CU's LDS, and a right-hand side needs no other
+// workgroup, so that an iteration is five barriers instead of three launches of 9 to 17 us that
+// each leave most of the chip idle.  The vector that the stencil reads is in LDS, the residuals and
+// links come from L2, and the first wave advances the shifts' recurrences.  Bound by the latency of
+// one or two waves per SIMD (LDS, links, reductions).  A whole 4^4 map of 192 right-hand sides:
+// FP64 11.1 -> 4.2 ms; 96 point sources on 420 sites (two tiles) in FP64 5.9 ms, mixed 4.0 ms
+// against about 10 in separate launches.
+// The sums have the order of the separate kernels (tiles of the stencil's blocks, their waves, one
+// wave over the tiles), so that results are equal bit for bit.
+template <class T, bool FULL>
+struct RawLink {
+    static constexpr int n = std::is_same<T, float>::value ? 3 : FULL ? 9 : 6, per = std::is_same<T, float>::value ? 3 : 9;
+    typename Store<T>::link v[n];
+    __device__ __forceinline__ void load(const typename Store<T>::link *U, int V, int mu, int s) {
+#pragma unroll
+        for (int k = 0; k < n; ++k) v[k] = unit_get(U + (size_t)(mu * per + k) * V, s);
+    }
+    __device__ __forceinline__ void unpack(cpx<T> u[9]) const {
+        if constexpr (std::is_same<T, float>::value) {
+            unpack_rows(v[0], v[1], v[2], u);
+        } else {
+#pragma unroll
+            for (int k = 0; k < n; ++k) u[k] = {v[k].x, v[k].y};
+            if constexpr (!FULL) third_row(u);
+        }
+    }
+};
+
+template <class T, bool FULL, bool EXACT, int MAXT>
+__global__ __launch_bounds__(MAXT) void k_cg_small(const typename Store<T>::link *__restrict__ U, Geom g,
+                                                            MSState S, int tpt, int np, T kappa, T sigma,
+                                                            const typename Store<T>::vec *p_in,
+                                                            typename Store<T>::vec *p_out, size_t pst,
+                                                            typename Store<T>::vec *ring, int n0, int iters) {
+    using vec = typename Store<T>::vec;
+    using link = typename Store<T>::link;
+    constexpr int TU = tile_units<T>, UN = Store<T>::units, CU = 12 / UN;
+    extern __shared__ __align__(16) unsigned char tile_raw[];
+    vec *field = reinterpret_cast<vec *>(tile_raw);   // [site][tile_units]
+    __shared__ double red[2][kSmallThreads / 64];
+    __shared__ int finished;
+    // (p, tmp and an accumulator in registers at once would not fit the 256 of two waves per SIMD)
+    if ((int)blockIdx.x >= *S.count) return;
+    const int slot = S.list[blockIdx.x];
+    if (S.done[slot]) return;
+    // the thread's site, as the stencil's tiles order them
+    const int sb = threadIdx.x / tpt, i = threadIdx.x - sb * tpt;
+    int s;
+    bool ok_site = true;
+    if constexpr (EXACT) {
+        const int tiles_per_plane = g.ny / g.tile_y;
+        s = plane_order(sb / tiles_per_plane, g) * g.nx * g.ny + (sb % tiles_per_plane) * g.tile_y * g.nx + i;
+    } else {
+        int ty, m;
+        any_tile(g, ty, m);
+        if (m > 1) {
+            s = sb * m * g.nx * g.ny + i;
+            ok_site = i < m * g.nx * g.ny && s < g.V;
+        } else {
+            const int tiles_per_plane = (g.ny + ty - 1) / ty, y0 = (sb % tiles_per_plane) * ty;
+            s = plane_order(sb / tiles_per_plane, g) * g.nx * g.ny + y0 * g.nx + i;
+            ok_site = i < min(ty, g.ny - y0) * g.nx;
+        }
+        if (!ok_site) s = 0;   // idle: computes site 0, stores nothing, adds nothing
+    }
+    const Nbr nb = neighbours(s, g.nx, g.ny, g.nz, g.nt);
+    const size_t rs = UN * g.vs;
+    vec *rp = ring + (size_t)slot * S.K * rs;
+    double rr = S.rr[slot];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, wpt = tpt >> 6;
+    if (threadIdx.x == 0) finished = 0;
+    const auto put = [&](const cpx<T> *v) {
+        if (!ok_site) return;
+#pragma unroll
+        for (int k = 0; k < UN; ++k) {
+            if constexpr (CU == 1) field[s * TU + k] = make_double2(v[k].re, v[k].im);
+            else field[s * TU + k] = make_float4(v[2 * k].re, v[2 * k].im, v[2 * k + 1].re, v[2 * k + 1].im);
+        }
+    };
+    // the sum over the block in the order of the separate kernels; its barrier also ends the reads of
+    // the field before it
+    const auto total = [&](double d, int which) {
+        d = wave_sum(d);
+        if (lane == 0) red[which][wv] = d;
+        __syncthreads();
+        double v = 0.0;
+        if (lane < np)
+            for (int k = 0; k < wpt; ++k) v += red[which][lane * wpt + k];
+        return wave_sum(v);
+    };
+    cpx<T> acc[12], u[9], q[12], h[6], w[6];
+    // D_W or D_W^dag of the field at the own site, q = the field there
+    // Each link is loaded one hop ahead (its rows as stored), since one or two waves per SIMD hide
+    // little of the latency of L2; where registers are short, once the link before it is unpacked.
+    constexpr bool kAhead = std::is_same<T, float>::value || MAXT <= 256;
+    RawLink<T, FULL> l0, l1;
+#define SMPQ_SMALL_HOP(MU, SF, CUR, NEXT, NMU, NSITE, SITE, MUL, FIRST)              \
+        if constexpr (kAhead) {                                                      \
+            NEXT.load(Ur, g.V, NMU, NSITE);                                          \
+            __builtin_amdgcn_sched_barrier(0);                                       \
+            CUR.unpack(u);                                                           \
+        } else {                                                                     \
+            CUR.unpack(u);                                                           \
+            NEXT.load(Ur, g.V, NMU, NSITE);                                          \
+        }                                                                            \
+        tile_read(field, SITE, q);                                                   \
+        project<MU, SF>(q, h);                                                       \
+        MUL(u, h, w);                                                                \
+        accumulate<MU, SF, FIRST>(acc, w);                                           \
+        __builtin_amdgcn_sched_barrier(0);
+    // l0 holds U_z(x) before and after
+#define SMPQ_SMALL_HOPS(SF)                                                          \
+        SMPQ_SMALL_HOP(2, SF, l0, l1, 2, nb.bwd[2], nb.fwd[2], su3_mul, true)        \
+        SMPQ_SMALL_HOP(2, -SF, l1, l0, 3, s, nb.bwd[2], su3_dag_mul, false)          \
+        SMPQ_SMALL_HOP(3, SF, l0, l1, 3, nb.bwd[3], nb.fwd[3], su3_mul, false)       \
+        SMPQ_SMALL_HOP(3, -SF, l1, l0, 0, s, nb.bwd[3], su3_dag_mul, false)          \
+        SMPQ_SMALL_HOP(0, SF, l0, l1, 0, nb.bwd[0], nb.fwd[0], su3_mul, false)       \
+        SMPQ_SMALL_HOP(0, -SF, l1, l0, 1, s, nb.bwd[0], su3_dag_mul, false)          \
+        SMPQ_SMALL_HOP(1, SF, l0, l1, 1, nb.bwd[1], nb.fwd[1], su3_mul, false)       \
+        SMPQ_SMALL_HOP(1, -SF, l1, l0, 2, s, nb.bwd[1], su3_dag_mul, false)          \
+        _Pragma("unroll") for (int c = 0; c < 12; ++c)                               \
+            asm volatile("" : "+v"(acc[c].re), "+v"(acc[c].im));
+    l0.load(U, g.V, 2, s);
+    __shared__ ShiftLane shifts[64];
+    if (wv == 0) shifts[lane].load(S, slot);
+    Store<T>::load(p_in + slot * pst, g.vs, s, q);
+    put(q);
+    __syncthreads();
+#pragma unroll 1
+    for (int it = 0; it < iters; ++it) {
+        // opaque in each iteration, so that the links are not hoisted into registers (as in k_dslash_rl)
+        const link *Ur = U;
+        asm volatile("" : "+s"(Ur));
+        // tmp = D_W p, <p, (H^2 + sigma) p>
+        SMPQ_SMALL_HOPS(1)
+        cpx<T> p[12];
+        tile_read(field, s, p);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = p[c] - kappa * acc[c];
+        const double pap = total(ok_site ? norm_step<T>(acc, p, sigma) : 0.0, 0);
+        if (!(pap > 0.0) || !isfinite(pap)) {   // uniform over the block
+            if (wv == 0) shifts[lane].store(S, slot, false, rr, S.rr);
+            if (threadIdx.x == 0) S.status[slot] = kStatusBreakdown;
+            return;
+        }
+        const double a = rr / pap;
+        put(acc);
+        __syncthreads();
+        // r -= alpha (D_W^dag tmp + sigma p)
+        SMPQ_SMALL_HOPS(-1)
+        tile_read(field, s, q);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) acc[c] = q[c] - kappa * acc[c];
+        const int n = n0 + it;
+        Store<T>::load(rp + (size_t)(n == 0 ? S.K - 1 : n - 1) * rs, g.vs, s, q);
+        double d = residual_step<T>(acc, p, q, sigma, (T)a);
+        if (ok_site) {
+#pragma unroll
+            for (int k = 0; k < UN; ++k) unit_store_stream(rp + (size_t)n * rs, g.vs, k, s, q + k * CU);
+        } else {
+            d = 0.0;
+        }
+        const double rrn = total(d, 1);
+        const T b = (T)(rrn / rr);
+        if (wv == 0) {
+            ShiftLane sh = shifts[lane];
+            const bool still = sh.template advance<T>(S, slot, a, rr, rrn);
+            if (!still || it == iters - 1) sh.store(S, slot, still, rrn, S.rr);
+            else shifts[lane] = sh;
+            if (lane == 0 && !still) finished = 1;
+        }
+#pragma unroll
+        for (int c = 0; c < 12; ++c) q[c] = next_direction(T(1), q[c], b, p[c]);
+        rr = rrn;
+        put(q);
+        __syncthreads();
+        if (finished) return;   // uniform over the block; its direction is not needed any more
+    }
+#undef SMPQ_SMALL_HOPS
+#undef SMPQ_SMALL_HOP
+    if (ok_site) {
+#pragma unroll
+        for (int k = 0; k < UN; ++k) unit_store_stream(p_out + slot * pst, g.vs, k, s, q + k * CU);
+    }
+}
+
+// Threads of a k_cg_small block where one fits the lattice and the default variants are in use, else 0.
+static int small_block(int prec, const Geom &g, int &tpt, int &np) {
+    if (!g.adapt) return 0;
+    if (g.tile_y > 0) {
+        tpt = g.nx * g.tile_y;
+        np = tile_blocks(g);
+    } else {
+        int ty, m;
+        any_tile(g, ty, m);
+        if (ty == 0) return 0;
+        tpt = (m * g.nx * ty + 63) / 64 * 64;
+        np = any_blocks(g);
+    }
+    return (long long)tpt * np <= kSmallThreads && g.V <= kSmallThreads ? tpt * np : 0;
+}
+
+bool small_lattice(int prec, const Geom &g) {
+    int tpt, np;
+    return small_block(prec, g, tpt, np) > 0;
+}
+
+template <class T>
+static void launch_cg_small_t(const Geom &g, const MSState &s, const void *U, double kappa, double sigma,
+                              const void *p_in, void *p_out, size_t pst, void *ring, int n0, int iters,
+                              hipStream_t st) {
+    using vec = typename Store<T>::vec;
+    using link = typename Store<T>::link;
+    constexpr bool dbl = std::is_same<T, double>::value;
+    int tpt, np;
+    const int threads = small_block(dbl ? 0 : 1, g, tpt, np);
+    if (threads == 0 || n0 + iters > s.K) throw std::invalid_argument("not a small lattice, or too many iterations");
+    const size_t lds = (size_t)g.V * tile_units<T> * sizeof(vec);
+    const auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(s.B), dim3(threads), lds, st, (const link *)U, g, s, tpt, np, (T)kappa, (T)sigma,
+                           (const vec *)p_in, (vec *)p_out, pst, (vec *)ring, n0, iters);
+    };
+    // up to 256 threads the block has a SIMD's registers per wave
+    const bool exact = g.tile_y > 0;
+    if constexpr (dbl) {
+        if (g.f64_full) return exact ? go(k_cg_small<T, true, true, kSmallThreads>)
+                                     : go(k_cg_small<T, true, false, kSmallThreads>);
+        if (threads <= 256) return exact ? go(k_cg_small<T, false, true, 256>) : go(k_cg_small<T, false, false, 256>);
+    }
+    if (exact) go(k_cg_small<T, false, true, kSmallThreads>);
+    else go(k_cg_small<T, false, false, kSmallThreads>);
+}
+
+void launch_cg_small(int prec, const Geom &g, const MSState &s, const void *U, double kappa, double sigma,
+                     const void *p_in, void *p_out, size_t pst, void *ring, int n0, int iters, hipStream_t st) {
+    if (prec == 0)
+        launch_cg_small_t<double>(g, s, U, kappa, sigma, p_in, p_out, pst, ring, n0, iters, st);
+    else
+        launch_cg_small_t<float>(g, s, U, kappa, sigma, p_in, p_out, pst, ring, n0, iters, st);
 }
 
 // ------------------------------------------------------------------ block update of the shifts

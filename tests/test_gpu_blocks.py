@@ -121,3 +121,38 @@ def test_inexact_third_row_is_kept(dims):
             ref = np.stack([apply_dw(U, lat, KAPPA, p, dagger=dag) for p in psi])
             out = smpq.smpq_apply_dw(c, psi, dagger=dag)
             assert np.abs(out - ref).max() <= 1e-13 * np.abs(ref).max(), (tune, dag)
+
+
+@pytest.mark.parametrize("inexact", [False, True])    # FP64 links read as two rows, or in full
+@pytest.mark.parametrize("dims", [(4, 4, 4, 4), (3, 3, 3, 3), (8, 8, 2, 2), (5, 3, 4, 7), (16, 16, 2, 1), (17, 17, 1, 1)])
+def test_small_lattices_equal_separate_kernels(dims, inexact):
+    """Up to 512 threads of stencil tiles (one or two tiles of 256, 64-thread tiles, several planes or
+    ragged rows per tile) a right-hand side is solved by one workgroup; timed solves keep the separate
+    kernels, with results equal bit for bit: D_ov and point densities, in blocks cut short by
+    reliable updates and by convergence."""
+    print(f"small lattice {dims}, inexact links {inexact}", flush=True)
+    V = int(np.prod(dims))
+    U = si.near_identity_su3(dims, 0.3, 7)
+    if inexact:
+        U[:, :, 2] += 1e-11 * np.random.default_rng(8).standard_normal(U[:, :, 2].shape)
+    psi = si.random_spinors(dims, 2, 4)
+    for prec, reliable in ((0, 0), (1, 30)):
+        out = []
+        for timing in (False, True):
+            c = smpq.smpq_create(dims, 0)
+            smpq.smpq_load_gauge(c, U)
+            smpq.smpq_set_zolotarev(c, 14, 0.12, 2.75)
+            smpq.smpq_set_solver(c, prec, 1e-12, 5000, reliable)
+            smpq.smpq_set_timing(c, timing)
+            q, st = smpq.smpq_compute_qx_points(c, [0, V // 2, V - 1])
+            out.append((q, smpq.smpq_apply_dov(c, psi), st["total_iters"], st["shift_updates"]))
+        assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1]), prec
+        assert out[0][2:] == out[1][2:]
+    # a solve that breaks off at max_iter leaves the context usable
+    smpq.smpq_set_timing(c, False)
+    smpq.smpq_set_solver(c, 0, 1e-12, 10, 0)
+    with pytest.raises(smpq.SmpqError) as e:
+        smpq.smpq_apply_dov(c, psi)
+    assert e.value.status == -5
+    smpq.smpq_set_solver(c, 1, 1e-12, 5000, 30)
+    assert np.array_equal(smpq.smpq_apply_dov(c, psi), out[0][1])
