@@ -32,6 +32,7 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 namespace {
 
 constexpr int kMaxDevices = 64;
+constexpr int kGroupGraphs = 10;   // captured groups: five places in the longest block, two buffers
 std::mutex scratch_mu;
 void *scratch_ptr[kMaxDevices] = {};
 
@@ -209,12 +210,12 @@ struct smpq_ctx {
     // base direction's buffer; rebuilt when anything they capture (workspace, links,
     // coefficients, solver settings) changes
     // [timed][variant]; the timed graphs carry event nodes around the stencil and update kernels
-    hipGraphExec_t graphs[2][4] = {{nullptr, nullptr, nullptr, nullptr}, {nullptr, nullptr, nullptr, nullptr}};
-    long long graph_gen[2][4] = {{-1, -1, -1, -1}, {-1, -1, -1, -1}};
-    GroupTimers graph_timers[4];
+    hipGraphExec_t graphs[2][kGroupGraphs] = {};
+    long long graph_gen[2][kGroupGraphs] = {};   // c->gen a graph was captured at (0: none)
+    GroupTimers graph_timers[kGroupGraphs];
     GroupTimers eager_timers;
     bool graph_timing_ok = true;
-    long long gen = 0;
+    long long gen = 1;
     int *h_count = nullptr;     // pinned
     // stencil variant (see Geom)
     int f32_kind = 0, f32_nr = 2, f64_lgr = 0, band = 1, f64_kind = 0, f64_nr = 1, f32_il = 1, f64_il = 1;
@@ -331,12 +332,17 @@ void spinor_from_device(smpq_ctx *c, const double2 *dev, int n, double2 *stage, 
 constexpr int kGroup = 10;   // even: the buffers of |r|^2 alternate within a group
 constexpr size_t kUnit = 16;   // bytes of a storage unit (double2 or float4)
 
-// Iterations per block, longest first.  K > 1 needs a second buffer for the base direction.  With
-// K = 20 the update moves, per site and iteration in FP32 with n active shifts, 134 + 9.6 n bytes
-// (K = 10: 173 + 19 n; K = 1, which takes the memory of a residual updated in place:
-// 864 + 192 n, as much as an update in every iteration).  A longer block buys little more and
-// holds K vectors per right-hand side.
-constexpr int kBlockIters[] = {20, 10, 5, 2, 1};
+// Iterations per block, longest first.  K > 1 needs a second buffer for the base direction.  Per site
+// and iteration in FP32 with n active shifts the update moves 96 + (768 + 192 n) / K bytes: with
+// n = 7 on average 138 at K = 50, 202 at 20, 307 at 10; K = 1, which takes the memory of a
+// residual updated in place, as much as an update in every iteration.  50 is the usual interval of
+// the reliable updates, which end a block; against 20 whole solves take 1.5 to 3 % less time
+// (16^4 in FP64 295 -> 290 ms, the trace of D_W^-1 on 16^4 262 -> 254) for 30 more vectors per
+// right-hand side.  So it is taken only where it leaves three quarters of the device's memory to
+// others: three contexts on 16^3x32 with 120 right-hand sides and 112 GB each left the last one
+// smaller batches, 995 ms against 690.
+constexpr int kBlockIters[] = {50, 20, 10, 5, 2, 1};
+constexpr int kSharedBlock = 20;   // the longest block without that condition
 // Sites x right-hand sides that keep the kernels busy: below this a batch is not made smaller for a
 // longer block.
 constexpr long long kFillSites = 4 << 20;
@@ -496,8 +502,13 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
     const size_t limit = c->run_limit > 0 ? c->run_limit : c->mem_limit;
     const double budget = limit > 0 ? (double)limit : 0.80 * (double)(freeb + held);
     const int q = multiple_of_12 ? 12 : 1;
+    // without a limit, the batch that the workspace was laid out for stays possible however little
+    // other contexts have left
+    const Workspace &w = c->ws;
+    const bool reuse = limit == 0 && w.S.rr && w.prec == prec && w.NS == NS && w.check == c->shift_check;
     auto most = [&](int K) {
         long long B = (long long)(budget / (double)bytes_per_slot(c, prec, NS, K));
+        if (reuse && K == w.K) B = std::max<long long>(B, w.B);
         if (c->max_rhs > 0) B = std::min<long long>(B, c->max_rhs);
         return std::min<long long>(B, total_slots) / q * q;
     };
@@ -506,7 +517,9 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
     int K = 1;
     if (!short_block(prec))
         for (int k : kBlockIters)
-            if (most(k) >= std::max<long long>(fill, q)) {
+            if (most(k) >= std::max<long long>(fill, q) &&
+                (k <= kSharedBlock ||
+                 (double)most(k) * (double)bytes_per_slot(c, prec, NS, k) <= 0.25 * (double)totalb)) {
                 K = k;
                 break;
             }
@@ -529,7 +542,8 @@ void ensure_workspace_for(smpq_ctx *c, int prec, int NS, int B) {
     int K = 1;
     if (!short_block(prec))
         for (int k : kBlockIters)
-            if ((double)B * (double)bytes_per_slot(c, prec, NS, k) <= budget) {
+            if ((double)B * (double)bytes_per_slot(c, prec, NS, k) <=
+                (k <= kSharedBlock ? budget : std::min(budget, 0.25 * (double)totalb))) {
                 K = k;
                 break;
             }
@@ -697,7 +711,7 @@ GroupTimers *launch_group(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos
         enqueue_group(c, prec, S, pos, tm, false);
         return tm;
     }
-    const int v = (pos.n ? 2 : 0) + pos.par;   // a group starts a block or is the second half of one
+    const int v = 2 * (pos.n / kGroup) + pos.par;   // a group starts a block or is a later part of one
     if (c->graph_coef != c->coef) {   // the graphs hold the coefficients of the other set
         c->gen++;
         c->graph_coef = c->coef;
@@ -2088,7 +2102,7 @@ smpq_status smpq_compute_qx_multi(smpq_ctx *const *ctxs, int n_ctx, const int32_
             slotb[k] = (double)bytes_per_slot(c, prec, c->zolo.n, 1);
             share[k] = 12.0 * slotb[k];
             cap[k] = 12.0 * (double)cls[k].size() *
-                     (double)bytes_per_slot(c, prec, c->zolo.n, short_block(prec) ? 1 : kBlockIters[0]);
+                     (double)bytes_per_slot(c, prec, c->zolo.n, short_block(prec) ? 1 : kSharedBlock);
             pool -= share[k];
             open[k] = 1;
         }

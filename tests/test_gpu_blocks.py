@@ -43,7 +43,7 @@ def test_block_lengths_equal(prec, reliable, poles):
     smpq.smpq_set_scheme(c, (2, 2, 2, 2), 0)
     smpq.smpq_set_solver(c, prec, 1e-12, 5000, reliable)
     want = smpq.smpq_compute_qx_classes(c, [5])
-    for k in (20, 10, 5, 2, 1):
+    for k in (50, 20, 10, 5, 2, 1):
         smpq.smpq_set_memory_limit(c, 12 * _slot_bytes(prec, poles, k, 576))
         got = smpq.smpq_compute_qx_classes(c, [5])
         assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1]), k
