@@ -361,15 +361,20 @@ inline bool short_block(int prec) { return prec >= 2; }
 // K > 1, the second buffer of the base direction
 inline int dir_entries(int prec, int NS, int K) { return (dir_store(prec) == kDirF32 ? NS : 1) + (K > 1 ? 1 : 0); }
 
+// Between blocks only the last place of the ring is in use: from K = 5 on its first four places hold
+// the two FP64 vectors of a reliable update.  The per-shift check keeps vectors of its own.
+inline bool ring_scratch(int prec, int K, bool check) { return prec >= 1 && K >= 5 && !check; }
+
 size_t bytes_per_slot(const smpq_ctx *c, int prec, int NS, int K) {
     const size_t v64 = 12 * 16 * c->vs, v32 = 6 * 16 * c->vs, v16 = v32 / 2;
     // per-shift check: x_i for every shift, the residual and the saved y (+ tmp64 and ap64 in FP64)
     const size_t check = c->shift_check ? (NS + 2) * v64 + (prec == 0 ? 2 * v64 : 0) : 0;
-    // K residuals, tmp, the directions and y (+ in the FP32 path the FP64 x0, tmp64 and ap64 of the
-    // reliable updates)
+    // K residuals, tmp, the directions and y (+ in the FP32 path the FP64 x0 and, unless the ring has
+    // room for them, tmp64 and ap64 of the reliable updates)
     const size_t nt = K + 1 + dir_entries(prec, NS, K);
     if (prec == 0) return (nt + 1) * v64 + check;
-    return nt * v32 + (dir_store(prec) != kDirF32 ? NS * v16 : 0) + 4 * v64 + check;
+    return nt * v32 + (dir_store(prec) != kDirF32 ? NS * v16 : 0) + (ring_scratch(prec, K, c->shift_check) ? 2 : 4) * v64 +
+           check;
 }
 
 void release_vectors(Workspace &w) {
@@ -401,8 +406,10 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     w.y.ensure(v64 * B);
     if (prec >= 1) {
         w.x0.ensure(v64 * B);
-        w.tmp64.ensure(v64 * B);
-        w.ap64.ensure(v64 * B);
+        if (!ring_scratch(prec, K, w.check)) {
+            w.tmp64.ensure(v64 * B);
+            w.ap64.ensure(v64 * B);
+        }
     }
     if (w.check) {
         w.xs.ensure(v64 * B * NS);
@@ -506,23 +513,31 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
     // other contexts have left
     const Workspace &w = c->ws;
     const bool reuse = limit == 0 && w.S.rr && w.prec == prec && w.NS == NS && w.check == c->shift_check;
-    auto most = [&](int K) {
-        long long B = (long long)(budget / (double)bytes_per_slot(c, prec, NS, K));
-        if (reuse && K == w.K) B = std::max<long long>(B, w.B);
+    auto most = [&](int K, size_t extra = 0) {
+        long long B = (long long)(budget / (double)(bytes_per_slot(c, prec, NS, K) + extra));
+        if (reuse && K == w.K && extra == 0) B = std::max<long long>(B, w.B);
         if (c->max_rhs > 0) B = std::min<long long>(B, c->max_rhs);
         return std::min<long long>(B, total_slots) / q * q;
     };
-    // the longest block that leaves a batch of every source, or one that fills the device
-    const long long fill = std::min<long long>(most(1), (kFillSites / c->V + q) / q * q);
+    auto batches = [&](long long B) { return B < q ? 0 : (total_slots + B - 1) / B; };
+    // Mixed: the longest block that makes no more batches than K = 1 with two FP32 vectors to spare
+    // (the memory of 18 FP32 and four FP64 vectors per source).  A whole 16^3x32 map gets K = 10 in 5
+    // batches, 19.7 s; K = 20 would take 18.7 s in 8.  FP64: the longest block that leaves a batch of
+    // every source, or one that fills the device; batches of the same number would leave that map
+    // at K = 1, 65.5 s.
+    const long long allowed = std::max(batches(most(1)), batches(most(1, 2 * 6 * 16 * c->vs)));
+    const long long fill = std::max<long long>(std::min(most(1), (kFillSites / c->V + q) / q * q), q);
+    auto fits = [&](int k) { return prec == 0 ? most(k) >= fill : most(k) >= q && batches(most(k)) <= allowed; };
     int K = 1;
     if (!short_block(prec))
-        for (int k : kBlockIters)
-            if (most(k) >= std::max<long long>(fill, q) &&
+        for (int k : kBlockIters) {
+            if (fits(k) &&
                 (k <= kSharedBlock ||
                  (double)most(k) * (double)bytes_per_slot(c, prec, NS, k) <= 0.25 * (double)totalb)) {
                 K = k;
                 break;
             }
+        }
     const long long B = most(K);
     if (B < q) throw Fail{SMPQ_ENOMEM, "not enough device memory for one batch of right-hand sides"};
     // spread the right-hand sides evenly over the batches this limit implies
@@ -773,6 +788,11 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     const SolveLayout L(c, prec, S);
     // the residual a block starts from is at the ring's last position
     char *r0 = w.r.as<char>() + L.rs * (S.K - 1) * kUnit;
+    // FP64 scratch of the reliable updates and its stride per right-hand side
+    const bool in_ring = ring_scratch(prec, S.K, w.check);
+    double2 *t64 = in_ring ? w.r.as<double2>() : w.tmp64.as<double2>();
+    double2 *a64 = in_ring ? w.r.as<double2>() + 2 * L.rs : w.ap64.as<double2>();
+    const size_t st64 = in_ring ? L.rst : rs64;
 
     const bool check = c->shift_check && !c->refining;
     if (check && !w.check) throw Fail{SMPQ_ESTATE, "workspace laid out without the per-shift check"};
@@ -799,11 +819,11 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
         if (mixed && c->reliable > 0 && iter % c->reliable == 0) {
             // residual replacement: x0 up to date, r = b - (H^2 + s0) x0 in FP64
             if (pos.n > 0) enqueue_block_update(c, prec, S, pos);
-            launch_dslash(0, false, 0, c->U64.p, w.x0.p, rs64, 0, w.tmp64.p, rs64, nullptr, 0, 0, g,
+            launch_dslash(0, false, 0, c->U64.p, w.x0.p, rs64, 0, t64, st64, nullptr, 0, 0, g,
                           c->kappa, 0.0, act, S.B, nullptr, s);
-            launch_dslash(0, true, 1, c->U64.p, w.tmp64.p, rs64, 0, w.ap64.p, rs64, w.x0.p, rs64, 0, g,
+            launch_dslash(0, true, 1, c->U64.p, t64, st64, 0, a64, st64, w.x0.p, rs64, 0, g,
                           c->kappa, s0, act, S.B, S.partial, s);
-            launch_reliable(vp, g, S, src, w.ap64.as<double2>(), r0, L.rst, s);
+            launch_reliable(vp, g, S, src, a64, st64, r0, L.rst, s);
             launch_scalars_rr(S, np_unit, s);
             res.n_reliable++;
         }
@@ -829,11 +849,11 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
         *c->h_count = nslots;
         HIPCHK(hipMemcpyAsync(S.list, all.data(), sizeof(int) * nslots, hipMemcpyHostToDevice, s));
         HIPCHK(hipMemcpyAsync(S.count, c->h_count, sizeof(int), hipMemcpyHostToDevice, s));
-        launch_dslash(0, false, 0, c->U64.p, w.x0.p, rs64, 0, w.tmp64.p, rs64, nullptr, 0, 0, g, c->kappa, 0.0, act,
+        launch_dslash(0, false, 0, c->U64.p, w.x0.p, rs64, 0, t64, st64, nullptr, 0, 0, g, c->kappa, 0.0, act,
                       S.B, nullptr, s);
-        launch_dslash(0, true, 1, c->U64.p, w.tmp64.p, rs64, 0, w.ap64.p, rs64, w.x0.p, rs64, 0, g, c->kappa, s0,
+        launch_dslash(0, true, 1, c->U64.p, t64, st64, 0, a64, st64, w.x0.p, rs64, 0, g, c->kappa, s0,
                       act, S.B, S.partial, s);
-        launch_reliable(vp, g, S, src, w.ap64.as<double2>(), r0, L.rst, s);
+        launch_reliable(vp, g, S, src, a64, st64, r0, L.rst, s);
         launch_scalars_rr(S, np_unit, s);
         HIPCHK(hipGetLastError());
         std::vector<double> rr(nslots), bn(nslots);

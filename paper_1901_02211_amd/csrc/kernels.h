@@ -178,7 +178,7 @@ void launch_compact(const MSState &s, hipStream_t st);
 // or BF16 (mode 2).
 void launch_round16(const Geom &g, const MSState &s, void *v, size_t slot_stride, size_t extra, int mode,
                     hipStream_t st);
-void launch_reliable(int prec, const Geom &g, const MSState &s, const Source &src, const double2 *ap64,
+void launch_reliable(int prec, const Geom &g, const MSState &s, const Source &src, const double2 *ap64, size_t ast,
                      void *r, size_t rst, hipStream_t st);
 void launch_scalars_rr(const MSState &s, int npart, hipStream_t st);
 

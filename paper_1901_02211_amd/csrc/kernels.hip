@@ -2095,7 +2095,7 @@ void launch_compact(const MSState &s, hipStream_t st) {
 // stored in the iteration precision; partial |r|^2 of the stored values.
 template <class T>
 __global__ __launch_bounds__(kBlock) void k_reliable(Geom g, MSState S, Source src, const double2 *ap64,
-                                                     typename Store<T>::vec *r, size_t rst) {
+                                                     size_t ast, typename Store<T>::vec *r, size_t rst) {
     constexpr int C = Unit<T>::C;
     if ((int)blockIdx.y >= *S.count) return;
     const int slot = S.list[blockIdx.y];
@@ -2108,7 +2108,7 @@ __global__ __launch_bounds__(kBlock) void k_reliable(Geom g, MSState S, Source s
 #pragma unroll
         for (int i = 0; i < C; ++i) {
             const int c = u * C + i;
-            const cpx<double> d = source_entry(src, slot, c, s, g.vs) - ld64(ap64 + (size_t)slot * 12 * g.vs, g.vs, c, s);
+            const cpx<double> d = source_entry(src, slot, c, s, g.vs) - ld64(ap64 + slot * ast, g.vs, c, s);
             rv[i] = {(T)d.re, (T)d.im};
             nrm += (double)rv[i].re * rv[i].re + (double)rv[i].im * rv[i].im;
         }
@@ -2117,13 +2117,13 @@ __global__ __launch_bounds__(kBlock) void k_reliable(Geom g, MSState S, Source s
     block_partial(nrm, S.partial, (size_t)slot * S.pstride + blockIdx.x);
 }
 
-void launch_reliable(int prec, const Geom &g, const MSState &s, const Source &src, const double2 *ap64, void *r,
-                     size_t rst, hipStream_t st) {
+void launch_reliable(int prec, const Geom &g, const MSState &s, const Source &src, const double2 *ap64, size_t ast,
+                     void *r, size_t rst, hipStream_t st) {
     dim3 grid(unit_parts(prec, g), s.B);
     if (prec == 0)
-        hipLaunchKernelGGL(k_reliable<double>, grid, dim3(kBlock), 0, st, g, s, src, ap64, (double2 *)r, rst);
+        hipLaunchKernelGGL(k_reliable<double>, grid, dim3(kBlock), 0, st, g, s, src, ap64, ast, (double2 *)r, rst);
     else
-        hipLaunchKernelGGL(k_reliable<float>, grid, dim3(kBlock), 0, st, g, s, src, ap64, (float4 *)r, rst);
+        hipLaunchKernelGGL(k_reliable<float>, grid, dim3(kBlock), 0, st, g, s, src, ap64, ast, (float4 *)r, rst);
 }
 
 __global__ void k_scalars_rr(MSState S, int npart) {

@@ -25,10 +25,11 @@ KAPPA = 0.21
 
 def _slot_bytes(prec, ns, k, volume):
     """Device bytes per right-hand side: k residuals, tmp, the directions (one more with k > 1) and
-    y; mixed: those in FP32, y, x0 and two reliable-update vectors in FP64."""
+    y; mixed: those in FP32, y, x0 and, unless the ring holds them, two reliable-update vectors in
+    FP64."""
     v64 = 192 * (-(-volume // 256) * 256)
     n = k + 1 + ns + (k > 1)
-    return (n + 1) * v64 if prec == smpq.SMPQ_FP64 else n * v64 // 2 + 4 * v64
+    return (n + 1) * v64 if prec == smpq.SMPQ_FP64 else n * v64 // 2 + (2 if k >= 5 else 4) * v64
 
 
 @pytest.mark.parametrize("poles", [3, 14, 32])   # registers for up to 8, 14 and 32 directions
