@@ -1035,38 +1035,37 @@ void ensure_point_device(smpq_ctx *c) {
     HIPCHK(hipMemcpy(c->d_pptr.p, id.data(), sizeof(int) * (c->V + 1), hipMemcpyHostToDevice));
 }
 
-// Extreme Ritz values of H^2 after `steps` steps.  alpha_j and beta_j stay on the device, summed by
-// the kernels that use them, and are read once at the end: waiting for two sums in every step
-// took 64 us a step on 8^3 x 16, the four kernels take a third of that.
+// Extreme Ritz values of H^2 after `steps` steps.  alpha_j and the vectors' norms, the beta_j, stay on
+// the device, summed by the kernel that uses them, and are read once at the end: waiting for two
+// sums in every step took 64 us a step on 8^3 x 16, the three kernels take 26 us.
 void lanczos(smpq_ctx *c, int steps, uint64_t seed, double *tmin, double *tmax) {
     const Geom g = c->geom();
     const size_t v64 = 12 * 16 * c->vs;
     c->lz.ensure(4 * v64);
-    double2 *v = c->lz.as<double2>(), *vp = v + 12 * c->vs, *w = vp + 12 * c->vs, *t = w + 12 * c->vs;
-    const int np_ds = dslash_partials(0, g, true), np_w = site_blocks(g);
+    double2 *u = c->lz.as<double2>(), *up = u + 12 * c->vs, *w = up + 12 * c->vs, *t = w + 12 * c->vs;
+    const int np_ds = dslash_partials(0, g, true), np_u = site_blocks(g);
     DevMem part, ab;
-    part.ensure(sizeof(double) * 2 * partial_stride(g));
+    part.ensure(sizeof(double) * 3 * partial_stride(g));
     ab.ensure(sizeof(double) * 2 * steps);
-    double *pd = part.as<double>(), *pw = pd + partial_stride(g);
-    double *da = ab.as<double>(), *db = da + steps;
-    launch_random_start(g, seed, w, pw, c->stream);
-    launch_lanczos_scale(g, v, w, pw, np_w, nullptr, c->stream);
+    double *pd = part.as<double>(), *pu = pd + partial_stride(g), *pw = pu + partial_stride(g);
+    double *da = ab.as<double>(), *dn = da + steps;
+    launch_random_start(g, seed, u, pu, c->stream);
     Slots one{nullptr, nullptr, 1};
     for (int j = 0; j < steps; ++j) {
-        launch_dslash(0, false, 0, c->U64.p, v, 0, 0, t, 0, nullptr, 0, 0, g, c->kappa, 0.0, one, 1, nullptr,
+        launch_dslash(0, false, 0, c->U64.p, u, 0, 0, t, 0, nullptr, 0, 0, g, c->kappa, 0.0, one, 1, nullptr,
                       c->stream);
-        launch_dslash(0, true, 1, c->U64.p, t, 0, 0, w, 0, v, 0, 0, g, c->kappa, 0.0, one, 1, pd, c->stream);
-        launch_lanczos_step(g, w, v, j > 0 ? vp : nullptr, pd, np_ds, da + j, j > 0 ? db + j - 1 : nullptr, pw,
-                            c->stream);
-        if (j == steps - 1) break;
-        launch_lanczos_scale(g, vp, w, pw, np_w, db + j, c->stream);
-        std::swap(v, vp);
+        launch_dslash(0, true, 1, c->U64.p, t, 0, 0, w, 0, u, 0, 0, g, c->kappa, 0.0, one, 1, pd, c->stream);
+        launch_lanczos_step(g, w, u, j > 0 ? up : nullptr, pd, np_ds, pu, np_u, da + j, dn + j, pw, c->stream);
+        std::swap(up, u);
+        std::swap(u, w);
+        std::swap(pu, pw);
     }
     HIPCHK(hipGetLastError());
     std::vector<double> alpha(steps), beta(steps);
     HIPCHK(hipMemcpyAsync(alpha.data(), da, sizeof(double) * steps, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipMemcpyAsync(beta.data(), db, sizeof(double) * steps, hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipMemcpyAsync(beta.data(), dn, sizeof(double) * steps, hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    beta.erase(beta.begin());   // |u_0| is the start's; |u_j| is beta_{j-1}
     int taken = 1;   // an invariant subspace ends the process: what follows is not used
     while (taken < steps && beta[taken - 1] > 0.0 && std::isfinite(beta[taken - 1])) ++taken;
     alpha.resize(taken);
@@ -1085,7 +1084,7 @@ void lanczos_full(smpq_ctx *c, int steps, uint64_t seed, double2 *Qp, DevMem &w,
     hipStream_t s = c->stream;
     double2 *wp = w.as<double2>();
     launch_random_start(g, seed, wp, part.as<double>(), s);
-    launch_lanczos_scale(g, Qp, wp, part.as<double>(), site_blocks(g), nullptr, s);
+    launch_lanczos_scale(g, Qp, wp, part.as<double>(), site_blocks(g), s);
     double2 hw[1];
     alpha.clear();
     beta.clear();

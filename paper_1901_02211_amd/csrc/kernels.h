@@ -223,13 +223,15 @@ void launch_contract(const Geom &g, const double2 *U64, const double2 *y, double
 void launch_lanczos_update(const Geom &g, double2 *w, const double2 *v, const double2 *vprev, double alpha,
                            double beta, double *partial, hipStream_t st);
 // Lanczos on one vector with its scalars on the device: random_start: the SplitMix64 vector of
-// `seed`, unnormalised, and site_blocks partials of its |.|^2; step: alpha = sum of the np
-// dot_partials, w -= alpha v + *beta_in vprev (vprev null in the first step), site_blocks partials
-// of |w|^2; scale: beta = sqrt(sum of the np partials), v = w / beta, *beta_out = beta (nullable).
+// `seed`, unnormalised, and site_blocks partials of its |.|^2; step: n = *norm = |u| from its np_u
+// norm_partials, *alpha_out = (sum of the np dot_partials) / n^2, w = (w - alpha u) / n -
+// (n / norm[-1]) uprev (uprev null in the first step), site_blocks partials of |w|^2;
+// scale: v = w / |w|, |w| from its np partials.
 void launch_random_start(const Geom &g, uint64_t seed, double2 *w, double *partial, hipStream_t st);
-void launch_lanczos_step(const Geom &g, double2 *w, const double2 *v, const double2 *vprev, const double *dot_partials,
-                         int np, double *alpha_out, const double *beta_in, double *partial, hipStream_t st);
-void launch_lanczos_scale(const Geom &g, double2 *v, const double2 *w, const double *partials, int np, double *beta_out,
+void launch_lanczos_step(const Geom &g, double2 *w, const double2 *u, const double2 *uprev, const double *dot_partials,
+                         int np, const double *norm_partials, int np_u, double *alpha_out, double *norm,
+                         double *partial, hipStream_t st);
+void launch_lanczos_scale(const Geom &g, double2 *v, const double2 *w, const double *partials, int np,
                           hipStream_t st);
 void launch_scale(const Geom &g, double2 *dst, const double2 *src, double f, hipStream_t st);
 // dst = src over n float4 with cached (nontemporal = false) or non-temporal loads and stores:

@@ -2344,22 +2344,31 @@ void launch_random_start(const Geom &g, uint64_t seed, double2 *w, double *parti
     hipLaunchKernelGGL(k_random_start, dim3(site_blocks(g)), dim3(kBlock), 0, st, g, seed, w, partial);
 }
 
-// alpha = <v, w> from the stencil's partials; w -= alpha v + beta vprev; partial |w|^2.
-__global__ __launch_bounds__(kBlock) void k_lanczos_step(Geom g, double2 *w, const double2 *v, const double2 *vprev,
-                                                         const double *dot_partials, int np, double *alpha_out,
-                                                         const double *beta_in, double *partial) {
+// One Lanczos step on vectors kept unnormalised: n = |u| from its partials (the last step's beta),
+// alpha = <u, w> / n^2 from the stencil's, w = (w - alpha u) / n - (n / n_prev) u_prev, and w's
+// partial |w|^2.  Dividing here instead of in a kernel of its own leaves three launches a step; on
+// one right-hand side each is bound by its latency, 8 us on 8^3 x 16 (bounds there 9.4 -> 7.9 ms).
+__global__ __launch_bounds__(kBlock) void k_lanczos_step(Geom g, double2 *w, const double2 *u, const double2 *uprev,
+                                                         const double *dot_partials, int np,
+                                                         const double *norm_partials, int np_u, double *alpha_out,
+                                                         double *norm, double *partial) {
     const int s = blockIdx.x * kBlock + threadIdx.x;
-    const double a = wave_sum_partials(dot_partials, np);
-    const double b = vprev ? *beta_in : 0.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *alpha_out = a;
+    const double n2 = wave_sum_partials(norm_partials, np_u);
+    const double n = sqrt(n2), inv = 1.0 / n;
+    const double a = wave_sum_partials(dot_partials, np) / n2;
+    const double b = uprev ? n / norm[-1] : 0.0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *alpha_out = a;
+        *norm = n;
+    }
     double nrm = 0.0;
     if (s < g.V) {
 #pragma unroll
         for (int c = 0; c < 12; ++c) {
             cpx<double> t = ld64(w, g.vs, c, s);
-            const cpx<double> x = ld64(v, g.vs, c, s);
-            t = t - a * x;
-            if (vprev) t = t - b * ld64(vprev, g.vs, c, s);
+            const cpx<double> x = ld64(u, g.vs, c, s);
+            t = inv * (t - a * x);
+            if (uprev) t = t - b * ld64(uprev, g.vs, c, s);
             st64(w, g.vs, c, s, t);
             nrm += t.re * t.re + t.im * t.im;
         }
@@ -2367,28 +2376,28 @@ __global__ __launch_bounds__(kBlock) void k_lanczos_step(Geom g, double2 *w, con
     block_partial(nrm, partial, blockIdx.x);
 }
 
-void launch_lanczos_step(const Geom &g, double2 *w, const double2 *v, const double2 *vprev, const double *dot_partials,
-                         int np, double *alpha_out, const double *beta_in, double *partial, hipStream_t st) {
-    hipLaunchKernelGGL(k_lanczos_step, dim3(site_blocks(g)), dim3(kBlock), 0, st, g, w, v, vprev, dot_partials, np,
-                       alpha_out, beta_in, partial);
+void launch_lanczos_step(const Geom &g, double2 *w, const double2 *u, const double2 *uprev, const double *dot_partials,
+                         int np, const double *norm_partials, int np_u, double *alpha_out, double *norm,
+                         double *partial, hipStream_t st) {
+    hipLaunchKernelGGL(k_lanczos_step, dim3(site_blocks(g)), dim3(kBlock), 0, st, g, w, u, uprev, dot_partials, np,
+                       norm_partials, np_u, alpha_out, norm, partial);
 }
 
-// beta = |w| from its np partials; v = w / beta.
+// v = w / |w|, |w| from its np partials.
 __global__ __launch_bounds__(kBlock) void k_lanczos_scale(Geom g, double2 *v, const double2 *w,
-                                                          const double *partials, int np, double *beta_out) {
+                                                          const double *partials, int np) {
     const int nsb = site_blocks(g);
     const int c = blockIdx.x / nsb;
     const int s = (blockIdx.x % nsb) * kBlock + threadIdx.x;
     const double beta = sqrt(wave_sum_partials(partials, np));
-    if (beta_out && blockIdx.x == 0 && threadIdx.x == 0) *beta_out = beta;
     if (s >= g.V) return;
     const cpx<double> t = ld64(w, g.vs, c, s);
     st64(v, g.vs, c, s, (1.0 / beta) * t);
 }
 
-void launch_lanczos_scale(const Geom &g, double2 *v, const double2 *w, const double *partials, int np, double *beta_out,
+void launch_lanczos_scale(const Geom &g, double2 *v, const double2 *w, const double *partials, int np,
                           hipStream_t st) {
-    hipLaunchKernelGGL(k_lanczos_scale, dim3(unit_parts(0, g)), dim3(kBlock), 0, st, g, v, w, partials, np, beta_out);
+    hipLaunchKernelGGL(k_lanczos_scale, dim3(unit_parts(0, g)), dim3(kBlock), 0, st, g, v, w, partials, np);
 }
 
 __global__ __launch_bounds__(kBlock) void k_scale(Geom g, double2 *dst, const double2 *src, double f) {
