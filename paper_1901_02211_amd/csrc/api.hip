@@ -509,10 +509,10 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
     const size_t limit = c->run_limit > 0 ? c->run_limit : c->mem_limit;
     const double budget = limit > 0 ? (double)limit : 0.80 * (double)(freeb + held);
     const int q = multiple_of_12 ? 12 : 1;
-    // without a limit, the batch that the workspace was laid out for stays possible however little
-    // other contexts have left
+    // within a limit, the batch that the workspace was laid out for stays possible however little other
+    // contexts have left
     const Workspace &w = c->ws;
-    const bool reuse = limit == 0 && w.S.rr && w.prec == prec && w.NS == NS && w.check == c->shift_check;
+    const bool reuse = (limit == 0 || held <= limit) && w.S.rr && w.prec == prec && w.NS == NS && w.check == c->shift_check;
     auto most = [&](int K, size_t extra = 0) {
         long long B = (long long)(budget / (double)(bytes_per_slot(c, prec, NS, K) + extra));
         if (reuse && K == w.K && extra == 0) B = std::max<long long>(B, w.B);
@@ -538,6 +538,10 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
                 break;
             }
         }
+    // A workspace with room for every source and a block of 10 or more is kept as it is: laying out
+    // one that takes most of the device costs 5 s, more than the longer block saves a small call.
+    const long long all = c->max_rhs > 0 ? std::min(c->max_rhs, total_slots) : total_slots;
+    if (reuse && w.K >= kGroup && w.B >= all) K = w.K;
     const long long B = most(K);
     if (B < q) throw Fail{SMPQ_ENOMEM, "not enough device memory for one batch of right-hand sides"};
     // spread the right-hand sides evenly over the batches this limit implies

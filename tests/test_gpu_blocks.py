@@ -157,3 +157,23 @@ def test_small_lattices_equal_separate_kernels(dims, inexact):
     assert e.value.status == -5
     smpq.smpq_set_solver(c, 1, 1e-12, 5000, 30)
     assert np.array_equal(smpq.smpq_apply_dov(c, psi), out[0][1])
+
+
+@pytest.mark.parametrize("prec", [smpq.SMPQ_FP64, smpq.SMPQ_MIXED_FP32])
+def test_prepared_workspace_serves_smaller_calls(prec):
+    """A call with fewer sources between two whole maps changes neither their values nor their batches."""
+    dims = (4, 4, 4, 6)
+    print(f"small call between maps, precision {prec}", flush=True)
+    c = smpq.smpq_create(dims, 0)
+    smpq.smpq_load_gauge(c, si.near_identity_su3(dims, 0.3, 7))
+    smpq.smpq_set_zolotarev(c, 14, 0.13, 2.7)
+    smpq.smpq_set_scheme(c, (2, 2, 2, 2), 0)
+    smpq.smpq_set_solver(c, prec, 1e-12, 5000, 50)
+    for limit in (0, 96 * _slot_bytes(prec, 14, 10, 384)):
+        smpq.smpq_set_memory_limit(c, limit)
+        q, qi, Q, st = smpq.smpq_compute_qx(c)
+        one = smpq.smpq_compute_qx_classes(c, [5])
+        q2, qi2, Q2, st2 = smpq.smpq_compute_qx(c)
+        assert np.array_equal(q, q2) and np.array_equal(qi, qi2) and st["n_batches"] == st2["n_batches"]
+        mask = smpq.smpq_get_coloring(c) == 5
+        assert np.array_equal(one[0][mask], q[mask])
