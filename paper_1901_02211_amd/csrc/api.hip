@@ -253,6 +253,17 @@ void need_device(smpq_ctx *c) {
     HIPCHK(hipSetDevice(c->device));
 }
 
+// Copies between host and device run on the context's stream.  A blocking hipMemcpy runs on the legacy
+// stream, which the runtime refuses while another context captures its graphs, ending that capture too.
+void to_device(smpq_ctx *c, void *dst, const void *src, size_t bytes) {   // returns when src is free
+    HIPCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+}
+template <class T>
+void read_back(smpq_ctx *c, std::vector<T> &dst, const T *src) {   // dst holds it after a synchronisation
+    HIPCHK(hipMemcpyAsync(dst.data(), src, sizeof(T) * dst.size(), hipMemcpyDeviceToHost, c->stream));
+}
+
 template <class F>
 smpq_status guarded(smpq_ctx *c, F &&f) {
     if (!c) return SMPQ_EINVAL;
@@ -580,8 +591,8 @@ void upload_zolo(smpq_ctx *c) {
     for (int i = 0; i < n; ++i) dl[i] = c->zolo.q[i] - c->zolo.q[0];
     c->zc.ensure(sizeof(double) * n);
     c->zdelta.ensure(sizeof(double) * n);
-    HIPCHK(hipMemcpy(c->zc.p, c->zolo.c.data(), sizeof(double) * n, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(c->zdelta.p, dl.data(), sizeof(double) * n, hipMemcpyHostToDevice));
+    to_device(c, c->zc.p, c->zolo.c.data(), sizeof(double) * n);
+    to_device(c, c->zdelta.p, dl.data(), sizeof(double) * n);
     c->coef_eps = smpq_ctx::Coef{n, c->zolo.c0, c->zolo.q[0], c->zc.as<double>(), c->zdelta.as<double>()};
 }
 
@@ -590,7 +601,7 @@ void use_coef(smpq_ctx *c, bool inverse) {
     if (inverse && !c->inv_cd.p) {
         const double cd[2] = {1.0, 0.0};
         c->inv_cd.ensure(sizeof(cd));
-        HIPCHK(hipMemcpy(c->inv_cd.p, cd, sizeof(cd), hipMemcpyHostToDevice));
+        to_device(c, c->inv_cd.p, cd, sizeof(cd));
         c->coef_inv = smpq_ctx::Coef{1, 0.0, 0.0, c->inv_cd.as<double>(), c->inv_cd.as<double>() + 1};
     }
     c->coef = inverse ? &c->coef_inv : &c->coef_eps;
@@ -870,13 +881,14 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     c->cur_xs = nullptr;
     std::vector<int> status(nslots), iters(nslots);
     std::vector<long long> ent(nslots), actv(nslots), fl(nslots), flr(nslots), flp(nslots);
-    HIPCHK(hipMemcpy(status.data(), S.status, sizeof(int) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(iters.data(), S.iters, sizeof(int) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(ent.data(), S.cnt_entries, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(actv.data(), S.cnt_active, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(fl.data(), S.cnt_fl, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(flr.data(), S.cnt_fl_r, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(flp.data(), S.cnt_fl_p, sizeof(long long) * nslots, hipMemcpyDeviceToHost));
+    read_back(c, status, S.status);
+    read_back(c, iters, S.iters);
+    read_back(c, ent, S.cnt_entries);
+    read_back(c, actv, S.cnt_active);
+    read_back(c, fl, S.cnt_fl);
+    read_back(c, flr, S.cnt_fl_r);
+    read_back(c, flp, S.cnt_fl_p);
+    HIPCHK(hipStreamSynchronize(s));
     long long blocks = 0, ring_reads = 0, dir_moves = 0;
     for (int k = 0; k < nslots; ++k) {
         if (status[k] != kStatusOK) throw Fail{SMPQ_ENUMERIC, "CG breakdown: <p, A p> <= 0 or not finite"};
@@ -935,7 +947,7 @@ void check_shifts(smpq_ctx *c, int prec, int nslots, const Source &src, smpq_sta
     if (!c->inv_cd.p) {
         const double cd[2] = {1.0, 0.0};
         c->inv_cd.ensure(sizeof(cd));
-        HIPCHK(hipMemcpy(c->inv_cd.p, cd, sizeof(cd), hipMemcpyHostToDevice));
+        to_device(c, c->inv_cd.p, cd, sizeof(cd));
     }
     std::vector<double> ch(NS), dh(NS), bn(nslots);
     HIPCHK(hipMemcpyAsync(ch.data(), coef.c, sizeof(double) * NS, hipMemcpyDeviceToHost, s));
@@ -1024,9 +1036,9 @@ void ensure_scheme_device(smpq_ctx *c) {
     c->d_colour.ensure(sizeof(int) * c->V);
     c->d_cptr.ensure(sizeof(int) * (c->n_classes + 1));
     c->d_csites.ensure(sizeof(int) * c->V);
-    HIPCHK(hipMemcpy(c->d_colour.p, c->colour.data(), sizeof(int) * c->V, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(c->d_cptr.p, c->cptr.data(), sizeof(int) * (c->n_classes + 1), hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(c->d_csites.p, c->csites.data(), sizeof(int) * c->V, hipMemcpyHostToDevice));
+    to_device(c, c->d_colour.p, c->colour.data(), sizeof(int) * c->V);
+    to_device(c, c->d_cptr.p, c->cptr.data(), sizeof(int) * (c->n_classes + 1));
+    to_device(c, c->d_csites.p, c->csites.data(), sizeof(int) * c->V);
 }
 
 void ensure_point_device(smpq_ctx *c) {
@@ -1035,8 +1047,8 @@ void ensure_point_device(smpq_ctx *c) {
     for (int i = 0; i <= c->V; ++i) id[i] = i;
     c->d_pcolour.ensure(sizeof(int) * c->V);
     c->d_pptr.ensure(sizeof(int) * (c->V + 1));
-    HIPCHK(hipMemcpy(c->d_pcolour.p, id.data(), sizeof(int) * c->V, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(c->d_pptr.p, id.data(), sizeof(int) * (c->V + 1), hipMemcpyHostToDevice));
+    to_device(c, c->d_pcolour.p, id.data(), sizeof(int) * c->V);
+    to_device(c, c->d_pptr.p, id.data(), sizeof(int) * (c->V + 1));
 }
 
 // Extreme Ritz values of H^2 after `steps` steps.  alpha_j and the vectors' norms, the beta_j, stay on
@@ -1351,8 +1363,9 @@ void prepare_q(smpq_ctx *c, smpq_stats *st) {
 void finish_q(smpq_ctx *c, double *qx, double *qxi, smpq_stats *st) {
     const double t0 = now_s();
     std::vector<double> hi(c->V);
-    HIPCHK(hipMemcpy(qx, c->qx.p, sizeof(double) * c->V, hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(hi.data(), c->qxi.p, sizeof(double) * c->V, hipMemcpyDeviceToHost));
+    HIPCHK(hipMemcpyAsync(qx, c->qx.p, sizeof(double) * c->V, hipMemcpyDeviceToHost, c->stream));
+    read_back(c, hi, c->qxi.as<const double>());
+    HIPCHK(hipStreamSynchronize(c->stream));
     if (qxi) std::memcpy(qxi, hi.data(), sizeof(double) * c->V);
     if (st) {
         double sum = 0.0, mx = 0.0;
@@ -1639,8 +1652,8 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
                 }
         c->U64.ensure(sizeof(double) * V * 72);
         c->U32.ensure(sizeof(float) * V * 48);
-        HIPCHK(hipMemcpy(c->U64.p, u64.data(), sizeof(double) * V * 72, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(c->U32.p, u32.data(), sizeof(float) * V * 48, hipMemcpyHostToDevice));
+        to_device(c, c->U64.p, u64.data(), sizeof(double) * V * 72);
+        to_device(c, c->U32.p, u32.data(), sizeof(float) * V * 48);
         uint64_t h = 0xcbf29ce484222325ull;   // FNV-1a, 64 bit
         const unsigned char *bytes = reinterpret_cast<const unsigned char *>(U);
         for (size_t i = 0; i < n * sizeof(double); ++i) h = (h ^ bytes[i]) * 0x100000001b3ull;
