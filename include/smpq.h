@@ -409,7 +409,7 @@ smpq_status smpq_bench_stream(smpq_ctx *ctx, size_t bytes, int launches, int non
  * (nx <= 64; f32_nr = 4, 8 or 16); 3 = kind 1 with the plane's x and y links in LDS instead
  * of registers, at 3 waves per SIMD; 4 = kind 2's tiles with the links read for every
  * right-hand side, or every two where there are more than one, instead of held in registers
- * (f32_nr = 1, 2, 4 or 8; 3-4 waves per SIMD), the tile without halo rows when it is the whole plane.  plane_band (kinds 1-4; 1, 2 or 4, dividing nz): the
+ * (f32_nr = 1, 2, 4 or 8; 3-4 waves per SIMD), the tile without halo rows when it is the whole plane.  plane_band (kinds 1-4; 1, 2 or 4, dividing nz; kind 0 ignores it): the
  * blocks take the (z, t) planes in bands of that many z with t running inside a band, so the
  * +-t neighbours of a plane were read shortly before (1 = z fastest).  FP64 stencil:
  * f64_kind 0 is the FP32 kind 0 with 2^f64_lgr = 1, 2 or 4 right-hand sides per block in turn;

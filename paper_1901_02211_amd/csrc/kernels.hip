@@ -31,6 +31,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "tiles.h"
 #include "wilson_site.h"
 
 namespace smpq {
@@ -151,15 +152,6 @@ __device__ __forceinline__ void load_link<float>(const float4 *U, int V, int mu,
 __device__ __forceinline__ int xcd_swizzle(int b, int nb) {
     const int q = nb >> 3, r = nb & 7, xcd = b & 7, k = b >> 3;
     return xcd * q + (xcd < r ? xcd : r) + k;
-}
-
-// Plane p of the block order -> (z, t) plane index z + nz t.  The planes are taken in bands of
-// g.band consecutive z: t runs over the whole extent inside a band, so that the +-t
-// neighbours of a plane were staged g.band blocks earlier (still in L2) rather than nz.
-__device__ __forceinline__ int plane_order(int p, const Geom &g) {
-    if (g.band == 1) return p;
-    const int per = g.band * g.nt, b = p / per, i = p % per;
-    return b * g.band + i % g.band + g.nz * (i / g.band);
 }
 
 // Neighbours of site s = (x, y) of the (z, t) plane pl = z + nz t without per-thread integer
@@ -606,23 +598,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 // row is further than rounding from that.
 enum { kTileExact, kTileAny, kTileNone };
 
-// Rows ty of one plane and planes m of a kTileAny block (ty = ny where m > 1); ty = 0: kTileNone.
-__host__ __device__ __forceinline__ void any_tile(const Geom &g, int &ty, int &m) {
-    const int nxy = g.nx * g.ny, planes = g.nz * g.nt;
-    m = 1;
-    if (nxy <= kBlock) {
-        ty = g.ny;
-        m = kBlock / nxy < planes ? kBlock / nxy : planes;
-    } else if (g.nx <= kBlock / 2) {
-        int tiles = (nxy + kBlock - 1) / kBlock;
-        while ((g.ny + tiles - 1) / tiles * g.nx > kBlock) ++tiles;
-        ty = (g.ny + tiles - 1) / tiles;
-        if (ty < 2) ty = 0;
-    } else {
-        ty = 0;
-    }
-}
-
 // u's third row from its first two
 __device__ __forceinline__ void third_row(cpx<double> u[9]) {
     const cpx<double> r0 = cfma(u[1], u[5], -1.0 * cmul(u[2], u[4]));
@@ -725,26 +700,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(RlWaves<
         const bool whole = ty == ny;             // whole planes: y wraps inside the tile
         const int rows = whole ? ty : ty + 2;    // rows of a plane held in LDS
         tsites = m * rows * nx;
-        int pl, y0 = 0, here = ty, i = threadIdx.x, mi = 0;
-        if (TILE == kTileAny && m > 1) {
-            mi = i / (nx * ny);
-            pl = sb * m + mi;
-            site_ok = mi < m && pl < g.nz * g.nt;
-            i -= mi * nx * ny;
+        int pl, y0, here = ty, i = threadIdx.x, mi = 0;
+        if constexpr (TILE == kTileAny) {
+            const AnySite a = any_site(g, ty, m, sb, threadIdx.x);
+            pl = a.pl;
+            y0 = a.y0;
+            here = a.here;
+            i = a.i;
+            mi = a.mi;
+            site_ok = a.ok;              // idle: the tile's first site, nothing stored
         } else {
-            const int tiles_per_plane = TILE == kTileAny ? (ny + ty - 1) / ty : ny / ty;
+            const int tiles_per_plane = ny / ty;
             pl = plane_order(sb / tiles_per_plane, g);
             y0 = (sb % tiles_per_plane) * ty;
-            if constexpr (TILE == kTileAny) {
-                here = min(ty, ny - y0);
-                site_ok = i < nx * here;
-            }
         }
         const bool halo_thread = !whole && (int)threadIdx.x < 2 * nx;
-        if (TILE == kTileAny && !site_ok) {      // idle: the tile's first site, nothing stored
-            i = mi = 0;
-            pl = m > 1 ? sb * m : pl;
-        }
         const int x = i % nx, yl = i / nx;
         const int plane0 = pl * nx * ny;
         s = plane0 + (y0 + yl) * nx + x;
@@ -924,15 +894,6 @@ int tile_rows(int nx, int ny) {
 }
 
 static int tile_blocks(const Geom &g) { return g.V / (g.nx * g.tile_y); }
-
-// Blocks of kind 0.
-static int any_blocks(const Geom &g) {
-    int ty, m;
-    any_tile(g, ty, m);
-    if (ty == 0) return site_blocks(g);
-    const int planes = g.nz * g.nt;
-    return m > 1 ? (planes + m - 1) / m : planes * ((g.ny + ty - 1) / ty);
-}
 
 // g with the FP32 variant of one direction in f32_kind, f32_nr and f32_il
 static Geom for_direction(const Geom &g, int prec, bool dag) {
@@ -1648,15 +1609,9 @@ __global__ __launch_bounds__(MAXT) void k_cg_small(const typename Store<T>::link
     } else {
         int ty, m;
         any_tile(g, ty, m);
-        if (m > 1) {
-            s = sb * m * g.nx * g.ny + i;
-            ok_site = i < m * g.nx * g.ny && s < g.V;
-        } else {
-            const int tiles_per_plane = (g.ny + ty - 1) / ty, y0 = (sb % tiles_per_plane) * ty;
-            s = plane_order(sb / tiles_per_plane, g) * g.nx * g.ny + y0 * g.nx + i;
-            ok_site = i < min(ty, g.ny - y0) * g.nx;
-        }
-        if (!ok_site) s = 0;   // idle: computes site 0, stores nothing, adds nothing
+        const AnySite a = any_site(g, ty, m, sb, i);   // idle: computes a site, stores and adds nothing
+        s = (a.pl * g.ny + a.y0) * g.nx + a.i;
+        ok_site = a.ok;
     }
     const Nbr nb = neighbours(s, g.nx, g.ny, g.nz, g.nt);
     const size_t rs = UN * g.vs;
