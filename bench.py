@@ -64,15 +64,11 @@ DIR_STORAGE = {"fp32": ("SMPQ_MIXED_FP32", ""),
 
 
 def kernel_source_hash():
-    """Hash of the device code (kernels.hip and the headers it shares with host checks, without
-    comments and blank lines), so that profiles/traffic.json is used only for the kernels it was
-    measured on."""
+    """Hash of the device code (kernels.hip and wilson_site.h without comments and blank
+    lines), so that profiles/traffic.json is used only for the kernels it was measured on."""
     h = hashlib.sha256()
-    for f in ("kernels.hip", "wilson_site.h", "tiles.h"):
-        path = os.path.join(ROOT, "paper_1901_02211_amd", "csrc", f)
-        if not os.path.exists(path):
-            continue
-        with open(path) as fh:
+    for f in ("kernels.hip", "wilson_site.h"):
+        with open(os.path.join(ROOT, "paper_1901_02211_amd", "csrc", f)) as fh:
             for line in fh:
                 code = line.split("//", 1)[0].rstrip()
                 if code:
