@@ -31,7 +31,6 @@
 #include <type_traits>
 
 #include "kernels.h"
-#include "tiles.h"
 #include "wilson_site.h"
 
 namespace smpq {

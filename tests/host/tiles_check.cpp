@@ -1,9 +1,9 @@
-// Host-side checks of paper_1901_02211_amd/csrc/tiles.h, built by tests/test_tiles_host.py: the blocks of the
+// Host-side checks of paper_1901_02211_amd/csrc/wilson_site.h, built by tests/test_tiles_host.py: the blocks of the
 // stencils cover every site of a lattice once.  Exit status 0 = all pass.
 #include <cstdio>
 #include <vector>
 
-#include "../../paper_1901_02211_amd/csrc/tiles.h"
+#include "../../paper_1901_02211_amd/csrc/wilson_site.h"
 
 static int failures = 0;
 

@@ -1,4 +1,4 @@
-"""The block-to-site rules of the stencils (csrc/tiles.h), built for the host with g++ and checked over plane
+"""The block-to-site rules of the stencils (csrc/wilson_site.h), built for the host with g++ and checked over plane
 shapes and bands (tests/host/tiles_check.cpp)."""
 import os
 import shutil
