@@ -388,10 +388,16 @@ size_t bytes_per_slot(const smpq_ctx *c, int prec, int NS, int K) {
            check;
 }
 
-void release_vectors(Workspace &w) {
+// Free the right-hand-side vectors of the workspace (the next ensure_workspace lays it out again).
+void release_workspace(smpq_ctx *c) {
+    Workspace &w = c->ws;
     w.r.release(); w.tmp.release(); w.p.release(); w.ph.release(); w.y.release();
     w.x0.release(); w.tmp64.release(); w.ap64.release();
     w.xs.release(); w.rres.release(); w.ysave.release();
+    w.prec = -1;
+    w.B = 0;
+    w.S.rr = nullptr;
+    c->gen++;
 }
 
 // Device workspace for at least B right-hand sides of the given precision and shift count.
@@ -403,13 +409,15 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     const size_t v64 = 12 * 16 * c->vs, v32 = 6 * 16 * c->vs;
     const size_t vt = prec == 0 ? v64 : v32;
     if (w.prec == prec && w.NS == NS && w.K == K && w.B >= B && w.check == c->shift_check && w.S.rr) return;
-    c->gen++;
-    release_vectors(w);
-    w.prec = prec;
-    w.NS = NS;
-    w.B = B;
-    w.K = K;
-    w.check = c->shift_check;
+    release_workspace(c);
+    // the layout is valid once everything is allocated; an allocation that fails gives back the others
+    struct Undo {
+        smpq_ctx *c;
+        ~Undo() {
+            if (c) release_workspace(c);
+        }
+    } undo{c};
+    const bool check = c->shift_check;
     w.r.ensure(vt * B * K);
     w.tmp.ensure(vt * B);
     w.p.ensure(vt * B * dir_entries(prec, NS, K));
@@ -417,12 +425,12 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     w.y.ensure(v64 * B);
     if (prec >= 1) {
         w.x0.ensure(v64 * B);
-        if (!ring_scratch(prec, K, w.check)) {
+        if (!ring_scratch(prec, K, check)) {
             w.tmp64.ensure(v64 * B);
             w.ap64.ensure(v64 * B);
         }
     }
-    if (w.check) {
+    if (check) {
         w.xs.ensure(v64 * B * NS);
         w.rres.ensure(v64 * B);
         w.ysave.ensure(v64 * B);
@@ -443,6 +451,12 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     w.slot_class.ensure(sizeof(int) * B);
     w.slot_comp.ensure(sizeof(int) * B);
     w.batch_classes.ensure(sizeof(int) * (B / 12 + 1));
+    w.prec = prec;
+    w.NS = NS;
+    w.B = B;
+    w.K = K;
+    w.check = check;
+    undo.c = nullptr;
     MSState &S = w.S;
     double *d = w.st_d.as<double>();
     auto dbl = [&d](size_t n) { double *q = d; d += n; return q; };
@@ -489,16 +503,6 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     S.NS = NS;
     S.B = B;
     S.K = K;
-}
-
-// Free the right-hand-side vectors of the workspace (the next ensure_workspace lays it out again).
-void release_workspace(smpq_ctx *c) {
-    Workspace &w = c->ws;
-    release_vectors(w);
-    w.prec = -1;
-    w.B = 0;
-    w.S.rr = nullptr;
-    c->gen++;
 }
 
 size_t workspace_bytes(const smpq_ctx *c) {

@@ -1,0 +1,40 @@
+"""GPU: the workspace of a context when memory runs short or its options change."""
+import numpy as np
+import pytest
+
+import smpq_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+import paper_1901_02211_amd as smpq  # noqa: E402
+
+DIMS = (8, 8, 8, 8)
+
+
+def _ctx(prec=0, dims=DIMS):
+    c = smpq.smpq_create(dims, 0)
+    smpq.smpq_load_gauge(c, si.near_identity_su3(dims, 0.3, 7))
+    smpq.smpq_set_zolotarev(c, 14, 0.15, 2.75)
+    smpq.smpq_set_scheme(c, (2, 2, 2, 2), 0)
+    smpq.smpq_set_solver(c, prec, 1e-12, 5000, 50)
+    return c
+
+
+@pytest.mark.parametrize("prec,limit", [(0, 4 << 40),      # the first vector does not fit the device
+                                        (0, 380 << 30),    # the ring does (200 GB), the directions do not
+                                        (1, 4 << 40)])
+def test_failed_layout_is_not_kept(prec, limit):
+    """A workspace larger than the device: every attempt is refused, and the context then works on."""
+    print(f"layout beyond the device, precision {prec}, limit {limit >> 30} GiB", flush=True)
+    c = _ctx(prec)
+    want = smpq.smpq_compute_qx_classes(c, [3])
+    smpq.smpq_set_point_scheme(c)                 # 49152 right-hand sides
+    smpq.smpq_set_memory_limit(c, limit)
+    for _ in range(2):
+        with pytest.raises(smpq.SmpqError) as e:
+            smpq.smpq_prepare(c)
+        assert e.value.status == -3
+    smpq.smpq_set_memory_limit(c, 0)
+    smpq.smpq_set_scheme(c, (2, 2, 2, 2), 0)
+    got = smpq.smpq_compute_qx_classes(c, [3])
+    assert np.array_equal(want[0], got[0]) and np.array_equal(want[1], got[1])
