@@ -600,14 +600,18 @@ void upload_zolo(smpq_ctx *c) {
     c->coef_eps = smpq_ctx::Coef{n, c->zolo.c0, c->zolo.q[0], c->zc.as<double>(), c->zdelta.as<double>()};
 }
 
+// Coefficients of one unshifted system: the trace of D_W^-1, the inner solves, refinements.
+void ensure_unit_coef(smpq_ctx *c) {
+    if (c->coef_inv.n) return;
+    const double cd[2] = {1.0, 0.0};
+    c->inv_cd.ensure(sizeof(cd));
+    to_device(c, c->inv_cd.p, cd, sizeof(cd));
+    c->coef_inv = smpq_ctx::Coef{1, 0.0, 0.0, c->inv_cd.as<double>(), c->inv_cd.as<double>() + 1};
+}
+
 // Select the coefficient set of the next solves (Zolotarev or the unshifted inverse).
 void use_coef(smpq_ctx *c, bool inverse) {
-    if (inverse && !c->inv_cd.p) {
-        const double cd[2] = {1.0, 0.0};
-        c->inv_cd.ensure(sizeof(cd));
-        to_device(c, c->inv_cd.p, cd, sizeof(cd));
-        c->coef_inv = smpq_ctx::Coef{1, 0.0, 0.0, c->inv_cd.as<double>(), c->inv_cd.as<double>() + 1};
-    }
+    if (inverse) ensure_unit_coef(c);
     c->coef = inverse ? &c->coef_inv : &c->coef_eps;
 }
 
@@ -948,11 +952,7 @@ void check_shifts(smpq_ctx *c, int prec, int nslots, const Source &src, smpq_sta
     const size_t vbytes = rs64 * sizeof(double2);
     const size_t pstride = partial_stride(g);
     const int np = unit_parts(0, g);
-    if (!c->inv_cd.p) {
-        const double cd[2] = {1.0, 0.0};
-        c->inv_cd.ensure(sizeof(cd));
-        to_device(c, c->inv_cd.p, cd, sizeof(cd));
-    }
+    ensure_unit_coef(c);
     std::vector<double> ch(NS), dh(NS), bn(nslots);
     HIPCHK(hipMemcpyAsync(ch.data(), coef.c, sizeof(double) * NS, hipMemcpyDeviceToHost, s));
     HIPCHK(hipMemcpyAsync(dh.data(), coef.delta, sizeof(double) * NS, hipMemcpyDeviceToHost, s));

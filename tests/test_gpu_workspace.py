@@ -38,3 +38,16 @@ def test_failed_layout_is_not_kept(prec, limit):
     smpq.smpq_set_scheme(c, (2, 2, 2, 2), 0)
     got = smpq.smpq_compute_qx_classes(c, [3])
     assert np.array_equal(want[0], got[0]) and np.array_equal(want[1], got[1])
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_inverse_after_a_shift_check(prec):
+    """The unshifted system's coefficients are there whichever call needs them first."""
+    print(f"trace of D_W^-1 after a shift check, precision {prec}", flush=True)
+    want = smpq.smpq_compute_trinv(_ctx(prec), [3])[0]
+    assert np.abs(want).max() > 1.0
+    c = _ctx(prec)
+    smpq.smpq_set_shift_check(c, True, 0.0)
+    smpq.smpq_compute_qx_classes(c, [5])
+    smpq.smpq_set_shift_check(c, False)
+    assert np.array_equal(smpq.smpq_compute_trinv(c, [3])[0], want)
