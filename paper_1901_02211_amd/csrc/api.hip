@@ -195,6 +195,7 @@ struct smpq_ctx {
     std::vector<int32_t> cptr, csites;
     DevMem d_colour, d_cptr, d_csites;
     DevMem d_pcolour, d_pptr;   // point scheme (identity) on demand
+    bool scheme_there = false, points_there = false;   // these arrays are filled
     Workspace ws;
     DevMem qx, qxi, lz;
     DevMem io;   // spinors of the host-buffer calls, see IoBuffer
@@ -1036,23 +1037,25 @@ void check_shifts(smpq_ctx *c, int prec, int nslots, const Source &src, smpq_sta
 }
 
 void ensure_scheme_device(smpq_ctx *c) {
-    if (c->d_colour.p) return;
+    if (c->scheme_there) return;
     c->d_colour.ensure(sizeof(int) * c->V);
     c->d_cptr.ensure(sizeof(int) * (c->n_classes + 1));
     c->d_csites.ensure(sizeof(int) * c->V);
     to_device(c, c->d_colour.p, c->colour.data(), sizeof(int) * c->V);
     to_device(c, c->d_cptr.p, c->cptr.data(), sizeof(int) * (c->n_classes + 1));
     to_device(c, c->d_csites.p, c->csites.data(), sizeof(int) * c->V);
+    c->scheme_there = true;
 }
 
 void ensure_point_device(smpq_ctx *c) {
-    if (c->d_pcolour.p) return;
+    if (c->points_there) return;
     std::vector<int> id(c->V + 1);
     for (int i = 0; i <= c->V; ++i) id[i] = i;
     c->d_pcolour.ensure(sizeof(int) * c->V);
     c->d_pptr.ensure(sizeof(int) * (c->V + 1));
     to_device(c, c->d_pcolour.p, id.data(), sizeof(int) * c->V);
     to_device(c, c->d_pptr.p, id.data(), sizeof(int) * (c->V + 1));
+    c->points_there = true;
 }
 
 // Extreme Ritz values of H^2 after `steps` steps.  alpha_j and the vectors' norms, the beta_j, stay on
@@ -1266,9 +1269,10 @@ void set_zolo(smpq_ctx *c, int n, double lo, double hi) {
     } catch (const std::exception &e) {
         throw Fail{SMPQ_ENUMERIC, e.what()};
     }
-    c->have_zolo = true;
+    c->have_zolo = false;
     c->gen++;
     if (c->device >= 0) upload_zolo(c);
+    c->have_zolo = true;
 }
 
 void auto_zolo(smpq_ctx *c, smpq_stats *st) {
@@ -1654,6 +1658,7 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
                         u32[f + 1] = (float)src[1];
                     }
                 }
+        c->have_gauge = false;   // until the new field is whole
         c->U64.ensure(sizeof(double) * V * 72);
         c->U32.ensure(sizeof(float) * V * 48);
         to_device(c, c->U64.p, u64.data(), sizeof(double) * V * 72);
@@ -1775,6 +1780,7 @@ static void install_scheme(smpq_ctx *c, std::vector<int32_t> &&col, int ncls) {
     std::vector<int> fill(c->cptr.begin(), c->cptr.end() - 1);
     for (int s = 0; s < c->V; ++s) c->csites[fill[c->colour[s]]++] = s;
     c->have_scheme = true;
+    c->scheme_there = false;
     c->d_colour.release();
     c->d_cptr.release();
     c->d_csites.release();
