@@ -567,10 +567,10 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
 }
 
 // A workspace for at least B right-hand sides whatever the context's memory limit: the one at hand,
-// or a new one with the longest block that fits the free memory.
+// or a new one for just these with the longest block that fits the free memory.
 void ensure_workspace_for(smpq_ctx *c, int prec, int NS, int B) {
     const Workspace &w = c->ws;
-    if (w.prec == prec && w.NS == NS && w.B >= B) return ensure_workspace(c, prec, NS, w.B, w.K);
+    if (w.S.rr && w.prec == prec && w.NS == NS && w.B >= B && w.check == c->shift_check) return;
     size_t freeb = 0, totalb = 0;
     HIPCHK(hipMemGetInfo(&freeb, &totalb));
     const double budget = 0.80 * (double)(freeb + workspace_bytes(c));

@@ -1,4 +1,6 @@
 """GPU: the workspace of a context when memory runs short or its options change."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -51,3 +53,31 @@ def test_inverse_after_a_shift_check(prec):
     smpq.smpq_compute_qx_classes(c, [5])
     smpq.smpq_set_shift_check(c, False)
     assert np.array_equal(smpq.smpq_compute_trinv(c, [3])[0], want)
+
+
+class Memory:
+    """Free device memory, from the HIP runtime the library is linked to."""
+
+    def __init__(self):
+        self.hip = ctypes.CDLL("libamdhip64.so.7")
+
+    def free(self):
+        a, b = ctypes.c_size_t(), ctypes.c_size_t()
+        assert self.hip.hipMemGetInfo(ctypes.byref(a), ctypes.byref(b)) == 0
+        return a.value
+
+
+def test_locality_after_switching_the_check_on():
+    """The twelve solves of the locality need a workspace of twelve when the one at hand has no room for the
+    check, not one as large as that with the check's vectors on top (70 GB: more than its limit)."""
+    print("locality with the shift check on beside a workspace without it", flush=True)
+    want = smpq.smpq_dov_locality(_ctx(), 5)[0]
+    c, mem = _ctx(), Memory()
+    free = mem.free()
+    smpq.smpq_set_point_scheme(c)
+    smpq.smpq_set_memory_limit(c, 48 << 30)
+    smpq.smpq_prepare(c)
+    assert free - mem.free() > 40 << 30
+    smpq.smpq_set_shift_check(c, True, 0.0)
+    assert np.array_equal(smpq.smpq_dov_locality(c, 5)[0], want)
+    assert free - mem.free() < 2 << 30        # 12 x (67 + 18) FP64 vectors of 0.8 MB and small arrays
