@@ -566,14 +566,18 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
     return BatchPlan{(int)std::min(B, even), K};
 }
 
-// A workspace for at least B right-hand sides whatever the context's memory limit: the one at hand,
-// or a new one for just these with the longest block that fits the free memory.
+// A workspace for at least B right-hand sides: the one at hand, or a new one for just these with the
+// longest block that fits the memory limit or, without one, the free memory.  K = 1 is taken
+// whatever the limit: these calls have always laid out all their sources.
 void ensure_workspace_for(smpq_ctx *c, int prec, int NS, int B) {
     const Workspace &w = c->ws;
-    if (w.S.rr && w.prec == prec && w.NS == NS && w.B >= B && w.check == c->shift_check) return;
+    const size_t limit = c->run_limit > 0 ? c->run_limit : c->mem_limit;
+    if (w.S.rr && w.prec == prec && w.NS == NS && w.B >= B && w.check == c->shift_check &&
+        (limit == 0 || w.K == 1 || workspace_bytes(c) <= limit))
+        return;
     size_t freeb = 0, totalb = 0;
     HIPCHK(hipMemGetInfo(&freeb, &totalb));
-    const double budget = 0.80 * (double)(freeb + workspace_bytes(c));
+    const double budget = limit > 0 ? (double)limit : 0.80 * (double)(freeb + workspace_bytes(c));
     int K = 1;
     if (!short_block(prec))
         for (int k : kBlockIters)

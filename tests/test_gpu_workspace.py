@@ -81,3 +81,28 @@ def test_locality_after_switching_the_check_on():
     smpq.smpq_set_shift_check(c, True, 0.0)
     assert np.array_equal(smpq.smpq_dov_locality(c, 5)[0], want)
     assert free - mem.free() < 2 << 30        # 12 x (67 + 18) FP64 vectors of 0.8 MB and small arrays
+
+
+@pytest.mark.parametrize("vectors", [17, 25, 40])      # K = 1, 5 and 20 of the locality's 14 shifts
+def test_locality_and_deflation_keep_to_the_limit(vectors):
+    """A memory limit of 12 x (K + 17) FP64 vectors (16 + K with K > 1) or a little more: what the locality
+    holds afterwards stays below it, and so does what the inner solves of a deflation hold."""
+    dims = (16, 16, 16, 16)
+    vec = 192 * 16 ** 4
+    print(f"locality and deflation within {vectors} vectors a source", flush=True)
+    c, mem = _ctx(0, dims), Memory()
+    smpq.smpq_dov_locality(_ctx(0, dims), 5)           # the library's own one-time allocations
+    small = 48 << 20                                   # reductions, scalars, scheme arrays, graphs
+    free = mem.free()
+    smpq.smpq_set_memory_limit(c, 12 * vectors * vec)
+    m = smpq.smpq_dov_locality(c, 5)[0]
+    assert free - mem.free() <= 12 * vectors * vec + small
+    assert np.array_equal(m, smpq.smpq_dov_locality(_ctx(0, dims), 5)[0])
+    # deflation: one source and one shift, 4 vectors with K = 1 (54 with K = 50)
+    c = _ctx(0, dims)
+    free = mem.free()
+    smpq.smpq_set_memory_limit(c, 4 * vec)
+    with pytest.raises(smpq.SmpqError) as e:
+        smpq.smpq_deflate(c, 1, 4)                     # too few steps: refused after the solves
+    assert e.value.status == -5
+    assert free - mem.free() <= 4 * vec + 4 * vec + small      # and the four vectors of the bounds
