@@ -1607,7 +1607,7 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
         double row3 = 0.0;   // largest deviation of a third row from the one rebuilt from the first two
         for (size_t l = 0; l < (size_t)4 * c->V; ++l) {
             const double *u = U + 18 * l;
-            double err2 = 0.0;   // largest |(U^dag U - 1)_ab|^2
+            bool unitary = true;   // every |(U^dag U - 1)_ab| <= 1e-10; products that overflow are not
             for (int a = 0; a < 3; ++a)
                 for (int b = 0; b < 3; ++b) {
                     double re = 0.0, im = 0.0;   // (U^dag U)_ab = sum_k conj(U_ka) U_kb
@@ -1618,7 +1618,7 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
                         im += ar * bi - ai * br;
                     }
                     re -= a == b;
-                    err2 = std::max(err2, re * re + im * im);
+                    unitary = unitary && re * re + im * im <= 1e-20;
                 }
             // det by cofactor expansion along the first row
             auto C = [&](int r, int k) { return std::pair<double, double>(u[2 * (3 * r + k)], u[2 * (3 * r + k) + 1]); };
@@ -1641,7 +1641,7 @@ smpq_status smpq_load_gauge(smpq_ctx *c, const double *U, size_t n) {
                 const auto x = sub(mul(C(0, (b + 1) % 3), C(1, (b + 2) % 3)), mul(C(0, (b + 2) % 3), C(1, (b + 1) % 3)));
                 row3 = std::max(row3, std::max(std::fabs(C(2, b).first - x.first), std::fabs(C(2, b).second + x.second)));
             }
-            if (err2 > 1e-20 || std::hypot(det.first - 1.0, det.second) > 1e-10)
+            if (!unitary || !(std::hypot(det.first - 1.0, det.second) <= 1e-10))
                 throw Fail{SMPQ_ENUMERIC, "gauge link is not in SU(3) (|U^dag U - 1| or |det U - 1| > 1e-10)"};
         }
         need_device(c);
