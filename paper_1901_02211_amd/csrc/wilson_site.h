@@ -43,6 +43,14 @@ __host__ __device__ __forceinline__ cpx<T> cjmul(cpx<T> a, cpx<T> b) {
 // a * b + c with a single rounding
 __host__ __device__ __forceinline__ float fmadd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __host__ __device__ __forceinline__ double fmadd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+// the products in FP64 with their rounding written out, so that every kernel rounds them alike (left to the
+// compiler, which of the two products is fused differed between two forms of one kernel)
+__host__ __device__ __forceinline__ cpx<double> cmul(cpx<double> a, cpx<double> b) {
+    return {fmadd(a.re, b.re, -(a.im * b.im)), fmadd(a.re, b.im, a.im * b.re)};
+}
+__host__ __device__ __forceinline__ cpx<double> cjmul(cpx<double> a, cpx<double> b) {
+    return {fmadd(a.re, b.re, a.im * b.im), fmadd(a.re, b.im, -(a.im * b.re))};
+}
 // c + a * b and c + conj(a) * b as chains of fused multiply-adds: sums of complex products
 // written this way take 4 instructions per term instead of 6 (the compiler does not
 // reassociate a sum of products into such a chain by itself)
