@@ -414,10 +414,11 @@ smpq_status smpq_bench_stream(smpq_ctx *ctx, size_t bytes, int launches, int non
  * +-t neighbours of a plane were read shortly before (1 = z fastest).  FP64 stencil:
  * f64_kind 0 is the FP32 kind 0 with 2^f64_lgr = 1, 2 or 4 right-hand sides per block in turn;
  * f64_kind 1 stages xy-tiles in LDS as FP32 kind 2 does (one halo row on each side unless the
- * tile is the whole plane), f64_nr = 1, 2, 4 or 8 right-hand sides per block, the links read as
- * their first two rows with the third rebuilt in the solver's iterations (in full elsewhere, and
- * where a loaded link's third row differs from that by more than 1e-14; where a tile fits;
- * plane_band applies too).
+ * tile is the whole plane), f64_nr = 1, 2, 4 or 8 right-hand sides per block (where a tile fits;
+ * plane_band applies too).  Chosen with smpq_set_tuning or by smpq_autotune its solver iterations read
+ * links as their first two rows with the third rebuilt (in full where a loaded link's third row
+ * differs from that by more than 1e-14); the other variants, the default ones and D_W itself
+ * read every entry;
  * f32_interleave (FP32 kind 4) and f64_interleave (FP64 kind 1): 1, 2, 4, 8 or 16 blocks in a
  * row take successive groups of right-hand sides of the same tile before the blocks move on
  * to the next tile, so that the links a tile reads for each right-hand side come from L2;

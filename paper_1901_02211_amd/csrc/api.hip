@@ -282,8 +282,9 @@ smpq_status guarded(smpq_ctx *c, F &&f) {
 }
 
 // Links of a field computed in FP64 have a third row within a few 1e-15 of the conjugate cross
-// product of the first two, and the FP64 stencils rebuild it from them (384 instead of 576 bytes a
-// site); a field accepted with more than this (up to 1e-10) keeps its own third rows.
+// product of the first two, and the tile variant f64_kind 1, where it was chosen, rebuilds it from them
+// (384 instead of 576 bytes a site); a field accepted with more than this (up to 1e-10) keeps its own
+// third rows there too.
 constexpr double kRow3Tol = 1e-14;
 
 // Device memory of one host-buffer call: the context's, enlarged as needed, given back at the end

@@ -30,7 +30,7 @@ struct Geom {
     int f64_kind, f64_nr;
     int f32_il, f64_il;
     int adapt;      // no variant chosen: each launch takes the one that suits its size
-    int f64_full;   // FP64 links: read all nine entries (else two rows, the third rebuilt)
+    int f64_full;   // a chosen f64_kind 1 reads all nine link entries too (else two rows, the third rebuilt)
     // the FP32 variant of the D_W^dag launches (f32_kind, f32_nr and f32_il above apply to D_W):
     // the two stencils of a CG iteration have different epilogues and favour different variants
     int f32_dag_kind, f32_dag_nr, f32_dag_il;

@@ -591,10 +591,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 8))) 
 //   kTileAny    the same for any plane, with idle threads: several whole planes where they are small,
 //               else ty rows of one plane, the last tile of a plane maybe shorter (kind 0)
 //   kTileNone   256 consecutive sites, all neighbours through the caches (kind 0, nx > 128)
-// A tile that is not whole planes has one halo row on each side.  Links: their first two rows (FP64
-// 96 bytes, FP32 48), the third rebuilt as conj(row0 x row1) (exact for SU(3) up to rounding); in
-// FP64 all nine entries (FULL) outside the solver's iterations, and there where a loaded link's third
-// row is further than rounding from that.
+// A tile that is not whole planes has one halo row on each side.  Links: in FP32 their first two rows (48
+// bytes), the third rebuilt as conj(row0 x row1) (exact for SU(3) up to rounding); in FP64 all nine
+// entries (FULL), or two rows (96 of 144 bytes) in the solver's iterations where the caller chose that.
 enum { kTileExact, kTileAny, kTileNone };
 
 // u's third row from its first two
@@ -654,9 +653,8 @@ __device__ __forceinline__ void tile_read(const float4 *tile, int l, cpx<float> 
 // In FP64 the second accumulator would leave one wave per SIMD.
 //
 // Waves per SIMD the kernel is compiled for: three for a pair in FP32; three for the FP64 solver's
-// two epilogues (3 and 2) with one right-hand side per block, which need 164-171 VGPRs, just above
-// the 168 that three waves allow, and run 9 % faster so than at two with at most two registers
-// spilled.
+// two epilogues (3 and 2) on tiles with one right-hand side per block, which fit the 168 VGPRs of three
+// waves (with rebuilt rows four are spilled) and are 9 % faster so than at two.
 template <class T, int P, int EPI, int TILE, bool ONE>
 struct RlWaves {
     static constexpr int min = std::is_same<T, double>::value ? ((TILE == kTileExact ? ONE : TILE == kTileAny) && (EPI == 2 || EPI == 3) ? 3 : 1)
@@ -1014,21 +1012,22 @@ static void launch_rl(bool exact, const void *U, const void *in, size_t in_strid
     int ty, m;
     any_tile(g, ty, m);
     if constexpr (std::is_same<T, double>::value) {
-        // D_W itself and H^2 + sigma (epilogues 0 and 1) keep the links as loaded: a rebuilt row costs
-        // a few 1e-16 of the result, which the solver's iterations (2 and 3) do not notice
-        if constexpr (EPI == 0 || EPI == 1) {
-            if (exact) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, true, false>);
-            else if (ty > 0) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, true, false>);
-            else go(launch_rl_t<double, 1, DAG, EPI, kTileNone, true, false>);
-        } else {
-            if (exact && g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, true, false>);
-            else if (exact && nr == 1) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, true>);
-            else if (exact) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, false>);
-            else if (ty > 0 && g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, true, false>);
-            else if (ty > 0) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, false, false>);
-            else if (g.f64_full) go(launch_rl_t<double, 1, DAG, EPI, kTileNone, true, false>);
-            else go(launch_rl_t<double, 1, DAG, EPI, kTileNone, false, false>);
+        // Links are read in full unless the caller chose the tile variant (f64_kind 1), whose iterations
+        // (epilogues 2 and 3) rebuild third rows where those of the loaded links are within rounding of it;
+        // D_W itself and H^2 + sigma keep the links as loaded.  A rebuilt row takes the error of D_W from
+        // 1.7e-16 to 4.8e-16 of its largest entry, and that of D_ov at the finest tolerance from
+        // 4.31e-15 to 4.38e-15, for 2 to 10 % of an FP64 solve (four 16^4 classes, r = 4: 312 ms in
+        // full, 289 with two rows; four points on 12^4 110 and 99).
+        const bool rows = (EPI == 2 || EPI == 3) && exact && !g.adapt && !g.f64_full;
+        if constexpr (EPI == 2 || EPI == 3) {
+            if (rows && nr == 1) return go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, true>);
+            if (rows) return go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, false>);
         }
+        if (exact && nr == 1) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, true, true>);
+        else if (exact) go(launch_rl_t<double, 1, DAG, EPI, kTileExact, true, false>);
+        else if (ty > 0 && nr == 1) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, true, true>);
+        else if (ty > 0) go(launch_rl_t<double, 1, DAG, EPI, kTileAny, true, false>);
+        else go(launch_rl_t<double, 1, DAG, EPI, kTileNone, true, false>);
     } else {
         if (exact && nr > 1) go(launch_rl_t<float, 2, DAG, EPI, kTileExact, false, false>);
         else if (exact) go(launch_rl_t<float, 1, DAG, EPI, kTileExact, false, true>);
@@ -1562,13 +1561,13 @@ void launch_base_direction(int prec, const Geom &g, const MSState &s, const void
 // against about 10 in separate launches.
 // The sums have the order of the separate kernels (tiles of the stencil's blocks, their waves, one
 // wave over the tiles), so that results are equal bit for bit.
-template <class T, bool FULL>
+template <class T>
 struct RawLink {
-    static constexpr int n = std::is_same<T, float>::value ? 3 : FULL ? 9 : 6, per = std::is_same<T, float>::value ? 3 : 9;
+    static constexpr int n = std::is_same<T, float>::value ? 3 : 9;
     typename Store<T>::link v[n];
     __device__ __forceinline__ void load(const typename Store<T>::link *U, int V, int mu, int s) {
 #pragma unroll
-        for (int k = 0; k < n; ++k) v[k] = unit_get(U + (size_t)(mu * per + k) * V, s);
+        for (int k = 0; k < n; ++k) v[k] = unit_get(U + (size_t)(mu * n + k) * V, s);
     }
     __device__ __forceinline__ void unpack(cpx<T> u[9]) const {
         if constexpr (std::is_same<T, float>::value) {
@@ -1576,12 +1575,11 @@ struct RawLink {
         } else {
 #pragma unroll
             for (int k = 0; k < n; ++k) u[k] = {v[k].x, v[k].y};
-            if constexpr (!FULL) third_row(u);
         }
     }
 };
 
-template <class T, bool FULL, bool EXACT, int MAXT>
+template <class T, bool EXACT, int MAXT>
 __global__ __launch_bounds__(MAXT) void k_cg_small(const typename Store<T>::link *__restrict__ U, Geom g,
                                                             MSState S, int tpt, int np, T kappa, T sigma,
                                                             const typename Store<T>::vec *p_in,
@@ -1640,36 +1638,39 @@ __global__ __launch_bounds__(MAXT) void k_cg_small(const typename Store<T>::link
     cpx<T> acc[12], u[9], q[12], h[6], w[6];
     // D_W or D_W^dag of the field at the own site, q = the field there
     // Each link is loaded one hop ahead (its rows as stored), since one or two waves per SIMD hide
-    // little of the latency of L2; where registers are short, once the link before it is unpacked.
+    // little of the latency of L2; in FP64 only up to 256 threads, whose registers hold two links of
+    // 36 (on 512 threads 139-192 were spilled, a
+    // map of four classes on 4^3 x 8 8.7 ms against 6.9 so).
     constexpr bool kAhead = std::is_same<T, float>::value || MAXT <= 256;
-    RawLink<T, FULL> l0, l1;
-#define SMPQ_SMALL_HOP(MU, SF, CUR, NEXT, NMU, NSITE, SITE, MUL, FIRST)              \
+    [[maybe_unused]] RawLink<T> l0, l1;
+#define SMPQ_SMALL_HOP(MU, SF, CUR, LSITE, NEXT, NMU, NSITE, SITE, MUL, FIRST)       \
         if constexpr (kAhead) {                                                      \
             NEXT.load(Ur, g.V, NMU, NSITE);                                          \
             __builtin_amdgcn_sched_barrier(0);                                       \
             CUR.unpack(u);                                                           \
-        } else {                                                                     \
-            CUR.unpack(u);                                                           \
-            NEXT.load(Ur, g.V, NMU, NSITE);                                          \
         }                                                                            \
         tile_read(field, SITE, q);                                                   \
         project<MU, SF>(q, h);                                                       \
+        if constexpr (!kAhead) {                                                     \
+            __builtin_amdgcn_sched_barrier(0);                                       \
+            load_link<T>(Ur, g.V, MU, LSITE, u);                                     \
+        }                                                                            \
         MUL(u, h, w);                                                                \
         accumulate<MU, SF, FIRST>(acc, w);                                           \
         __builtin_amdgcn_sched_barrier(0);
     // l0 holds U_z(x) before and after
-#define SMPQ_SMALL_HOPS(SF)                                                          \
-        SMPQ_SMALL_HOP(2, SF, l0, l1, 2, nb.bwd[2], nb.fwd[2], su3_mul, true)        \
-        SMPQ_SMALL_HOP(2, -SF, l1, l0, 3, s, nb.bwd[2], su3_dag_mul, false)          \
-        SMPQ_SMALL_HOP(3, SF, l0, l1, 3, nb.bwd[3], nb.fwd[3], su3_mul, false)       \
-        SMPQ_SMALL_HOP(3, -SF, l1, l0, 0, s, nb.bwd[3], su3_dag_mul, false)          \
-        SMPQ_SMALL_HOP(0, SF, l0, l1, 0, nb.bwd[0], nb.fwd[0], su3_mul, false)       \
-        SMPQ_SMALL_HOP(0, -SF, l1, l0, 1, s, nb.bwd[0], su3_dag_mul, false)          \
-        SMPQ_SMALL_HOP(1, SF, l0, l1, 1, nb.bwd[1], nb.fwd[1], su3_mul, false)       \
-        SMPQ_SMALL_HOP(1, -SF, l1, l0, 2, s, nb.bwd[1], su3_dag_mul, false)          \
-        _Pragma("unroll") for (int c = 0; c < 12; ++c)                               \
+#define SMPQ_SMALL_HOPS(SF)                                                                     \
+        SMPQ_SMALL_HOP(2, SF, l0, s, l1, 2, nb.bwd[2], nb.fwd[2], su3_mul, true)                \
+        SMPQ_SMALL_HOP(2, -SF, l1, nb.bwd[2], l0, 3, s, nb.bwd[2], su3_dag_mul, false)          \
+        SMPQ_SMALL_HOP(3, SF, l0, s, l1, 3, nb.bwd[3], nb.fwd[3], su3_mul, false)               \
+        SMPQ_SMALL_HOP(3, -SF, l1, nb.bwd[3], l0, 0, s, nb.bwd[3], su3_dag_mul, false)          \
+        SMPQ_SMALL_HOP(0, SF, l0, s, l1, 0, nb.bwd[0], nb.fwd[0], su3_mul, false)               \
+        SMPQ_SMALL_HOP(0, -SF, l1, nb.bwd[0], l0, 1, s, nb.bwd[0], su3_dag_mul, false)          \
+        SMPQ_SMALL_HOP(1, SF, l0, s, l1, 1, nb.bwd[1], nb.fwd[1], su3_mul, false)               \
+        SMPQ_SMALL_HOP(1, -SF, l1, nb.bwd[1], l0, 2, s, nb.bwd[1], su3_dag_mul, false)          \
+        _Pragma("unroll") for (int c = 0; c < 12; ++c)                                          \
             asm volatile("" : "+v"(acc[c].re), "+v"(acc[c].im));
-    l0.load(U, g.V, 2, s);
+    if constexpr (kAhead) l0.load(U, g.V, 2, s);
     __shared__ ShiftLane shifts[64];
     if (wv == 0) shifts[lane].load(S, slot);
     Store<T>::load(p_in + slot * pst, g.vs, s, q);
@@ -1772,12 +1773,10 @@ static void launch_cg_small_t(const Geom &g, const MSState &s, const void *U, do
     // up to 256 threads the block has a SIMD's registers per wave
     const bool exact = g.tile_y > 0;
     if constexpr (dbl) {
-        if (g.f64_full) return exact ? go(k_cg_small<T, true, true, kSmallThreads>)
-                                     : go(k_cg_small<T, true, false, kSmallThreads>);
-        if (threads <= 256) return exact ? go(k_cg_small<T, false, true, 256>) : go(k_cg_small<T, false, false, 256>);
+        if (threads <= 256) return exact ? go(k_cg_small<T, true, 256>) : go(k_cg_small<T, false, 256>);
     }
-    if (exact) go(k_cg_small<T, false, true, kSmallThreads>);
-    else go(k_cg_small<T, false, false, kSmallThreads>);
+    if (exact) go(k_cg_small<T, true, kSmallThreads>);
+    else go(k_cg_small<T, false, kSmallThreads>);
 }
 
 void launch_cg_small(int prec, const Geom &g, const MSState &s, const void *U, double kappa, double sigma,
