@@ -368,8 +368,8 @@ inline int vec_prec(int prec) { return prec == 0 ? 0 : 1; }
 inline int vec16_mode(int prec) { return prec == 4 ? 1 : prec == 5 ? 2 : 0; }
 inline int dir_store(int prec) { return prec == 2 ? kDirF16 : prec == 3 ? kDirBF16 : kDirF32; }
 
-// The 16-bit precisions round what they store after every iteration, so their block is one long.
-inline bool short_block(int prec) { return prec >= 2; }
+// 16-bit directions are rounded as they are stored, after every iteration: their block is one long.
+inline bool short_block(int prec) { return dir_store(prec) != kDirF32; }
 // entries of p per right-hand side: the shifts (only the base one with 16-bit directions) and, with
 // K > 1, the second buffer of the base direction
 inline int dir_entries(int prec, int NS, int K) { return (dir_store(prec) == kDirF32 ? NS : 1) + (K > 1 ? 1 : 0); }
@@ -443,7 +443,7 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     }
     const size_t pstride = partial_stride(g);
     const size_t BN = (size_t)B * NS, BKN = BN * K;
-    w.st_d.ensure(sizeof(double) * ((size_t)B * 7 + 5 * BN + 4 * BKN));
+    w.st_d.ensure(sizeof(double) * ((size_t)B * (7 + K) + 5 * BN + 4 * BKN));
     w.st_i.ensure(sizeof(int) * ((size_t)B * 8 + 2 * BN + 16));
     w.st_l.ensure(sizeof(long long) * (size_t)B * 5);
     w.partial.ensure(sizeof(double) * (size_t)B * pstride);
@@ -478,6 +478,7 @@ void ensure_workspace(smpq_ctx *c, int prec, int NS, int B, int K) {
     S.h_a = dbl(BKN);
     S.h_b = dbl(BKN);
     S.h_z = dbl(BKN);
+    S.h_rr = dbl((size_t)B * K);
     S.dir_norm = 1.0 / std::sqrt(24.0 * (double)c->V);
     int *ip = w.st_i.as<int>();
     auto intg = [&ip](size_t n) { int *q = ip; ip += n; return q; };
@@ -646,6 +647,8 @@ struct SolveLayout {
           pst(rs * dir_entries(prec, S.NS, S.K)),
           alt(S.K > 1 ? dir_entries(prec, S.NS, 1) : 0) {}
     size_t base(int par) const { return par ? (size_t)alt * rs : 0; }
+    // the current base direction: a block's first iteration finds it where the last block left it
+    size_t base_at(const BlockPos &pos) const { return pos.n == 0 || !alt ? base(pos.par) : base(pos.par ^ 1); }
     // ring position of the residual that iteration n of a block reads (it writes position n)
     static int ring_in(int n, int K) { return n == 0 ? K - 1 : n - 1; }
 };
@@ -680,13 +683,12 @@ void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, i
     const SolveLayout L(c, prec, S);
     const size_t rs = L.rs;
     const void *U = vp == 0 ? c->U64.p : c->U32.p;
-    // the current base direction: the block's first iteration finds it where the last block left it
-    const size_t pofs = pos.n == 0 || !L.alt ? L.base(pos.par) : L.base(pos.par ^ 1);
+    const size_t pofs = L.base_at(pos);
     const size_t r_in = rs * SolveLayout::ring_in(pos.n, S.K), r_out = rs * pos.n;
     char *rp = w.r.as<char>(), *pp = w.p.as<char>();
     // partials per slot of the first (D_W p) and the second (D_W^dag) stencil
     const int np_ds = dslash_partials(vp, g, false), np_dag = dslash_partials(vp, g, true);
-    const bool fused = L.alt && dslash_takes_partials(vp, g, true) && std::max(np_ds, np_dag) <= kFusedPartials;
+    const bool fused = L.alt && !S.vec16 && dslash_takes_partials(vp, g, true) && std::max(np_ds, np_dag) <= kFusedPartials;
     double *rr_in = fused && gi % 2 ? S.rr1 : S.rr, *rr_out = fused && gi % 2 == 0 ? S.rr1 : S.rr;
     const Slots act{S.list, S.count, 0};
     const double s0 = c->coef->s0;
@@ -694,8 +696,7 @@ void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, i
     launch_dslash(vp, false, 3, U, w.p.p, L.pst, pofs, w.tmp.p, rs, nullptr, 0, 0, g, c->kappa, s0, act, B, S.partial,
                   s, ResidualStep{}, S.done);
     if (tm) tm->dslash.record(s, captured);
-    const int m16 = vec16_mode(prec);
-    if (m16) launch_round16(g, S, w.tmp.p, rs, 0, m16, s);   // D_W p as 16-bit storage would hold it
+    if (S.vec16) launch_round16(g, S, w.tmp.p, rs, 0, S.vec16, s);   // D_W p as 16-bit storage would hold it
     if (!fused) launch_scalars_alpha(S, np_ds, s);
     ResidualStep rstep{S.alpha, S.status, (ptrdiff_t)r_in - (ptrdiff_t)r_out};
     if (fused) {
@@ -717,7 +718,7 @@ void enqueue_iteration(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, i
     else
         pos.advance(1, S.K);
     if (tm) tm->update.record(s, captured);
-    if (m16) launch_round16(g, S, w.p.p, L.pst, L.base(pos.par), m16, s);   // the new base direction
+    if (S.vec16) launch_round16(g, S, w.p.p, L.pst, L.base_at(pos), S.vec16, s);   // the new base direction
 }
 
 // One group of kGroup iterations from the given position, then the list of the slots still iterating.
@@ -727,12 +728,12 @@ void enqueue_group(smpq_ctx *c, int prec, const MSState &S, BlockPos &pos, Group
     const int vp = vec_prec(prec);
     const Geom g = c->geom();
     const SolveLayout L(c, prec, S);
-    if (!tm && L.alt && small_lattice(vp, g)) {
+    if (!tm && L.alt && !S.vec16 && small_lattice(vp, g)) {
         char *pp = c->ws.p.as<char>();
         for (int left = kGroup; left > 0;) {
             const int n = std::min(left, S.K - pos.n);
             launch_cg_small(vp, g, S, vp == 0 ? c->U64.p : c->U32.p, c->kappa, c->coef->s0,
-                            pp + L.base(pos.n == 0 ? pos.par : pos.par ^ 1) * kUnit, pp + L.base(pos.par ^ 1) * kUnit,
+                            pp + L.base_at(pos) * kUnit, pp + L.base(pos.par ^ 1) * kUnit,
                             L.pst, c->ws.r.p, pos.n, n, c->stream);
             left -= n;
             if (pos.n + n == S.K) enqueue_block_update(c, prec, S, pos);
@@ -801,6 +802,7 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     // a solve may use fewer shifts than the workspace holds (a refinement solves one)
     if (c->coef->n > w.NS) throw Fail{SMPQ_ESTATE, "workspace laid out for fewer shifts than the solve"};
     S.NS = c->coef->n;
+    S.vec16 = vec16_mode(prec);
     S.i0 = 0;            // q ascending: the smallest shift is the base system
     S.tol = c->tol;
     S.c = c->coef->c;
@@ -835,8 +837,8 @@ BatchResult run_batch(smpq_ctx *c, int prec, int nslots, const Source &src, smpq
     launch_scalars_init(S, np_unit, nslots, s);
     if (dir != kDirF32) launch_dir16_init(g, S, nslots, r0, L.rst, dir, w.ph.p, s);
     launch_compact(S, s);
-    if (vec16_mode(prec))   // the first base direction, b, with the scale |b|
-        launch_round16(g, S, w.p.p, L.pst, 0, vec16_mode(prec), s);
+    if (S.vec16)   // the first base direction, b, with the scale |b|
+        launch_round16(g, S, w.p.p, L.pst, 0, S.vec16, s);
     HIPCHK(hipGetLastError());
 
     BatchResult res;

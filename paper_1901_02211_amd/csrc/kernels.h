@@ -73,6 +73,10 @@ struct MSState {
     // 16-bit shifted directions: p_i is stored as p_i / sh_scale[slot NS + i]; the scale that
     // decodes the stored direction and the reciprocal of the one the block update stores with
     double *sh_scale, *s_sold, *s_snew;
+    // the vectors the stencil reads rounded to 16 bits (0: not, 1: FP16, 2: BF16), and |r|^2 after each
+    // iteration of the block, [slot][K], from which the block update scales the base direction alike
+    int vec16;
+    double *h_rr;
     double dir_norm;     // 1 / sqrt(24 V): a direction of norm n has entries of size ~ n dir_norm
     long long *cnt_entries, *cnt_active;               // listed shifts, iterations
     long long *cnt_fl, *cnt_fl_r, *cnt_fl_p;           // block updates, residuals and directions they moved
@@ -135,7 +139,7 @@ size_t partial_stride(const Geom &g);           // slot stride of the partial bu
 // BF16 scaled by a per-direction FP64 factor (the base direction, which the stencil reads,
 // stays FP32).  With 16-bit storage, p holds only the base direction of each slot and ph the NS
 // directions in 16 bits (the base entry unused).
-enum { kDirF32 = 0, kDirF16 = 1, kDirBF16 = 2 };
+enum { kDirF32 = 0, kDirF16 = 1, kDirBF16 = 2, kDirVec16 = 3 };   // the last: see vec16
 
 // r = p_i = b, y = c0 b; FP32 path: x0 = 0 (null otherwise).  r and p have slot strides rst and
 // pst (units).  With 16-bit directions only r and the base direction are written;

@@ -1425,6 +1425,7 @@ struct ShiftLane {
             static_cast<T *>(S.h_b)[h] = (T)hb;
             static_cast<T *>(S.h_z)[h] = (T)hz;
         }
+        if (S.vec16 && i == 0) S.h_rr[(size_t)slot * S.K + j] = rrn;
         entries += __popcll(__ballot(listed));
         act = act && !conv;
         alpha_prev = a;
@@ -1824,6 +1825,21 @@ void launch_block_end(const MSState &s, bool base_inline, int dir, hipStream_t s
     hipLaunchKernelGGL(k_block_end, dim3(s.B), dim3(64), 0, st, s, base_inline ? 1 : 0, dir);
 }
 
+// The rounding of vectors that the stencil reads, mode 1: FP16 after division by sqrt(|r|^2 / (24 V)), where
+// the entries of a vector of norm |r| lie near 1; mode 2: BF16 (FP32's exponent range); to nearest even.
+struct Round16 {
+    int mode;
+    float sc, inv;
+    __device__ __forceinline__ Round16(int m, double rr, int V) : mode(m) {
+        const float scale = mode == 1 ? (float)sqrt(rr / (24.0 * (double)V)) : 1.f;
+        sc = scale > 0.f ? scale : 1.f;
+        inv = 1.f / sc;
+    }
+    __device__ __forceinline__ float operator()(float x) const {
+        return mode == 1 ? (float)(_Float16)(x * inv) * sc : (float)(__bf16)x;
+    }
+};
+
 // acc += w v in FP64
 template <class T>
 __device__ __forceinline__ void add_scaled(double w, cpx<T> v, cpx<double> &acc) {
@@ -1847,8 +1863,10 @@ __global__ __launch_bounds__(kBlock) void k_block_update(
     const unsigned *__restrict__ fl_wr, const double *__restrict__ h_cy, const double *__restrict__ h_a,
     const T *__restrict__ h_z, const T *__restrict__ h_b, const double *__restrict__ s_sold,
     const double *__restrict__ s_snew, const typename Store<T>::vec *__restrict__ ring, typename Store<T>::vec *p,
-    size_t pst, int base_sel, double2 *y, double2 *x0, void *ph, double2 *xs) {
+    size_t pst, int base_sel, double2 *y, double2 *x0, void *ph, double2 *xs, int vec16,
+    const double *__restrict__ h_rr) {
     using vec = typename Store<T>::vec;
+    constexpr bool DIR16 = D == kDirF16 || D == kDirBF16;
     constexpr int C = Unit<T>::C;
     const int slot = blockIdx.y;
     const int m = fl_m[slot];
@@ -1876,9 +1894,9 @@ __global__ __launch_bounds__(kBlock) void k_block_update(
 #pragma unroll
         for (int c = 0; c < C; ++c) pv[i][c] = {T(0), T(0)};
         if (rd >> i & 1) {
-            if (D == kDirF32 || i == i0)
+            if (!DIR16 || i == i0)
                 Unit<T>::load_stream(pp + (i == i0 ? base_sel : i) * rs, g.vs, u, s, pv[i]);
-            else if constexpr (D != kDirF32)
+            else if constexpr (DIR16)
                 load_dir16<D>(static_cast<typename Dir16<D>::v *>(ph) + ((size_t)slot * NS + i) * rs, g.vs, u, s,
                               (float)s_sold[slot * NS + i], pv[i]);
             if constexpr (XS) {
@@ -1914,6 +1932,13 @@ __global__ __launch_bounds__(kBlock) void k_block_update(
                 }
 #pragma unroll
                 for (int c = 0; c < C; ++c) pv[i][c] = next_direction(z, rv[c], b, pv[i][c]);
+                if constexpr (D == kDirVec16) {
+                    if (i == i0) {   // as k_round16 stored it for the next iteration's stencil
+                        const Round16 round(vec16, h_rr[(size_t)slot * K + l], g.V);
+#pragma unroll
+                        for (int c = 0; c < C; ++c) pv[i][c] = {round(pv[i][c].re), round(pv[i][c].im)};
+                    }
+                }
             }
         }
     }
@@ -1921,9 +1946,9 @@ __global__ __launch_bounds__(kBlock) void k_block_update(
     for (int i = 0; i < CH; ++i) {
         if (rd >> i & 1) {
             if (wr >> i & 1) {
-                if (D == kDirF32 || i == i0)
+                if (!DIR16 || i == i0)
                     Unit<T>::store_stream(pp + (i == i0 ? base_sel : i) * rs, g.vs, u, s, pv[i]);
-                else if constexpr (D != kDirF32)
+                else if constexpr (DIR16)
                     store_dir16<D>(static_cast<typename Dir16<D>::v *>(ph) + ((size_t)slot * NS + i) * rs, g.vs, u, s,
                                    (float)s_snew[slot * NS + i], pv[i]);
             }
@@ -1947,7 +1972,7 @@ static void launch_block_update_t(const Geom &g, const MSState &s, const void *r
     using vec = typename Store<T>::vec;
     dim3 grid(unit_parts(std::is_same<T, double>::value ? 0 : 1, g), s.B);
     hipLaunchKernelGGL((k_block_update<T, CH, D, XS>), grid, dim3(kBlock), 0, st, g, s.NS, s.K, s.i0, s.fl_m, s.fl_rd,
-                       s.fl_wr, s.h_cy, s.h_a, (const T *)s.h_z, (const T *)s.h_b, s.s_sold, s.s_snew, (const vec *)ring, (vec *)p, pst, base_sel, y, x0, ph, xs);
+                       s.fl_wr, s.h_cy, s.h_a, (const T *)s.h_z, (const T *)s.h_b, s.s_sold, s.s_snew, (const vec *)ring, (vec *)p, pst, base_sel, y, x0, ph, xs, s.vec16, s.h_rr);
 }
 
 // Registers for as many directions as the solve has: one (the trace of D_W^-1, refinement and inner
@@ -1977,16 +2002,18 @@ void launch_block_update(int prec, const Geom &g, const MSState &s, const void *
         launch_block_update_d<float, kDirF16, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
     else if (dir == kDirBF16)
         launch_block_update_d<float, kDirBF16, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else if (s.vec16 && s.K > 1 && xs)
+        launch_block_update_d<float, kDirVec16, true>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
+    else if (s.vec16 && s.K > 1)   // with K = 1 the base direction is rounded once it is stored
+        launch_block_update_d<float, kDirVec16, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
     else if (xs)
         launch_block_update_d<float, kDirF32, true>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
     else
         launch_block_update_d<float, kDirF32, false>(g, s, ring, p, pst, base_sel, y, x0, ph, xs, st);
 }
 
-// Evaluated precision: an FP32 vector of every listed slot rounded in place to what 16-bit
-// storage would hold, FP16 after division by the slot's scale sqrt(|r|^2 / (24 V)) (entries of
-// a vector of norm ~|r| then lie near 1) or BF16 (FP32's exponent range); round to nearest
-// even.  Applied to the vectors the stencil reads (the base direction and D_W p) after the
+// Evaluated precision: an FP32 vector of every listed slot rounded in place to what 16-bit storage would
+// hold.  Applied to the vectors the stencil reads (the base direction and D_W p) after the
 // kernels that write them, so that those compute in FP32 and only storage is emulated.
 __global__ __launch_bounds__(kBlock) void k_round16(Geom g, MSState S, float4 *v, size_t slot_stride, size_t extra,
                                                     int mode) {
@@ -1997,13 +2024,9 @@ __global__ __launch_bounds__(kBlock) void k_round16(Geom g, MSState S, float4 *v
     const int s = (blockIdx.x % nsb) * kBlock + threadIdx.x;
     if (s >= g.V) return;
     float4 *p = v + slot * slot_stride + extra + (size_t)u * g.vs + s;
-    const float scale = mode == 1 ? (float)sqrt(S.rr[slot] / (24.0 * (double)g.V)) : 1.f;
-    const float sc = scale > 0.f ? scale : 1.f, inv = 1.f / sc;
+    const Round16 round(mode, S.rr[slot], g.V);
     const float4 t = *p;
-    float x[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = mode == 1 ? (float)(_Float16)(x[i] * inv) * sc : (float)(__bf16)x[i];
-    *p = make_float4(x[0], x[1], x[2], x[3]);
+    *p = make_float4(round(t.x), round(t.y), round(t.z), round(t.w));
 }
 
 void launch_round16(const Geom &g, const MSState &s, void *v, size_t slot_stride, size_t extra, int mode,
