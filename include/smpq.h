@@ -401,8 +401,8 @@ smpq_status smpq_bench_copy(smpq_ctx *ctx, size_t bytes, int launches, double *m
  * smpq_bench_copy's library copy. */
 smpq_status smpq_bench_stream(smpq_ctx *ctx, size_t bytes, int launches, int nontemporal, double *ms_per_copy);
 
-/* Stencil variants.  f32_kind: 0 = any lattice (f32_nr = 2, 4 or 8 right-hand sides per block, two
- * at a time, the links read for each two; several whole xy-planes or rows of one staged in LDS,
+/* Stencil variants.  f32_kind: 0 = any lattice (f32_nr = 1, or 2, 4 or 8 right-hand sides per block,
+ * two at a time, the links read for each two; several whole xy-planes or rows of one staged in LDS,
  * one site per thread, no LDS where nx > 128); 1 = one 16x16 xy-plane per block staged
  * in LDS (nx*ny = 256; f32_nr = 4, 8 or 16); 2 = xy-tiles of ty rows plus one halo row on
  * each side staged in LDS, ty the largest divisor of ny with nx*ty <= 256 and a multiple of 64
@@ -445,8 +445,8 @@ typedef struct {
  * *chosen (may be NULL); on an error the previous choice is kept.  Without this call or
  * smpq_set_tuning every launch takes a variant by the lattice and its number of right-hand sides
  * (on 16 x 16 planes kind 1 / 8 for D_W and kind 4 / 2, interleave 2, for D_W^dag; kind 4 / 1 on
- * other tiles and with few right-hand sides; else kind 0; FP64 kind 1 / 1, interleave 2, where a
- * tile fits), and smpq_get_tuning reports those of a large batch. */
+ * other tiles and with few right-hand sides; else kind 0 / 1; FP64 kind 1 / 1, interleave 2, where
+ * a tile fits, but with every link entry read), and smpq_get_tuning reports those of a large batch. */
 smpq_status smpq_autotune(smpq_ctx *ctx, int n_rhs, smpq_tuning *chosen);
 
 /* Select the variants explicitly.  SMPQ_EINVAL (previous choice kept) if a variant is not

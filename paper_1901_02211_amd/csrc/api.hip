@@ -219,8 +219,8 @@ struct smpq_ctx {
     long long gen = 1;
     int *h_count = nullptr;     // pinned
     // stencil variant (see Geom)
-    int f32_kind = 0, f32_nr = 2, f64_lgr = 0, band = 1, f64_kind = 0, f64_nr = 1, f32_il = 1, f64_il = 1;
-    int f32_dag_kind = 0, f32_dag_nr = 2, f32_dag_il = 1;   // the D_W^dag launches
+    int f32_kind = 0, f32_nr = 1, f64_lgr = 0, band = 1, f64_kind = 0, f64_nr = 1, f32_il = 1, f64_il = 1;
+    int f32_dag_kind = 0, f32_dag_nr = 1, f32_dag_il = 1;   // the D_W^dag launches
     bool adapt = true;       // no stencil variant chosen by smpq_autotune or smpq_set_tuning
     bool f64_full = false;   // a loaded link's third row is further than rounding from the other two's product
     Geom geom() const {
@@ -2444,6 +2444,7 @@ smpq_status smpq_autotune(smpq_ctx *c, int n_rhs, smpq_tuning *chosen) {
         };
         std::vector<Cand> cand = {{0, 2, 1, 1}, {0, 4, 1, 1}, {0, 8, 1, 1}};
         const Geom g0 = c->geom();
+        if (g0.tile_y == 0) cand.push_back({0, 1, 1, 1});   // the default there; else kind 4 / 1 is the same tile
         for (int kind = 1; kind <= 4; ++kind) {
             if (kind == 2 || kind == 4 ? g0.tile_y == 0 : !plane_tileable(g0)) continue;
             for (int nr : kind == 4 ? std::vector<int>{1, 2, 4, 8} : std::vector<int>{4, 8, 16})

@@ -914,6 +914,9 @@ static Geom for_direction(const Geom &g, int prec, bool dag) {
 //    24^4: 0.75 against 1.20)
 //  - FP64: links read for every right-hand side, two in turn where a tile is one wave
 //    (8^4: 0.226 ms a pair of stencils against 0.239)
+//  - any-lattice tiles in FP32: one right-hand side per block; two per link read leave half as many blocks
+//    and are 0 to 20 % slower in whole solves of 12 to 96 right-hand sides (10^4 x 12 12.6 ms against
+//    10.9, 6 x 10 x 6 x 14 x 96 30.5 against 28.2) and within 2 % with more (12^4 x 192 202 against 205)
 //  - tiles: exact ones where they fit, else kTileAny (12^4 in FP64 0.416 ms a pair of stencils
 //    against 0.449 without LDS and with right-hand sides interleaved over the lanes)
 //  - two right-hand sides of a tile in a row (interleave 2) wherever links are read for one or two
@@ -976,7 +979,7 @@ static bool valid_f32(const Geom &g) {
     if (g.f32_kind == 2) return tiled && nr_tile && band_ok;
     if (g.f32_kind == 4)
         return tiled && band_ok && (g.f32_nr == 1 || g.f32_nr == 2 || g.f32_nr == 4 || g.f32_nr == 8) && il_ok(g.f32_il);
-    return g.f32_kind == 0 && (g.f32_nr == 2 || g.f32_nr == 4 || g.f32_nr == 8);
+    return g.f32_kind == 0 && (g.f32_nr == 1 || g.f32_nr == 2 || g.f32_nr == 4 || g.f32_nr == 8);
 }
 
 // The kernels that read the links for every turn, nr right-hand sides per block.

@@ -62,3 +62,22 @@ def test_rounded_vectors_do_not_depend_on_the_block(prec, reliable, check):
                 got = (e.status,)
             want = want or got
             assert got == want, k
+
+
+@pytest.mark.parametrize("dims", [(12, 12, 4, 3), (6, 10, 4, 2), (130, 4, 4, 1), (8, 8, 4, 4), (16, 16, 4, 4)])
+def test_reported_and_autotuned_variants_give_the_default_results(dims):
+    """The variant that a context reports, and the one that the autotuner picks, set explicitly: mixed D_ov and
+    FP32 D_W equal to those of the default variants bit for bit."""
+    print(f"reported and autotuned variants on {dims}", flush=True)
+    psi = si.random_spinors(dims, 3, 4)
+    d = _ctx(dims, 1)
+    reported = smpq.smpq_get_tuning(d)
+    for pick in (False, True):
+        c = _ctx(dims, 1)
+        if pick:
+            t = smpq.smpq_autotune(c, 12)
+            assert t["f32_kind"] in ((0,) if dims[0] in (12, 6, 130) else (0, 1, 2, 3, 4)), t
+        else:
+            smpq.smpq_set_tuning(c, **reported)
+        assert np.array_equal(smpq.smpq_apply_dw(c, psi, precision=1), smpq.smpq_apply_dw(d, psi, precision=1))
+        assert np.array_equal(smpq.smpq_apply_dov(c, psi), smpq.smpq_apply_dov(d, psi))

@@ -35,3 +35,23 @@ def test_any_lattice_variant_takes_any_band(band):
             with pytest.raises(smpq.SmpqError) as e:
                 smpq.smpq_set_tuning(c, *args)
             assert e.value.status == -1
+
+
+@pytest.mark.parametrize("dims", [(12, 12, 12, 12), (6, 10, 6, 14), (130, 4, 2, 2), (3, 3, 3, 3), (1, 5, 3, 4)])
+def test_reported_default_is_the_one_in_use_without_a_tile(dims):
+    """Without a tile every default launch takes the any-lattice kernel with one right-hand side per block: a
+    context reports that, and accepts what it reports."""
+    c = smpq.smpq_create(dims, -1)
+    t = smpq.smpq_get_tuning(c)
+    assert (t["f32_kind"], t["f32_nr"], t["f32_dag_kind"], t["f32_dag_nr"]) == (0, 1, 0, 1)
+    assert (t["f64_kind"], t["f64_lgr"]) == (0, 0)
+    smpq.smpq_set_tuning(c, **t)
+    assert smpq.smpq_get_tuning(c) == t
+
+
+@pytest.mark.parametrize("dims", [(8, 8, 4, 4), (16, 16, 4, 4), (24, 24, 4, 4), (16, 32, 2, 2)])
+def test_reported_default_is_accepted_with_a_tile(dims):
+    c = smpq.smpq_create(dims, -1)
+    t = smpq.smpq_get_tuning(c)
+    smpq.smpq_set_tuning(c, **t)
+    assert smpq.smpq_get_tuning(c) == t
