@@ -116,7 +116,7 @@ typedef struct {
 } smpq_stats;
 
 /* Environment: SMPQ_TRACE (any value) when a context is created makes it print one line per
- * device batch to stderr (sources, CG iterations, solve time). */
+ * device batch to stderr (sources, iterations per block update, CG iterations, solve time). */
 
 /* Create a context for a lattice dims[4] = {nx, ny, nz, nt} on HIP device `device`
  * (-1: host only).  kappa starts at 0.21 (section 1), the solver at FP64 with

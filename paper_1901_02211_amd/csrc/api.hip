@@ -1347,8 +1347,8 @@ void qx_classes(smpq_ctx *c, const std::vector<int> &classes, bool point, smpq_s
         HIPCHK(hipGetLastError());
         HIPCHK(hipStreamSynchronize(c->stream));
         if (c->trace)
-            std::fprintf(stderr, "smpq: batch of %d sources on V = %d: %lld iterations (max %lld), %.3f s solve\n",
-                         12 * nc, c->V, r.iters_sum, r.iters_max, t1 - t0);
+            std::fprintf(stderr, "smpq: batch of %d sources on V = %d in blocks of %d: %lld iterations (max %lld), "
+                         "%.3f s solve\n", 12 * nc, c->V, w.K, r.iters_sum, r.iters_max, t1 - t0);
         if (st) {
             st->t_solve_s += t1 - t0;
             st->t_contract_s += now_s() - t1;

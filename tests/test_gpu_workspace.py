@@ -1,5 +1,6 @@
 """GPU: the workspace of a context when memory runs short or its options change."""
 import ctypes
+import re
 
 import numpy as np
 import pytest
@@ -106,3 +107,29 @@ def test_locality_and_deflation_keep_to_the_limit(vectors):
         smpq.smpq_deflate(c, 1, 4)                     # too few steps: refused after the solves
     assert e.value.status == -5
     assert free - mem.free() <= 4 * vec + 4 * vec + small      # and the four vectors of the bounds
+
+
+@pytest.mark.parametrize("check", [False, True])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_limits_pick_the_block_lengths(prec, check, monkeypatch, capfd):
+    """A limit with room for K residuals a source gives blocks of K iterations, and every length the same
+    q(x).  In mixed precision K = 2 needs the check: without it five residuals leave room for the reliable
+    updates' two FP64 vectors and take less memory than two with these vectors beside them."""
+    monkeypatch.setenv("SMPQ_TRACE", "1")
+    c = _ctx(prec, (6, 4, 4, 6))
+    if check:
+        smpq.smpq_set_shift_check(c, True, 0.0)
+    vec, ns, want = 192 * 768, 14, None
+    capfd.readouterr()
+    for k in (50, 20, 10, 5, 2, 1):
+        n = k + 1 + ns + (k > 1)
+        if prec == 0:
+            slot = (n + 1) * vec + (ns + 4) * vec * check
+        else:
+            slot = n * vec // 2 + (2 if k >= 5 and not check else 4) * vec + (ns + 2) * vec * check
+        smpq.smpq_set_memory_limit(c, 12 * slot)
+        got = smpq.smpq_compute_qx_classes(c, [5])
+        used = [int(v) for v in re.findall(r"blocks of (\d+)", capfd.readouterr().err)]
+        assert used == [5 if k == 2 and prec == 1 and not check else k]
+        want = want if want is not None else got[0]
+        assert np.array_equal(got[0], want), k
