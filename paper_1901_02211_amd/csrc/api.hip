@@ -556,10 +556,11 @@ BatchPlan choose_batch(smpq_ctx *c, int prec, int NS, int total_slots, bool mult
                 break;
             }
         }
-    // A workspace with room for every source and a block of 10 or more is kept as it is: laying out
-    // one that takes most of the device costs 5 s, more than the longer block saves a small call.
+    // A workspace with room for every source is kept as it is if its block has 10 iterations or more, or
+    // if it takes more than a quarter of the device: laying out one that takes most of it costs 5 s,
+    // more than the longer block saves a small call, and the next large call would lay it out again.
     const long long all = c->max_rhs > 0 ? std::min(c->max_rhs, total_slots) : total_slots;
-    if (reuse && w.K >= kGroup && w.B >= all) K = w.K;
+    if (reuse && w.B >= all && (w.K >= kGroup || (double)held > 0.25 * (double)totalb)) K = w.K;
     const long long B = most(K);
     if (B < q) throw Fail{SMPQ_ENOMEM, "not enough device memory for one batch of right-hand sides"};
     // spread the right-hand sides evenly over the batches this limit implies

@@ -133,3 +133,21 @@ def test_limits_pick_the_block_lengths(prec, check, monkeypatch, capfd):
         assert used == [5 if k == 2 and prec == 1 and not check else k]
         want = want if want is not None else got[0]
         assert np.array_equal(got[0], want), k
+
+
+def test_large_workspace_outlives_a_small_call(monkeypatch, capfd):
+    """A map's workspace of 90 GB in blocks of 5 (more batches with longer ones) serves a call with one
+    source class as it is."""
+    print("a small call beside a large workspace", flush=True)
+    want = smpq.smpq_compute_qx_points(_ctx(1), [7])[0]
+    monkeypatch.setenv("SMPQ_TRACE", "1")
+    c, mem = _ctx(1), Memory()
+    smpq.smpq_set_point_scheme(c)
+    smpq.smpq_set_memory_limit(c, 90 * 10 ** 9)
+    smpq.smpq_prepare(c)
+    free = mem.free()
+    capfd.readouterr()
+    got = smpq.smpq_compute_qx_points(c, [7])[0]
+    assert re.findall(r"blocks of (\d+)", capfd.readouterr().err) == ["5"]
+    assert abs(mem.free() - free) < 1 << 30
+    assert np.array_equal(got, want)
