@@ -77,7 +77,7 @@ def kernel_source_hash():
 
 
 # names of the FP32 stencil variants, by the tuning's kind number
-F32_KINDS = ("site", "plane", "xy-tile", "plane, xy links in LDS", "xy-tile, links read per right-hand side")
+F32_KINDS = ("any lattice", "plane", "xy-tile", "plane, xy links in LDS", "xy-tile, links read per right-hand side")
 
 
 def measured_traffic(kernel, workload):
@@ -467,7 +467,7 @@ def main():
                    "stencil_variants": {"f32_kind": F32_KINDS[tuning["f32_kind"]],
                                         "f32_rhs_per_thread": tuning["f32_nr"],
                                         "plane_band": tuning["plane_band"],
-                                        "f64_kind": ["lanes", "xy-tile"][tuning.get("f64_kind", 0)],
+                                        "f64_kind": ["any lattice", "xy-tile"][tuning.get("f64_kind", 0)],
                                         "f64_rhs_per_block": (tuning["f64_nr"] if tuning.get("f64_kind", 0) == 1
                                                               else 1 << tuning["f64_lgr"]),
                                         "f32_interleave": tuning.get("f32_interleave", 1),

@@ -445,8 +445,9 @@ typedef struct {
  * *chosen (may be NULL); on an error the previous choice is kept.  Without this call or
  * smpq_set_tuning every launch takes a variant by the lattice and its number of right-hand sides
  * (on 16 x 16 planes kind 1 / 8 for D_W and kind 4 / 2, interleave 2, for D_W^dag; kind 4 / 1 on
- * other tiles and with few right-hand sides; else kind 0 / 1; FP64 kind 1 / 1, interleave 2, where
- * a tile fits, but with every link entry read), and smpq_get_tuning reports those of a large batch. */
+ * other tiles and with few right-hand sides; else kind 0 / 1; FP64 kind 1 / 1, interleave 2 or, on
+ * 16 x 16 planes, 4, where a tile fits, but with every link entry read, else kind 0, interleaved by
+ * two itself), and smpq_get_tuning reports those of a large batch. */
 smpq_status smpq_autotune(smpq_ctx *ctx, int n_rhs, smpq_tuning *chosen);
 
 /* Select the variants explicitly.  SMPQ_EINVAL (previous choice kept) if a variant is not

@@ -1556,7 +1556,7 @@ smpq_status smpq_create(const int dims[4], int device, smpq_ctx **out) {
     if (tile_rows(dims[0], dims[1]) > 0) {
         const bool plane = dims[0] * dims[1] == 256;
         c->f64_kind = 1;
-        c->f64_il = 2;
+        c->f64_il = plane ? 4 : 2;
         c->f32_kind = plane ? 1 : 4;
         c->f32_nr = plane ? 8 : 1;
         c->f32_il = plane ? 1 : 2;
@@ -2504,7 +2504,7 @@ smpq_status smpq_autotune(smpq_ctx *c, int n_rhs, smpq_tuning *chosen) {
             c->f32_dag_kind = b.k2.kind;
             c->f32_dag_nr = b.k2.nr;
             c->f32_dag_il = b.k2.il;
-            // FP64: lanes interleaving 1, 2 or 4 right-hand sides; xy-tiles with 2, 4 or 8 per
+            // FP64: the any-lattice kernel with 1, 2 or 4 right-hand sides; xy-tiles with 1 to 8 per
             // block (same plane order band as the FP32 choice) where a tile fits
             double best = INFINITY;
             struct Cand64 {
@@ -2524,7 +2524,7 @@ smpq_status smpq_autotune(smpq_ctx *c, int n_rhs, smpq_tuning *chosen) {
                 const double t = std::min(time_dslash(c, tb, 0, n_rhs, 2, 10, &by, 1),
                                           time_dslash(c, tb, 0, n_rhs, 2, 10, &by, 1));
                 if (c->trace)
-                    std::fprintf(stderr, "smpq: autotune FP64 kind %d, lanes 2^%d / %d per block, interleave %d: "
+                    std::fprintf(stderr, "smpq: autotune FP64 kind %d, 2^%d (kind 0) or %d (kind 1) per block, interleave %d: "
                                  "%.3f ms per pair (%.0f GB/s) on %d right-hand sides\n", k.kind, k.lgr, k.nr, k.il, t,
                                  by / t * 1e-6, std::min(n_rhs, tb.n_rhs));
                 if (t < best) {

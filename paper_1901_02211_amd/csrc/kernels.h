@@ -17,15 +17,14 @@ constexpr int kBlock = 256;
 struct Geom {
     int nx, ny, nz, nt, V;
     size_t vs;
-    // stencil tuning (chosen per lattice, see smpq_autotune): FP32 kernel kind (0: one site per
-    // thread, 1: 16x16 xy-plane per block in LDS, 2: xy-tile of tile_y rows with y-halos in
-    // LDS), FP32 right-hand sides per thread, log2 of the right-hand sides interleaved over the
-    // lanes of an FP64 block, and the z-band of the plane order of kinds 1 and 2;
-    // tile_y = tile_rows(nx, ny) (0 when no tile fits); FP64 kernel kind (0: any lattice, 2^f64_lgr
-    // right-hand sides per block; 1: xy-tiles in LDS like the FP32 kind 2, f64_nr right-hand sides
-    // per block; the links are read per right-hand side); f32_il / f64_il: in
-    // the tile kernels (FP32 kind 4, FP64 kind 1) consecutive blocks take that many groups of
-    // right-hand sides of one tile before the next tile, so that the tile's links are still in L2
+    // stencil variants (smpq_tuning in smpq.h).  f32_kind: 0 any lattice, f32_nr right-hand sides per
+    // block; 1 and 3 a 16x16 xy-plane per block in LDS, links in registers for f32_nr sides (3: x and y
+    // links in LDS); 2 xy-tiles of tile_y rows with halo rows, links in registers; 4 the same tiles, links
+    // read for every side or every two.  f64_kind: 0 any lattice, 2^f64_lgr sides per block; 1 xy-tiles,
+    // f64_nr per block.  band: z-band of the plane order of kinds 1 to 4.  tile_y = tile_rows(nx, ny) (0
+    // when no tile fits).  f32_il / f64_il: in FP32 kind 4 and FP64 kind 1 consecutive blocks take that
+    // many groups of right-hand sides of one tile before the next tile, so that the tile's links are
+    // still in L2
     int f32_kind, f32_nr, f64_lgr, band, tile_y;
     int f64_kind, f64_nr;
     int f32_il, f64_il;
@@ -127,10 +126,10 @@ void launch_dslash(int prec, bool dag, int epi, const void *U, const void *in, s
 bool dslash_takes_partials(int prec, const Geom &g, bool dag);   // the variant can compute alpha itself
 __host__ __device__ int site_blocks(const Geom &g);   // blocks of 256 sites
 int dslash_partials(int prec, const Geom &g, bool dag);   // partials per slot of the stencil epilogue
-bool plane_tileable(const Geom &g);
+bool plane_tileable(const Geom &g);   // the xy-plane has exactly 256 sites
 // Rows per xy-tile: the largest divisor ty >= 2 of ny with nx * ty <= 256 and a multiple of 64
 // (nx <= 64); 0 when there is none.
-int tile_rows(int nx, int ny);                    // the xy-plane has exactly 256 sites
+int tile_rows(int nx, int ny);
 bool valid_tuning(int prec, const Geom &g);            // g's tuning names an instantiated variant
 int unit_parts(int prec, const Geom &g);        // partials per slot written by element-wise kernels
 size_t partial_stride(const Geom &g);           // slot stride of the partial buffer (>= both)

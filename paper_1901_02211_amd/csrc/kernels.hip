@@ -919,7 +919,10 @@ static Geom for_direction(const Geom &g, int prec, bool dag) {
 //    10.9, 6 x 10 x 6 x 14 x 96 30.5 against 28.2) and within 2 % with more (12^4 x 192 202 against 205)
 //  - tiles: exact ones where they fit, else kTileAny (12^4 in FP64 0.416 ms a pair of stencils
 //    against 0.449 without LDS and with right-hand sides interleaved over the lanes)
-//  - two right-hand sides of a tile in a row (interleave 2) wherever links are read for one or two
+//  - two right-hand sides of a tile in a row (interleave 2) wherever links are read for one or two, in FP64
+//    four on 16 x 16 planes: whole FP64 links then come from L2 more often (four 12^4 classes 115 -> 105 ms
+//    and 48 right-hand sides on 130 x 4^3 69 -> 61 with 2 against 1, 16^4 classes 324 -> 315 with 4
+//    against 2; four on 24^4, tiles with halo rows, 822 -> 873); FP32 kind 0 takes 1
 // Results do not depend on the choice.
 static Geom adapted(Geom d, int prec, bool dag, int n) {
     const bool exact = d.tile_y > 0;
@@ -928,7 +931,7 @@ static Geom adapted(Geom d, int prec, bool dag, int n) {
         d.f64_kind = exact ? 1 : 0;
         d.f64_lgr = 0;
         d.f64_nr = exact && d.nx * d.tile_y == 64 && (long long)tile_blocks(d) * n >= 16 * 256 ? 2 : 1;
-        d.f64_il = exact ? il : 1;
+        d.f64_il = exact && plane_tileable(d) && n >= 4 ? 4 : il;
         return d;
     }
     const long long work = exact ? (long long)tile_blocks(d) * n : 0;   // tiles x right-hand sides
@@ -1019,8 +1022,8 @@ static void launch_rl(bool exact, const void *U, const void *in, size_t in_strid
         // (epilogues 2 and 3) rebuild third rows where those of the loaded links are within rounding of it;
         // D_W itself and H^2 + sigma keep the links as loaded.  A rebuilt row takes the error of D_W from
         // 1.7e-16 to 4.8e-16 of its largest entry, and that of D_ov at the finest tolerance from
-        // 4.31e-15 to 4.38e-15, for 2 to 10 % of an FP64 solve (four 16^4 classes, r = 4: 312 ms in
-        // full, 289 with two rows; four points on 12^4 110 and 99).
+        // 4.31e-15 to 4.38e-15, for up to 4 % of an FP64 solve (four 16^4 classes, r = 4: 303 ms in full, 290
+        // with two rows; four points on 12^4 99.8 and 99.0).
         const bool rows = (EPI == 2 || EPI == 3) && exact && !g.adapt && !g.f64_full;
         if constexpr (EPI == 2 || EPI == 3) {
             if (rows && nr == 1) return go(launch_rl_t<double, 1, DAG, EPI, kTileExact, false, true>);
@@ -1048,7 +1051,7 @@ static void launch_dslash_t(const void *U, const void *in, size_t in_stride, siz
                             const ResidualStep &rstep, const int *done, hipStream_t st) {
     const bool lds = g.f64_kind == 1;
     launch_rl<T, DAG, EPI>(lds, U, in, in_stride, in_extra, out, out_stride, aux, aux_stride, aux_extra, g,
-                           lds ? g.f64_nr : 1 << g.f64_lgr, lds ? g.f64_il : 1, kappa, sigma, sl, max_slots, partial,
+                           lds ? g.f64_nr : 1 << g.f64_lgr, g.f64_il, kappa, sigma, sl, max_slots, partial,
                            rstep, done, st);
 }
 

@@ -81,3 +81,17 @@ def test_reported_and_autotuned_variants_give_the_default_results(dims):
             smpq.smpq_set_tuning(c, **reported)
         assert np.array_equal(smpq.smpq_apply_dw(c, psi, precision=1), smpq.smpq_apply_dw(d, psi, precision=1))
         assert np.array_equal(smpq.smpq_apply_dov(c, psi), smpq.smpq_apply_dov(d, psi))
+
+
+@pytest.mark.parametrize("dims", [(12, 12, 4, 3), (6, 10, 4, 2), (130, 4, 2, 2), (16, 16, 4, 2), (24, 24, 2, 2), (8, 8, 4, 4)])
+def test_interleaved_sides_equal_single_ones(dims):
+    """Default FP64 launches take two or four right-hand sides of a tile in a row, the last group maybe in part:
+    D_W and D_ov of 1 to 7 sides equal those of each side alone bit for bit."""
+    print(f"interleaved right-hand sides on {dims}", flush=True)
+    psi = si.random_spinors(dims, 7, 4)
+    c = _ctx(dims, 0)
+    one = [np.concatenate([f(psi[i:i + 1]) for i in range(7)]) for f in
+           (lambda p: smpq.smpq_apply_dw(c, p), lambda p: smpq.smpq_apply_dov(c, p))]
+    for n in (2, 3, 4, 5, 7):
+        assert np.array_equal(smpq.smpq_apply_dw(c, psi[:n]), one[0][:n])
+        assert np.array_equal(smpq.smpq_apply_dov(c, psi[:n]), one[1][:n])
