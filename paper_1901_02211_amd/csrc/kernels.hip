@@ -912,13 +912,13 @@ static Geom for_direction(const Geom &g, int prec, bool dag) {
 //  - D_W^dag in FP32: links read per pair on 256-site tiles where that leaves eight blocks per CU
 //    (1.33 ms against 1.75 with kind 1), else for every right-hand side (8^4: 0.070 against 0.149,
 //    24^4: 0.75 against 1.20)
-//  - FP64: links read for every right-hand side, two in turn where a tile is one wave
-//    (8^4: 0.226 ms a pair of stencils against 0.239)
+//  - FP64: links read for every right-hand side, two in turn where a tile is one wave and there are
+//    many (a whole 8^4 map 74.4 ms against 76.9; 24^4, larger tiles: 901 against 822)
 //  - any-lattice tiles in FP32: one right-hand side per block; two per link read leave half as many blocks
 //    and are 0 to 20 % slower in whole solves of 12 to 96 right-hand sides (10^4 x 12 12.6 ms against
 //    10.9, 6 x 10 x 6 x 14 x 96 30.5 against 28.2) and within 2 % with more (12^4 x 192 202 against 205)
-//  - tiles: exact ones where they fit, else kTileAny (12^4 in FP64 0.416 ms a pair of stencils
-//    against 0.449 without LDS and with right-hand sides interleaved over the lanes)
+//  - tiles: exact ones where they fit, else kTileAny (12^4 in FP64, two-row links: 0.416 ms a pair of
+//    stencils against 0.449 without LDS and with right-hand sides interleaved over the lanes)
 //  - two right-hand sides of a tile in a row (interleave 2) wherever links are read for one or two, in FP64
 //    four on 16 x 16 planes: whole FP64 links then come from L2 more often (four 12^4 classes 115 -> 105 ms
 //    and 48 right-hand sides on 130 x 4^3 69 -> 61 with 2 against 1, 16^4 classes 324 -> 315 with 4
@@ -1564,7 +1564,7 @@ void launch_base_direction(int prec, const Geom &g, const MSState &s, const void
 // each leave most of the chip idle.  The vector that the stencil reads is in LDS, the residuals and
 // links come from L2, and the first wave advances the shifts' recurrences.  Bound by the latency of
 // one or two waves per SIMD (LDS, links, reductions).  A whole 4^4 map of 192 right-hand sides:
-// FP64 11.1 -> 4.2 ms; 96 point sources on 420 sites (two tiles) in FP64 5.9 ms, mixed 4.0 ms
+// FP64 11.1 -> 4.2 ms; 96 point sources on 420 sites (two tiles) in FP64 6.7 ms, mixed 3.9 ms
 // against about 10 in separate launches.
 // The sums have the order of the separate kernels (tiles of the stencil's blocks, their waves, one
 // wave over the tiles), so that results are equal bit for bit.
