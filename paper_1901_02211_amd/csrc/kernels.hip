@@ -1564,7 +1564,7 @@ void launch_base_direction(int prec, const Geom &g, const MSState &s, const void
 // each leave most of the chip idle.  The vector that the stencil reads is in LDS, the residuals and
 // links come from L2, and the first wave advances the shifts' recurrences.  Bound by the latency of
 // one or two waves per SIMD (LDS, links, reductions).  A whole 4^4 map of 192 right-hand sides:
-// FP64 11.1 -> 4.2 ms; 96 point sources on 420 sites (two tiles) in FP64 6.7 ms, mixed 3.9 ms
+// FP64 11.1 -> 4.2 ms; 96 point sources on 420 sites (two tiles) in FP64 6.5 ms, mixed 3.9 ms
 // against about 10 in separate launches.
 // The sums have the order of the separate kernels (tiles of the stencil's blocks, their waves, one
 // wave over the tiles), so that results are equal bit for bit.
@@ -1644,10 +1644,9 @@ __global__ __launch_bounds__(MAXT) void k_cg_small(const typename Store<T>::link
     };
     cpx<T> acc[12], u[9], q[12], h[6], w[6];
     // D_W or D_W^dag of the field at the own site, q = the field there
-    // Each link is loaded one hop ahead (its rows as stored), since one or two waves per SIMD hide
-    // little of the latency of L2; in FP64 only up to 256 threads, whose registers hold two links of
-    // 36 (on 512 threads 139-192 were spilled, a
-    // map of four classes on 4^3 x 8 8.7 ms against 6.9 so).
+    // Each link is loaded one hop ahead (its rows as stored), since one or two waves per SIMD hide little
+    // of the latency of L2; in FP64 only up to 256 threads, whose registers hold two links of 36 (on 512
+    // threads 139-192 were spilled, a map of four classes on 4^3 x 8 8.7 ms against 6.8 so).
     constexpr bool kAhead = std::is_same<T, float>::value || MAXT <= 256;
     [[maybe_unused]] RawLink<T> l0, l1;
 #define SMPQ_SMALL_HOP(MU, SF, CUR, LSITE, NEXT, NMU, NSITE, SITE, MUL, FIRST)       \
@@ -1718,7 +1717,11 @@ __global__ __launch_bounds__(MAXT) void k_cg_small(const typename Store<T>::link
             d = 0.0;
         }
         const double rrn = total(d, 1);
+        // the next direction goes to the field first, so that no spinor is held beside the recurrences
         const T b = (T)(rrn / rr);
+#pragma unroll
+        for (int c = 0; c < 12; ++c) q[c] = next_direction(T(1), q[c], b, p[c]);
+        put(q);
         if (wv == 0) {
             ShiftLane sh = shifts[lane];
             const bool still = sh.template advance<T>(S, slot, a, rr, rrn);
@@ -1726,16 +1729,14 @@ __global__ __launch_bounds__(MAXT) void k_cg_small(const typename Store<T>::link
             else shifts[lane] = sh;
             if (lane == 0 && !still) finished = 1;
         }
-#pragma unroll
-        for (int c = 0; c < 12; ++c) q[c] = next_direction(T(1), q[c], b, p[c]);
         rr = rrn;
-        put(q);
         __syncthreads();
         if (finished) return;   // uniform over the block; its direction is not needed any more
     }
 #undef SMPQ_SMALL_HOPS
 #undef SMPQ_SMALL_HOP
     if (ok_site) {
+        tile_read(field, s, q);
 #pragma unroll
         for (int k = 0; k < UN; ++k) unit_store_stream(p_out + slot * pst, g.vs, k, s, q + k * CU);
     }
